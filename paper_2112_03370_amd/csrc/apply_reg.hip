@@ -107,6 +107,36 @@ __device__ __forceinline__ void dft32(float2 (&v)[32]) {
   }
 }
 
+// The middle half (outputs 8..23) of the radix-32 DFT of v, into v[8..24).  The last step of the
+// inverse needs no more: outputs start lambda >= 2^13 samples into the window, end as far before
+// its end, and slot j holds the window's points t + 512 j.
+__device__ __forceinline__ void dft32_middle(float2 (&v)[32]) {
+  float2 e[16], o[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    e[i] = v[2 * i];
+    o[i] = v[2 * i + 1];
+  }
+  dft<16>(e);
+  dft<16>(o);
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const float2 E = e[out_slot<16>(k)];
+    float2 O = o[out_slot<16>(k)];
+    if (k == 8)
+      O = mul_mi(O);
+    else if (k != 0)
+      O = cmul(O, make_float2(kCos32[k], -kSin32[k]));
+    // O is rounded before the sum, as in the full transform (where it has two uses): with one use
+    // the compiler would fold the sum into O's own multiply-adds and change its last bits.
+    asm("" : "+v"(O.x), "+v"(O.y));
+    if (k >= 8)
+      v[k] = cadd(E, O);
+    else
+      v[k + 16] = csub(E, O);
+  }
+}
+
 // Radix-16 DFT on v[off..off+16) in natural order.
 template <int OFF>
 __device__ __forceinline__ void dft16_at(float2 (&v)[32]) {
@@ -431,26 +461,20 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(4))) void k_
   transpose_ba<0>(v, lds, tid, k3b, n1b);
   transpose_ba<1>(v, lds, tid, k3b, n1b);
   twiddle_a(v, tid, tw0, tw1);
-  dft32(v);
+  dft32_middle(v);
 
   // ---- outputs to LDS: sample 2m is Re, 2m+1 is -Im of point m = t + 512 j ------------------
   const int out_len = c.out_len;
-  if ((lam & 1) == 0) {
+  if (lam == kHalf / 2 && out_len == kHalf) {  // every middle point is an output pair
 #pragma unroll
-    for (int j = 0; j < 32; ++j) {
-      const int i = 2 * (tid + kT * j) - lam;  // even
-      if (i >= 0 && i + 1 < out_len) {
-        *reinterpret_cast<float2*>(lds + i) = make_float2(v[j].x, -v[j].y);
-      } else if (i >= 0 && i < out_len) {
-        lds[i] = v[j].x;
-      }
-    }
+    for (int j = 8; j < 24; ++j)
+      *reinterpret_cast<float2*>(lds + 2 * (tid + kT * (j - 8))) = make_float2(v[j].x, -v[j].y);
   } else {
 #pragma unroll
-    for (int j = 0; j < 32; ++j) {
+    for (int j = 8; j < 24; ++j) {
       const int i = 2 * (tid + kT * j) - lam;
-      if (i >= 0 && i < out_len) lds[i] = v[j].x;
-      if (i + 1 >= 0 && i + 1 < out_len) lds[i + 1] = -v[j].y;
+      if (static_cast<unsigned>(i) < static_cast<unsigned>(out_len)) lds[i] = v[j].x;
+      if (static_cast<unsigned>(i + 1) < static_cast<unsigned>(out_len)) lds[i + 1] = -v[j].y;
     }
   }
   __syncthreads();
