@@ -31,17 +31,26 @@ using namespace fft;
 constexpr int kGatherLane = 8;
 constexpr int kScatterLane = 8;
 
+// Runs listed per wavefront and scatter round.  The list lives in the wavefront's own outputs, which
+// it has read by then: from the complex point after its slice's first (with odd lambda the first
+// and last are shared with the neighbouring wavefronts) on.  A slice that starts within 256
+// samples of the window's end may reach past it: at most kListSlack points.
+constexpr int kListed = 64;
+constexpr int kListSlack = 96;
+static_assert(run_list_bytes<3, kListed>() <= 254 * sizeof(float2),
+              "run list must fit between the shared points of a slice");
+
 template <int LOG, bool kFromData>
 __global__ __launch_bounds__(FftCfg<LOG>::T) void k_apply_fused(
     const int32_t* __restrict__ lpix, const float* __restrict__ wq, const float* __restrict__ wu,
-    const double* __restrict__ x0, const float* __restrict__ d0, int d_vec, double* __restrict__ y0,
+    const double* __restrict__ x0, const float* __restrict__ d0, double* __restrict__ y0,
     int ncol, int64_t ldx, int64_t ldy, const Chunk* __restrict__ chunks,
     const float* __restrict__ spec,
     const float2* __restrict__ tw0g, const float2* __restrict__ tw1g, int lam,
     const int32_t* __restrict__ done) {
   using C = FftCfg<LOG>;
   constexpr int NC = C::NC, N = C::N, T = C::T;
-  __shared__ float2 buf[C::LDS];
+  __shared__ float2 buf[C::LDS + kListSlack];
   __shared__ float2 tw0[128];
   __shared__ float2 tw1[N / 128];
   if (done != nullptr && *done) return;
@@ -57,8 +66,9 @@ __global__ __launch_bounds__(FftCfg<LOG>::T) void k_apply_fused(
   const double* __restrict__ x = kFromData ? x0 : x0 + col * ldx;
   const float* __restrict__ d = kFromData ? d0 + col * ldx : d0;
   double* __restrict__ y = y0 + col * ldy;
-  const int64_t in0 = c.out0 - lam;
-  const int64_t b0 = c.blk_start, b1 = c.blk_start + c.blk_len;
+  const SegmentStreams win = segment_streams(lpix, wq, wu, d, c.out0 - lam);
+  int lo, hi;
+  window_range(c, lam, N, lo, hi);
 
   // ---- gather the N-sample window (zero outside the block) ---------------------------------
   // Four rounds of T SG samples, one window quarter each.  With N = 4 lambda the right half of
@@ -71,21 +81,8 @@ __global__ __launch_bounds__(FftCfg<LOG>::T) void k_apply_fused(
   const int rot = ((wg / ncol) & 1) == 0 ? 2 : 0;
   for (int rr = 0; rr < 4; ++rr) {
     const int n = ((rr + rot) & 3) * (T * SG) + tid * SG;
-    const int64_t g = in0 + n;
     float v[SG];
-    if (g >= b0 && g + SG <= b1 && (g & 3) == 0 && (!kFromData || d_vec)) {
-      LanePointing<SG, kFromData> lane;
-      lane.load(lpix, wq, wu, d, g);
-      lane.resolve(x, v);
-    } else {
-#pragma unroll
-      for (int j = 0; j < SG; ++j) {
-        const int64_t gj = g + j;
-        v[j] = 0.0f;
-        if (gj >= b0 && gj < b1)
-          v[j] = gather_one<kFromData>(lpix[gj], wq[gj], wu[gj], x, kFromData ? d[gj] : 0.0f);
-      }
-    }
+    gather_lane<SG, kFromData>(win, x, n, lo, hi, v);
     // samples n..n+SG-1 are complex points n/2.. (n/2 even: contiguous pairs after padding)
     float2* dst = buf + pad(n >> 1);
 #pragma unroll
@@ -101,38 +98,26 @@ __global__ __launch_bounds__(FftCfg<LOG>::T) void k_apply_fused(
   // ---- scatter the segment's outputs ----------------------------------------------------------
   constexpr int SS = kScatterLane;
   const AtomicFlush flush{y};
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   for (int base = 0; base < c.out_len; base += T * SS) {  // same trip count for every lane
     const int i0 = base + tid * SS;
-    const int64_t o = c.out0 + i0;
-    int key[SS];
+    float u[SS];
+    LanePointing<SS, false> lane;
+    lane.load(win, lam + i0, lam, lam + c.out_len);
+#pragma unroll
+    for (int j = 0; j < SS; ++j)
+      u[j] = i0 + j < c.out_len ? real_out(buf, lam + i0 + j) : 0.0f;
+    lane.bridge_flags(u);
     double v[SS][3];
-    if (i0 + SS <= c.out_len && (o & 3) == 0) {
-      LanePointing<SS, false> lane;
-      lane.load(lpix, wq, wu, nullptr, o);
 #pragma unroll
-      for (int j = 0; j < SS; ++j) {
-        const double tv = real_out(buf, lam + i0 + j);
-        key[j] = lane.kk[j];
-        v[j][0] = tv;
-        v[j][1] = static_cast<double>(lane.qq[j]) * tv;
-        v[j][2] = static_cast<double>(lane.uu[j]) * tv;
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < SS; ++j) {
-        key[j] = -1;
-        v[j][0] = v[j][1] = v[j][2] = 0.0;
-        if (i0 + j < c.out_len) {
-          const int64_t oj = o + j;
-          key[j] = lpix[oj];
-          const double tv = real_out(buf, lam + i0 + j);
-          v[j][0] = tv;
-          v[j][1] = static_cast<double>(wq[oj]) * tv;
-          v[j][2] = static_cast<double>(wu[oj]) * tv;
-        }
-      }
+    for (int j = 0; j < SS; ++j) {
+      const double tv = u[j];
+      v[j][0] = tv;
+      v[j][1] = static_cast<double>(lane.qq[j]) * tv;
+      v[j][2] = static_cast<double>(lane.uu[j]) * tv;
     }
-    wave_merge_runs_n<SS, 3>(key, v, flush);
+    wave_merge_runs_listed<SS, 3, kListed>(
+        lane.kk, v, flush, buf + pad(((lam + base + 64 * SS * wave) >> 1) + 1));
   }
 }
 
@@ -140,17 +125,15 @@ template <int LOG>
 mm_status launch(Plan* P, const double* x, const float* d, int64_t ldx, double* y, int64_t ldy,
                  int ncol, const int32_t* done, hipStream_t s) {
   using C = FftCfg<LOG>;
-  const bool vec = (reinterpret_cast<uintptr_t>(d) & 15u) == 0 && (ldx & 3) == 0;
-  const int d_vec = vec ? 1 : 0;
   const int64_t grid = static_cast<int64_t>(P->n_chunks) * ncol;
   if (grid > INT32_MAX) return fail(MM_ERR_UNSUPPORTED, "too many segment x column workgroups");
   if (d != nullptr) {
     hipLaunchKernelGGL((k_apply_fused<LOG, true>), dim3(static_cast<unsigned>(grid)), dim3(C::T), 0,
-                       s, P->lpix, P->wq, P->wu, x, d, d_vec, y, ncol, ldx, ldy, P->chunks,
+                       s, P->lpix, P->wq, P->wu, x, d, y, ncol, ldx, ldy, P->chunks,
                        P->spec, P->tw0, P->tw1, P->lambda_max, done);
   } else {
     hipLaunchKernelGGL((k_apply_fused<LOG, false>), dim3(static_cast<unsigned>(grid)), dim3(C::T), 0,
-                       s, P->lpix, P->wq, P->wu, x, d, d_vec, y, ncol, ldx, ldy, P->chunks,
+                       s, P->lpix, P->wq, P->wu, x, d, y, ncol, ldx, ldy, P->chunks,
                        P->spec, P->tw0, P->tw1, P->lambda_max, done);
   }
   MM_HIP_TRY(hipGetLastError());

@@ -265,32 +265,15 @@ __device__ __forceinline__ void spectrum_self(float2& X, float sa, float sb, flo
   X = make_float2(p * X.x + q * X.y, -(p * X.y + q * X.x));
 }
 
-// Window samples [H kHalf, (H + 1) kHalf) (zero outside the block [b0, b1)) through LDS into
+// Window samples [H kHalf, (H + 1) kHalf) (zero outside the block's [lo, hi)) through LDS into
 // the A layout: z[t + 512 j] = (t[2m], t[2m+1]), m = t + 512 j, j in [16 H, 16 H + 16).
 template <int H, bool kFromData>
 __device__ __forceinline__ void gather_half(float2 (&v)[32], float* lds, int tid,
-                                            const int32_t* __restrict__ lpix,
-                                            const float* __restrict__ wq,
-                                            const float* __restrict__ wu,
-                                            const double* __restrict__ x,
-                                            const float* __restrict__ d, int d_vec, int64_t in0,
-                                            int64_t b0, int64_t b1) {
+                                            const SegmentStreams& win,
+                                            const double* __restrict__ x, int lo, int hi) {
   for (int n = tid * kLane; n < kHalf; n += kT * kLane) {
-    const int64_t g = in0 + H * kHalf + n;
     float s[kLane];
-    if (g >= b0 && g + kLane <= b1 && (g & 3) == 0 && (!kFromData || d_vec)) {
-      LanePointing<kLane, kFromData> lane;
-      lane.load(lpix, wq, wu, d, g);
-      lane.resolve(x, s);
-    } else {
-#pragma unroll
-      for (int j = 0; j < kLane; ++j) {
-        const int64_t gj = g + j;
-        s[j] = 0.0f;
-        if (gj >= b0 && gj < b1)
-          s[j] = gather_one<kFromData>(lpix[gj], wq[gj], wu[gj], x, kFromData ? d[gj] : 0.0f);
-      }
-    }
+    gather_lane<kLane, kFromData>(win, x, H * kHalf + n, lo, hi, s);
     *reinterpret_cast<float4*>(lds + n) = make_float4(s[0], s[1], s[2], s[3]);
     *reinterpret_cast<float4*>(lds + n + 4) = make_float4(s[4], s[5], s[6], s[7]);
   }
@@ -304,7 +287,7 @@ __device__ __forceinline__ void gather_half(float2 (&v)[32], float* lds, int tid
 template <bool kFromData>
 __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(4))) void k_apply_reg(
     const int32_t* __restrict__ lpix, const float* __restrict__ wq, const float* __restrict__ wu,
-    const double* __restrict__ x0, const float* __restrict__ d0, int d_vec, double* __restrict__ y0,
+    const double* __restrict__ x0, const float* __restrict__ d0, double* __restrict__ y0,
     int ncol, int64_t ldx, int64_t ldy, const Chunk* __restrict__ chunks,
     const float2* __restrict__ tab, const float2* __restrict__ tw0g,
     const float2* __restrict__ tw1g, int lam, const int32_t* __restrict__ done) {
@@ -330,8 +313,9 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(4))) void k_
   const double* __restrict__ x = kFromData ? x0 : x0 + col * ldx;
   const float* __restrict__ d = kFromData ? d0 + col * ldx : d0;
   double* __restrict__ y = y0 + col * ldy;
-  const int64_t in0 = c.out0 - lam;
-  const int64_t b0 = c.blk_start, b1 = c.blk_start + c.blk_len;
+  const SegmentStreams win = segment_streams(lpix, wq, wu, d, c.out0 - lam);
+  int lo, hi;
+  window_range(c, lam, kN, lo, hi);
 
   // thread roles: A layout t = tid; B layout (k3, n1); C layout two mirror tasks
   const int k3b = tid >> 4, n1b = tid & 15;
@@ -351,11 +335,11 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(4))) void k_
   // segments gather their right half first and odd ones their left half first, so that both
   // readers of a shared half fetch it together and the second finds it in L2.
   if (((wg / ncol) & 1) == 0) {
-    gather_half<1, kFromData>(v, lds, tid, lpix, wq, wu, x, d, d_vec, in0, b0, b1);
-    gather_half<0, kFromData>(v, lds, tid, lpix, wq, wu, x, d, d_vec, in0, b0, b1);
+    gather_half<1, kFromData>(v, lds, tid, win, x, lo, hi);
+    gather_half<0, kFromData>(v, lds, tid, win, x, lo, hi);
   } else {
-    gather_half<0, kFromData>(v, lds, tid, lpix, wq, wu, x, d, d_vec, in0, b0, b1);
-    gather_half<1, kFromData>(v, lds, tid, lpix, wq, wu, x, d, d_vec, in0, b0, b1);
+    gather_half<0, kFromData>(v, lds, tid, win, x, lo, hi);
+    gather_half<1, kFromData>(v, lds, tid, win, x, lo, hi);
   }
 
   // ---- forward transform --------------------------------------------------------------------
@@ -484,44 +468,28 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(4))) void k_
   // wavefront's list of completed runs, flushed one FP64 value per lane.
   const AtomicFlush flush{y};
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  static_assert(kListed * (3 * sizeof(double) + sizeof(int)) <= 64 * kLane * sizeof(float),
+  static_assert(run_list_bytes<3, kListed>() <= 64 * kLane * sizeof(float),
                 "run list must fit the wavefront's slice of the staged outputs");
   static_assert((kHalf + kT * kLane - 1) / (kT * kLane) * (kT * kLane) <= kLdsF,
                 "every round's slices lie inside the staging buffer");
   for (int base = 0; base < out_len; base += kT * kLane) {  // same trip count for every lane
     const int i0 = base + tid * kLane;
-    const int64_t o = c.out0 + i0;
-    int key[kLane];
+    float u[kLane];
+    LanePointing<kLane, false> lane;
+    lane.load(win, lam + i0, lam, lam + out_len);
+#pragma unroll
+    for (int j = 0; j < kLane; ++j) u[j] = lds[i0 + j];
+    lane.bridge_flags(u);
     double val[kLane][3];
-    if (i0 + kLane <= out_len && (o & 3) == 0) {
-      LanePointing<kLane, false> lane;
-      lane.load(lpix, wq, wu, nullptr, o);
 #pragma unroll
-      for (int j = 0; j < kLane; ++j) {
-        const double tv = lds[i0 + j];
-        key[j] = lane.kk[j];
-        val[j][0] = tv;
-        val[j][1] = static_cast<double>(lane.qq[j]) * tv;
-        val[j][2] = static_cast<double>(lane.uu[j]) * tv;
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < kLane; ++j) {
-        key[j] = -1;
-        val[j][0] = val[j][1] = val[j][2] = 0.0;
-        if (i0 + j < out_len) {
-          const int64_t oj = o + j;
-          key[j] = lpix[oj];
-          const double tv = lds[i0 + j];
-          val[j][0] = tv;
-          val[j][1] = static_cast<double>(wq[oj]) * tv;
-          val[j][2] = static_cast<double>(wu[oj]) * tv;
-        }
-      }
+    for (int j = 0; j < kLane; ++j) {
+      const double tv = u[j];
+      val[j][0] = tv;
+      val[j][1] = static_cast<double>(lane.qq[j]) * tv;
+      val[j][2] = static_cast<double>(lane.uu[j]) * tv;
     }
-    double* sval = reinterpret_cast<double*>(lds + base + 64 * kLane * wave);
-    int* skey = reinterpret_cast<int*>(sval + 3 * kListed);
-    wave_merge_runs_listed<kLane, 3, kListed, AtomicFlush, true>(key, val, flush, skey, sval);
+    wave_merge_runs_listed<kLane, 3, kListed>(lane.kk, val, flush,
+                                              lds + base + 64 * kLane * wave);
   }
 }
 
@@ -565,17 +533,15 @@ mm_status launch_apply_reg(Plan* P, const double* x, const float* d, int64_t ldx
                            int64_t ldy, int32_t ncol, const int32_t* done, hipStream_t s) {
   if (!apply_reg_supported(P) || P->spec_reg == nullptr)
     return fail(MM_ERR_UNSUPPORTED, "register FFT kernel: segment shape");
-  const bool vec = (reinterpret_cast<uintptr_t>(d) & 15u) == 0 && (ldx & 3) == 0;
-  const int d_vec = vec ? 1 : 0;
   const int64_t grid = static_cast<int64_t>(P->n_chunks) * ncol;
   if (grid > INT32_MAX) return fail(MM_ERR_UNSUPPORTED, "too many segment x column workgroups");
   if (d != nullptr) {
     hipLaunchKernelGGL((k_apply_reg<true>), dim3(static_cast<unsigned>(grid)), dim3(kT), 0, s,
-                       P->lpix, P->wq, P->wu, x, d, d_vec, y, ncol, ldx, ldy, P->chunks, P->spec_reg,
+                       P->lpix, P->wq, P->wu, x, d, y, ncol, ldx, ldy, P->chunks, P->spec_reg,
                        P->tw0, P->tw1, P->lambda_max, done);
   } else {
     hipLaunchKernelGGL((k_apply_reg<false>), dim3(static_cast<unsigned>(grid)), dim3(kT), 0, s,
-                       P->lpix, P->wq, P->wu, x, d, d_vec, y, ncol, ldx, ldy, P->chunks, P->spec_reg,
+                       P->lpix, P->wq, P->wu, x, d, y, ncol, ldx, ldy, P->chunks, P->spec_reg,
                        P->tw0, P->tw1, P->lambda_max, done);
   }
   MM_HIP_TRY(hipGetLastError());

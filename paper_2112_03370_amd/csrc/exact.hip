@@ -29,6 +29,7 @@
 #include <cmath>
 
 #include "mm_internal.h"
+#include "segment_io.h"
 #include "wave_runs.h"
 
 namespace mm {
@@ -264,19 +265,6 @@ __global__ __launch_bounds__(kXThreads) void k_x_spectrum(
   out[base + k] = spectrum_q(Z[base + k], Z[base + ((NC - k) & (NC - 1))], tw[k], S[k], S[NC - k]);
 }
 
-struct XFlush {
-  double* y;
-  __device__ void operator()(int key, const double (&v)[3]) const {
-    double* dst = y + 3 * static_cast<int64_t>(key);
-    unsafeAtomicAdd(dst + 0, v[0]);
-    unsafeAtomicAdd(dst + 1, v[1]);
-    unsafeAtomicAdd(dst + 2, v[2]);
-  }
-  __device__ void one(int key, int c, double v) const {
-    unsafeAtomicAdd(y + 3 * static_cast<int64_t>(key) + c, v);
-  }
-};
-
 // ---- outputs of each segment, pointed back into the pixel domain -------------------------
 __global__ __launch_bounds__(kXThreads) void k_x_scatter(
     const double2* __restrict__ G, const int32_t* __restrict__ lpix,
@@ -284,8 +272,7 @@ __global__ __launch_bounds__(kXThreads) void k_x_scatter(
     int seg0, int lam, int NC, double inv_n, double* __restrict__ y) {
   // per wavefront: the runs it completes, listed before the atomics (one value per lane)
   constexpr int kScatterListed = 64;
-  __shared__ int skey[kXThreads / 64][kScatterListed];
-  __shared__ double sval[kXThreads / 64][3 * kScatterListed];
+  __shared__ double list[kXThreads / 64][run_list_bytes<3, kScatterListed>() / sizeof(double)];
   const int wave = static_cast<int>(threadIdx.x >> 6);
   const Chunk c = chunks[seg0 + blockIdx.y];
   const int64_t base = static_cast<int64_t>(blockIdx.y) * NC;
@@ -311,8 +298,7 @@ __global__ __launch_bounds__(kXThreads) void k_x_scatter(
       }
     }
   }
-  wave_merge_runs_listed<4, 3, kScatterListed, XFlush, true>(key, v, XFlush{y}, skey[wave],
-                                                             sval[wave]);
+  wave_merge_runs_listed<4, 3, kScatterListed>(key, v, AtomicFlush{y}, list[wave]);
 }
 
 // ---- direct product for short bands (direct plans) ---------------------------------------
@@ -369,7 +355,7 @@ __global__ __launch_bounds__(kXThreads) void k_x_direct(
         }
       }
     }
-    wave_merge_runs<3>(key, v, XFlush{y});
+    wave_merge_runs<3>(key, v, AtomicFlush{y});
   }
 }
 
@@ -495,97 +481,26 @@ __device__ __forceinline__ void xfft(double2 (&v)[16], double* sh, int t, bool p
   xpass<4, T>(v, t, 16 * R2 * R3, paired_last, tw);
 }
 
-// FP64 samples of one lane of 8 consecutive window samples [g, g + 8), all inside the block and
-// g a multiple of 4: the pointing comes in 16-byte loads, and scan runs keep a pixel for several
-// samples, so the pixel values of the lane's first and last samples are loaded together and a
-// third pixel only when one occurs.  The sums are those of the one-sample form.
+// FP64 samples of one lane of 8 consecutive window samples, zero outside [lo, hi): P x, the data
+// or the time-domain residual d - P x (zero at flagged samples).
 template <int kIn>
-__device__ __forceinline__ void xgather8(const int32_t* __restrict__ lpix,
-                                         const float* __restrict__ wq,
-                                         const float* __restrict__ wu,
-                                         const double* __restrict__ x,
-                                         const float* __restrict__ d, int64_t g,
-                                         double (&o)[8]) {
-  constexpr bool kData = kIn == kInData;
-  int kk[8];
-  float qq[8], uu[8], dd[8];
+__device__ __forceinline__ void xgather8(const SegmentStreams& win, const double* __restrict__ x,
+                                         int i, int lo, int hi, double (&o)[8]) {
+  gather_lane<8, kIn == kInData>(win, x, i, lo, hi, o);
+  if constexpr (kIn == kInResid) {
+    if (i + 8 <= lo || i >= hi) return;
+    LanePointing<8, true> lane;  // keys and data
+    lane.load(win, i, lo, hi);
 #pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int4 k4 = *reinterpret_cast<const int4*>(lpix + g + 4 * c);
-    kk[4 * c] = k4.x;
-    kk[4 * c + 1] = k4.y;
-    kk[4 * c + 2] = k4.z;
-    kk[4 * c + 3] = k4.w;
-    const float4 q4 = *reinterpret_cast<const float4*>((kData ? d : wq) + g + 4 * c);
-    qq[4 * c] = q4.x;
-    qq[4 * c + 1] = q4.y;
-    qq[4 * c + 2] = q4.z;
-    qq[4 * c + 3] = q4.w;
-    if constexpr (!kData) {
-      const float4 u4 = *reinterpret_cast<const float4*>(wu + g + 4 * c);
-      uu[4 * c] = u4.x;
-      uu[4 * c + 1] = u4.y;
-      uu[4 * c + 2] = u4.z;
-      uu[4 * c + 3] = u4.w;
-    }
-    if constexpr (kIn == kInResid) {
-      const float4 d4 = *reinterpret_cast<const float4*>(d + g + 4 * c);
-      dd[4 * c] = d4.x;
-      dd[4 * c + 1] = d4.y;
-      dd[4 * c + 2] = d4.z;
-      dd[4 * c + 3] = d4.w;
-    }
-  }
-  if constexpr (kData) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) o[j] = kk[j] < 0 ? 0.0 : static_cast<double>(qq[j]);
-  } else {
-    const int ka = kk[0], kb = kk[7];
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, b0 = 0.0, b1 = 0.0, b2 = 0.0;
-    if (ka >= 0) {
-      const double* m = x + 3 * static_cast<int64_t>(ka);
-      a0 = m[0];
-      a1 = m[1];
-      a2 = m[2];
-    }
-    if (kb >= 0 && kb != ka) {
-      const double* m = x + 3 * static_cast<int64_t>(kb);
-      b0 = m[0];
-      b1 = m[1];
-      b2 = m[2];
-    }
-    bool other = false;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int key = kk[j];
-      other |= key >= 0 && key != ka && key != kb;
-      const double q = static_cast<double>(qq[j]), u = static_cast<double>(uu[j]);
-      const double ta = a0 + q * a1 + u * a2;
-      const double tb = b0 + q * b1 + u * b2;
-      o[j] = key < 0 ? 0.0 : (key == ka ? ta : tb);
-    }
-    if (other) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int key = kk[j];
-        if (key >= 0 && key != ka && key != kb) {
-          const double* m = x + 3 * static_cast<int64_t>(key);
-          o[j] = m[0] + static_cast<double>(qq[j]) * m[1] + static_cast<double>(uu[j]) * m[2];
-        }
-      }
-    }
-    if constexpr (kIn == kInResid) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if (kk[j] >= 0) o[j] = static_cast<double>(dd[j]) - o[j];
-    }
+    for (int j = 0; j < 8; ++j)
+      if (lane.kk[j] >= 0) o[j] = static_cast<double>(lane.qq[j]) - o[j];
   }
 }
 
 template <int M, int kIn>
 __global__ __launch_bounds__(XFused<M>::T) void k_x_fused(
     const int32_t* __restrict__ lpix, const float* __restrict__ wq, const float* __restrict__ wu,
-    const double* __restrict__ x, const float* __restrict__ d, int dvec,
+    const double* __restrict__ x, const float* __restrict__ d,
     const Chunk* __restrict__ chunks, int lam, const double* __restrict__ spec,
     const double2* __restrict__ tw0, double inv_n, double* __restrict__ y) {
   using C = XFused<M>;
@@ -594,7 +509,9 @@ __global__ __launch_bounds__(XFused<M>::T) void k_x_fused(
   __shared__ __align__(16) double sh[C::LDS + 32];
   const Chunk c = chunks[blockIdx.x];
   const int t = threadIdx.x;
-  const int64_t b0 = c.blk_start, b1 = c.blk_start + c.blk_len;
+  const SegmentStreams win = segment_streams(lpix, wq, wu, d, c.out0 - lam);
+  int lo, hi;
+  window_range(c, lam, 2 * NC, lo, hi);
 
   // ---- window samples, packed as complex points at the first pass's slots ------------------
   // Two halves of NC samples (NC / 2 points) staged through LDS, where sample n of a half sits
@@ -605,30 +522,8 @@ __global__ __launch_bounds__(XFused<M>::T) void k_x_fused(
 #pragma unroll 1
     for (int r = 0; r < 2; ++r) {
       const int n = 8 * (t + r * T);  // sample of the half
-      const int64_t g = c.out0 - lam + static_cast<int64_t>(h) * NC + n;
       double o[8];
-      if (g >= b0 && g + 8 <= b1 && (g & 3) == 0 && (kIn == kInMap || dvec)) {
-        xgather8<kIn>(lpix, wq, wu, x, d, g, o);
-      } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int64_t gj = g + j;
-          double val = 0.0;
-          if (gj >= b0 && gj < b1) {
-            const int p = lpix[gj];
-            if (p >= 0) {
-              if constexpr (kIn == kInData) {
-                val = static_cast<double>(d[gj]);
-              } else {
-                const double* m = x + 3 * static_cast<int64_t>(p);
-                val = m[0] + static_cast<double>(wq[gj]) * m[1] + static_cast<double>(wu[gj]) * m[2];
-                if constexpr (kIn == kInResid) val = static_cast<double>(d[gj]) - val;
-              }
-            }
-          }
-          o[j] = val;
-        }
-      }
+      xgather8<kIn>(win, x, h * NC + n, lo, hi, o);
       double2* dst = reinterpret_cast<double2*>(sh + n);
 #pragma unroll
       for (int j = 0; j < 4; ++j) dst[j] = make_double2(o[2 * j], o[2 * j + 1]);
@@ -730,82 +625,43 @@ __global__ __launch_bounds__(XFused<M>::T) void k_x_fused(
   // slices lie inside sh); once read, that slice holds the wavefront's list of completed runs,
   // flushed one FP64 value per lane.
   constexpr int kXListed = 64;
-  static_assert(3 * kXListed + kXListed / 2 <= 512, "run list must fit a wavefront's slice");
+  static_assert(run_list_bytes<3, kXListed>() <= 512 * sizeof(double),
+                "run list must fit a wavefront's slice");
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   for (int base = 0; base < c.out_len; base += 8 * T) {  // same trip count for every lane
     const int i0 = base + 8 * t;
-    const int64_t o = c.out0 + i0;
-    int key[8];
+    LanePointing<8, false> lane;
+    lane.load(win, lam + i0, lam, lam + c.out_len);
+    double u[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) u[i] = sh[xpad(i0 + i)];
+    lane.bridge_flags(u);
     double vv[8][3];
-    if (i0 + 8 <= c.out_len && (o & 3) == 0) {
-      int kk[8];
-      float qq[8], uu[8];
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const int4 k4 = *reinterpret_cast<const int4*>(lpix + o + 4 * q);
-        const float4 q4 = *reinterpret_cast<const float4*>(wq + o + 4 * q);
-        const float4 u4 = *reinterpret_cast<const float4*>(wu + o + 4 * q);
-        kk[4 * q] = k4.x;
-        kk[4 * q + 1] = k4.y;
-        kk[4 * q + 2] = k4.z;
-        kk[4 * q + 3] = k4.w;
-        qq[4 * q] = q4.x;
-        qq[4 * q + 1] = q4.y;
-        qq[4 * q + 2] = q4.z;
-        qq[4 * q + 3] = q4.w;
-        uu[4 * q] = u4.x;
-        uu[4 * q + 1] = u4.y;
-        uu[4 * q + 2] = u4.z;
-        uu[4 * q + 3] = u4.w;
-      }
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const double u = sh[xpad(i0 + i)];
-        key[i] = kk[i];
-        vv[i][0] = u;
-        vv[i][1] = static_cast<double>(qq[i]) * u;
-        vv[i][2] = static_cast<double>(uu[i]) * u;
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int oi = i0 + i;
-        key[i] = -1;
-        vv[i][0] = vv[i][1] = vv[i][2] = 0.0;
-        if (oi < c.out_len) {
-          const int64_t g = c.out0 + oi;
-          const int p = lpix[g];
-          if (p >= 0) {
-            const double u = sh[xpad(oi)];
-            key[i] = p;
-            vv[i][0] = u;
-            vv[i][1] = static_cast<double>(wq[g]) * u;
-            vv[i][2] = static_cast<double>(wu[g]) * u;
-          }
-        }
-      }
+    for (int i = 0; i < 8; ++i) {
+      vv[i][0] = u[i];
+      vv[i][1] = static_cast<double>(lane.qq[i]) * u[i];
+      vv[i][2] = static_cast<double>(lane.uu[i]) * u[i];
     }
-    double* sval = sh + xpad(base + 512 * wave);
-    int* skey = reinterpret_cast<int*>(sval + 3 * kXListed);
-    wave_merge_runs_listed<8, 3, kXListed, XFlush, true>(key, vv, XFlush{y}, skey, sval);
+    wave_merge_runs_listed<8, 3, kXListed>(lane.kk, vv, AtomicFlush{y},
+                                           sh + xpad(base + 512 * wave));
   }
 }
 
 template <int M>
 mm_status launch_fused_m(Plan* P, const double* x, const float* d, double* y, hipStream_t s) {
   const double inv_n = 1.0 / static_cast<double>(P->fft_n);
-  const int dvec = (reinterpret_cast<uintptr_t>(d) & 15u) == 0 ? 1 : 0;
   if (x == nullptr)
     hipLaunchKernelGGL((k_x_fused<M, kInData>), dim3(P->n_chunks), dim3(XFused<M>::T), 0, s,
-                       P->lpix, P->wq, P->wu, x, d, dvec, P->chunks, P->lambda_max, P->x_spec,
+                       P->lpix, P->wq, P->wu, x, d, P->chunks, P->lambda_max, P->x_spec,
                        P->x_tw, inv_n, y);
   else if (d == nullptr)
     hipLaunchKernelGGL((k_x_fused<M, kInMap>), dim3(P->n_chunks), dim3(XFused<M>::T), 0, s,
-                       P->lpix, P->wq, P->wu, x, d, dvec, P->chunks, P->lambda_max, P->x_spec,
+                       P->lpix, P->wq, P->wu, x, d, P->chunks, P->lambda_max, P->x_spec,
                        P->x_tw, inv_n, y);
   else
     hipLaunchKernelGGL((k_x_fused<M, kInResid>), dim3(P->n_chunks), dim3(XFused<M>::T), 0, s,
-                       P->lpix, P->wq, P->wu, x, d, dvec, P->chunks, P->lambda_max, P->x_spec,
+                       P->lpix, P->wq, P->wu, x, d, P->chunks, P->lambda_max, P->x_spec,
                        P->x_tw, inv_n, y);
   MM_HIP_TRY(hipGetLastError());
   return MM_OK;

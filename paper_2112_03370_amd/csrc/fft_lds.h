@@ -188,6 +188,13 @@ struct FftCfg {
 };
 
 
+// a - b c with the product rounded before the difference.
+__device__ __forceinline__ float minus_product(float a, float b, float c) {
+#pragma clang fp contract(off)
+  const float bc = b * c;
+  return a - bc;
+}
+
 // Real spectrum step between the two transforms.  The N real samples are packed as NC complex
 // values z[m] = t[2m] + i t[2m+1] with transform Z; the step unpacks the real spectrum X at k
 // and NC - k, multiplies by the band symbol S (already scaled by 1/(2N)), repacks for the
@@ -233,11 +240,18 @@ __device__ __forceinline__ void symbol_multiply(float2* buf, const float* __rest
       const int k2 = (NC - k) & (NC - 1);
       const float a = 2.0f * sa[r], b = 2.0f * sb[r];
       const float sig = a + b, del = a - b;
-      const float ds = del * W[r].y;  // -2 delta s
-      const float p = sig + ds, p2 = sig - ds, q = del * W[r].x;
-      buf[pad(k)] = make_float2(p * Z[r].x + q * Z2[r].y, -(p * Z[r].y + q * Z2[r].x));
+      // The fused multiply-adds are written out: left to contraction, which of these are fused
+      // (and with them the last bit of a few bins) changes with unrelated edits of the kernels.
+      // The first pair's p2 (every pair's in one-wavefront segments) rounds its product first.
+      const float p = fmaf(del, W[r].y, sig);  // sig - 2 delta s
+      const float p2 = T == 64 || r0 + r == 0 ? minus_product(sig, del, W[r].y)
+                                              : fmaf(-del, W[r].y, sig);
+      const float q = del * W[r].x;
+      buf[pad(k)] =
+          make_float2(fmaf(q, Z2[r].y, p * Z[r].x), -fmaf(q, Z2[r].x, p * Z[r].y));
       if (k2 != k)  // k = 0 pairs with itself
-        buf[pad(k2)] = make_float2(p2 * Z2[r].x + q * Z[r].y, -(p2 * Z2[r].y + q * Z[r].x));
+        buf[pad(k2)] =
+            make_float2(fmaf(q, Z[r].y, p2 * Z2[r].x), -fmaf(q, Z[r].x, p2 * Z2[r].y));
     }
   }
   if (tid == 0) {  // k = NC/2: s = 1, c = 0, delta = 0

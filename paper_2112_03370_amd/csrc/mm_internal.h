@@ -50,6 +50,15 @@ struct Chunk {
   int32_t pad;
 };
 
+// Window samples of a segment that lie inside its block: [lo, hi) of [0, n), where window sample
+// i is sample out0 - lam + i of the streams.
+__device__ __forceinline__ void window_range(const Chunk& c, int lam, int n, int& lo, int& hi) {
+  const int64_t in0 = c.out0 - lam;
+  const int64_t b0 = c.blk_start - in0, b1 = c.blk_start + c.blk_len - in0;
+  lo = b0 > 0 ? static_cast<int>(b0) : 0;
+  hi = b1 < n ? static_cast<int>(b1) : n;
+}
+
 // Samples [start, start + len) with one diagonal weight c0 (plan-time tiles).
 struct Tile {
   int64_t start;

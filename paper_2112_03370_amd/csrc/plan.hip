@@ -16,6 +16,7 @@
 #include <unordered_map>
 
 #include "mm_internal.h"
+#include "segment_io.h"
 #include "wave_runs.h"
 
 namespace mm {
@@ -33,12 +34,6 @@ constexpr int kAccListed = 64;     // listed runs per wavefront there
 struct BjFlush {
   double* B;        // [n_pix_global][6]
   int32_t* hits;    // [n_pix_global]
-  __device__ void operator()(int key, const double (&v)[7]) const {
-    double* dst = B + 6 * static_cast<int64_t>(key);
-#pragma unroll
-    for (int c = 0; c < 6; ++c) unsafeAtomicAdd(dst + c, v[c]);
-    atomicAdd(hits + key, static_cast<int32_t>(v[6] + 0.5));
-  }
   __device__ void one(int key, int c, double v) const {
     if (c < 6) {
       unsafeAtomicAdd(B + 6 * static_cast<int64_t>(key) + c, v);
@@ -55,8 +50,7 @@ __global__ __launch_bounds__(kThreads) void k_plan_accumulate(
   const Tile tl = tiles[blockIdx.x];
   const BjFlush flush{B, hits};
   // per wavefront: the runs it completes, listed before the atomics
-  __shared__ int skey[kThreads / 64][kAccListed];
-  __shared__ double sval[kThreads / 64][7 * kAccListed];
+  __shared__ double list[kThreads / 64][run_list_bytes<7, kAccListed>() / sizeof(double)];
   const int wave = static_cast<int>(threadIdx.x >> 6);
   const double c0 = tl.c0;
   for (int off = 0; off < tl.len; off += kThreads * kAccLane) {  // same trip count for all lanes
@@ -65,15 +59,12 @@ __global__ __launch_bounds__(kThreads) void k_plan_accumulate(
     int gg[kAccLane];
     float qq[kAccLane], uu[kAccLane];
     bool in[kAccLane];
-    if (o0 + kAccLane <= tl.len && (i0 & 3) == 0) {  // 16-byte loads per stream
+    if (o0 + kAccLane <= tl.len) {  // 16-byte loads per stream
 #pragma unroll
-      for (int h = 0; h < kAccLane / 4; ++h) {
-        const int4 g4 = *reinterpret_cast<const int4*>(pix + i0 + 4 * h);
-        const float4 q4 = *reinterpret_cast<const float4*>(wq + i0 + 4 * h);
-        const float4 u4 = *reinterpret_cast<const float4*>(wu + i0 + 4 * h);
-        gg[4 * h] = g4.x; gg[4 * h + 1] = g4.y; gg[4 * h + 2] = g4.z; gg[4 * h + 3] = g4.w;
-        qq[4 * h] = q4.x; qq[4 * h + 1] = q4.y; qq[4 * h + 2] = q4.z; qq[4 * h + 3] = q4.w;
-        uu[4 * h] = u4.x; uu[4 * h + 1] = u4.y; uu[4 * h + 2] = u4.z; uu[4 * h + 3] = u4.w;
+      for (int h = 0; h < kAccLane; h += 4) {
+        load4u(pix + i0 + h, gg + h);
+        load4u(wq + i0 + h, qq + h);
+        load4u(wu + i0 + h, uu + h);
       }
 #pragma unroll
       for (int j = 0; j < kAccLane; ++j) in[j] = true;
@@ -110,8 +101,7 @@ __global__ __launch_bounds__(kThreads) void k_plan_accumulate(
         v[j][6] = 1.0;
       }
     }
-    wave_merge_runs_listed<kAccLane, 7, kAccListed, BjFlush, true>(key, v, flush, skey[wave],
-                                                                  sval[wave]);
+    wave_merge_runs_listed<kAccLane, 7, kAccListed>(key, v, flush, list[wave]);
   }
 }
 

@@ -22,59 +22,140 @@ struct AtomicFlush {
   }
 };
 
-template <bool kFromData>
-__device__ __forceinline__ float gather_one(int key, float q, float w, const double* __restrict__ x,
-                                            float dv) {
-  if (key < 0) return 0.0f;
-  if constexpr (kFromData) {
-    return dv;
-  } else {
-    const double* m = x + 3 * static_cast<int64_t>(key);
-    return static_cast<float>(m[0] + static_cast<double>(q) * m[1] + static_cast<double>(w) * m[2]);
-  }
+// 16-byte global accesses at 4-byte alignment: time streams are read from wherever a stationary
+// interval or a window starts.  gfx950 takes dword-aligned dwordx4 accesses, so lanes need no
+// aligned start; an unaligned wavefront only touches one more cache line.  (Scalar loads in their
+// place, one wait per sample, made one product of 61 detectors x 200,003 samples, lambda = 2047,
+// 2 % flags, take 254 us; with these loads 209 us, and with the flags and short runs handled as
+// below and in wave_runs.h 102 us.)
+typedef int int4_u __attribute__((ext_vector_type(4), aligned(4)));
+typedef float float4_u __attribute__((ext_vector_type(4), aligned(4)));
+
+__device__ __forceinline__ void load4u(const int32_t* p, int* v) {
+  const int4_u t = *reinterpret_cast<const int4_u*>(p);
+  v[0] = t.x;
+  v[1] = t.y;
+  v[2] = t.z;
+  v[3] = t.w;
+}
+__device__ __forceinline__ void load4u(const float* p, float* v) {
+  const float4_u t = *reinterpret_cast<const float4_u*>(p);
+  v[0] = t.x;
+  v[1] = t.y;
+  v[2] = t.z;
+  v[3] = t.w;
+}
+__device__ __forceinline__ void store4u(float* p, float a, float b, float c, float d) {
+  *reinterpret_cast<float4_u*>(p) = float4_u{a, b, c, d};
 }
 
-// Pointing of one lane: window samples [g, g + S), inside the block and 16-byte aligned (the
-// data instead of the weights when gathering d).
+// The pointing streams of one segment (and the data when gathering d), from the segment's first
+// window sample on: that sample may lie before the streams' own first sample (a window that
+// starts before the first interval), where nothing is read.  Uniform base plus 32-bit sample
+// offset: one address register per lane instead of a 64-bit add per access.
+struct SegmentStreams {
+  const int32_t* lpix;
+  const float* wq;
+  const float* wu;
+  const float* d;
+};
+
+__device__ __forceinline__ SegmentStreams segment_streams(const int32_t* lpix, const float* wq,
+                                                          const float* wu, const float* d,
+                                                          int64_t first) {
+  return SegmentStreams{lpix + first, wq + first, wu + first, d + first};
+}
+
+// Pointing of one lane: samples [i, i + S) of a segment (the data instead of the weights when
+// gathering d).  Samples outside [lo, hi) get key -1 and are not read.
 template <int S, bool kFromData>
 struct LanePointing {
   int kk[S];
   float qq[S], uu[S];
 
-  __device__ __forceinline__ void load(const int32_t* __restrict__ lpix,
-                                       const float* __restrict__ wq, const float* __restrict__ wu,
-                                       const float* __restrict__ d, int64_t g) {
+  // All S samples inside the streams.
+  __device__ __forceinline__ void load(const SegmentStreams& p, uint32_t i) {
 #pragma unroll
-    for (int c = 0; c < S / 4; ++c) {
-      const int4 k4 = *reinterpret_cast<const int4*>(lpix + g + 4 * c);
-      kk[4 * c] = k4.x;
-      kk[4 * c + 1] = k4.y;
-      kk[4 * c + 2] = k4.z;
-      kk[4 * c + 3] = k4.w;
-      const float4 q4 = *reinterpret_cast<const float4*>((kFromData ? d : wq) + g + 4 * c);
-      qq[4 * c] = q4.x;
-      qq[4 * c + 1] = q4.y;
-      qq[4 * c + 2] = q4.z;
-      qq[4 * c + 3] = q4.w;
-      if constexpr (!kFromData) {
-        const float4 u4 = *reinterpret_cast<const float4*>(wu + g + 4 * c);
-        uu[4 * c] = u4.x;
-        uu[4 * c + 1] = u4.y;
-        uu[4 * c + 2] = u4.z;
-        uu[4 * c + 3] = u4.w;
+    for (uint32_t c = 0; c < S; c += 4) {
+      load4u(p.lpix + (i + c), kk + c);
+      load4u((kFromData ? p.d : p.wq) + (i + c), qq + c);
+      if constexpr (!kFromData) load4u(p.wu + (i + c), uu + c);
+    }
+  }
+
+  __device__ __forceinline__ void load(const SegmentStreams& p, int i, int lo, int hi) {
+    if (i >= lo && i + S <= hi) {
+      load(p, static_cast<uint32_t>(i));
+      return;
+    }
+#pragma unroll
+    for (int j = 0; j < S; ++j) {
+      kk[j] = -1;
+      qq[j] = uu[j] = 0.0f;
+    }
+#pragma unroll
+    for (int j = 0; j < S; ++j) {  // the lanes that straddle an edge
+      if (i + j >= lo && i + j < hi) {
+        kk[j] = p.lpix[i + j];
+        qq[j] = (kFromData ? p.d : p.wq)[i + j];
+        if constexpr (!kFromData) uu[j] = p.wu[i + j];
       }
     }
   }
 
+  __device__ __forceinline__ int least_key() const {
+    int least = kk[0];
+#pragma unroll
+    for (int j = 1; j < S; ++j) least = min(least, kk[j]);
+    return least;
+  }
+
+  // Flagged samples continue the run of pixels that surrounds them, with zero weight and zero
+  // value: for the scatter, where every break in a run costs a listed run and its atomics.  Lanes
+  // without any pixel keep key -1.  (Weights and values at flagged samples may hold anything.)
+  template <class T>
+  __device__ __forceinline__ void bridge_flags(T (&v)[S]) {
+    if (!__any(least_key() < 0)) return;
+#pragma unroll
+    for (int j = 0; j < S; ++j) {
+      const bool skip = kk[j] < 0;
+      v[j] = skip ? T(0) : v[j];
+      qq[j] = skip ? 0.0f : qq[j];
+      uu[j] = skip ? 0.0f : uu[j];
+      if (j > 0) kk[j] = skip ? kk[j - 1] : kk[j];
+    }
+#pragma unroll
+    for (int j = S - 2; j >= 0; --j) kk[j] = kk[j] < 0 ? kk[j + 1] : kk[j];
+  }
+
   // Scan runs keep a pixel for several consecutive samples, so a lane usually sees one or two
-  // pixels: it loads the pixels of its first and last samples together, behind a single wait,
-  // and goes back for a third pixel only when one occurs.
-  __device__ __forceinline__ void resolve(const double* __restrict__ x, float (&v)[S]) const {
+  // pixels: the lane's first and last pixels are loaded together, with the first other pixel
+  // between them where some lane of the wavefront has one (short runs), all behind a single wait;
+  // further pixels, one at a time, only when they occur.
+  template <class T>
+  __device__ __forceinline__ void resolve(const double* __restrict__ x, T (&v)[S]) const {
     if constexpr (kFromData) {
 #pragma unroll
-      for (int j = 0; j < S; ++j) v[j] = kk[j] < 0 ? 0.0f : qq[j];
+      for (int j = 0; j < S; ++j) v[j] = kk[j] < 0 ? T(0) : static_cast<T>(qq[j]);
     } else {
-      const int ka = kk[0], kb = kk[S - 1];
+      // The tests for flagged samples sit behind a wavefront-uniform branch (per sample, the
+      // compiler turns them into a branch around that sample's sums).
+      int ka = kk[0], kb = kk[S - 1];
+      bool other = false;
+      const bool flagged = __any(least_key() < 0);
+      if (flagged) {
+        ka = kb = -1;  // the first and last pixels observed
+#pragma unroll
+        for (int j = 0; j < S; ++j) {
+          kb = kk[j] >= 0 ? kk[j] : kb;
+          ka = kk[S - 1 - j] >= 0 ? kk[S - 1 - j] : ka;
+        }
+#pragma unroll
+        for (int j = 1; j < S - 1; ++j) other |= kk[j] >= 0 && kk[j] != ka && kk[j] != kb;
+      } else {
+#pragma unroll
+        for (int j = 1; j < S - 1; ++j) other |= kk[j] != ka && kk[j] != kb;
+      }
       double a0 = 0.0, a1 = 0.0, a2 = 0.0, b0 = 0.0, b1 = 0.0, b2 = 0.0;
       if (ka >= 0) {
         const double* m = x + 3 * static_cast<int64_t>(ka);
@@ -88,31 +169,78 @@ struct LanePointing {
         b1 = m[1];
         b2 = m[2];
       }
-      bool other = false;
+      const bool more = __any(other);
+      int kc = -1;
+      double c0 = 0.0, c1 = 0.0, c2 = 0.0;
+      if (more) {
+#pragma unroll
+        for (int j = S - 2; j > 0; --j)
+          kc = kk[j] >= 0 && kk[j] != ka && kk[j] != kb ? kk[j] : kc;
+        if (kc >= 0) {
+          const double* m = x + 3 * static_cast<int64_t>(kc);
+          c0 = m[0];
+          c1 = m[1];
+          c2 = m[2];
+        }
+      }
 #pragma unroll
       for (int j = 0; j < S; ++j) {
-        const int key = kk[j];
-        other |= key >= 0 && key != ka && key != kb;
         // both candidate pixels' sums, then one select (cheaper than selecting three FP64
         // pixel values)
         const double q = static_cast<double>(qq[j]), u = static_cast<double>(uu[j]);
         const double ta = a0 + q * a1 + u * a2;
         const double tb = b0 + q * b1 + u * b2;
-        v[j] = key < 0 ? 0.0f : static_cast<float>(key == ka ? ta : tb);
+        v[j] = static_cast<T>(kk[j] == ka ? ta : tb);
       }
-      if (other) {  // a third pixel inside the lane
+      if (flagged) {
 #pragma unroll
-        for (int j = 0; j < S; ++j) {
-          const int key = kk[j];
-          if (key >= 0 && key != ka && key != kb) {
-            const double* m = x + 3 * static_cast<int64_t>(key);
-            v[j] = static_cast<float>(m[0] + static_cast<double>(qq[j]) * m[1] +
-                                      static_cast<double>(uu[j]) * m[2]);
+        for (int j = 0; j < S; ++j) v[j] = kk[j] < 0 ? T(0) : v[j];
+      }
+      if (more) {
+        int done = 0;  // samples before this one are resolved as far as kc goes
+        while (true) {
+#pragma unroll
+          for (int j = 1; j < S - 1; ++j) {
+            const double t = c0 + static_cast<double>(qq[j]) * c1 + static_cast<double>(uu[j]) * c2;
+            if (kc >= 0 && kk[j] == kc) v[j] = static_cast<T>(t);
+          }
+          // the next pixel after kc's first sample that none of the loaded ones was
+          int next = -1, at = S;
+#pragma unroll
+          for (int j = S - 2; j > 0; --j)
+            if (j > done && kk[j] >= 0 && kk[j] != ka && kk[j] != kb && kk[j] != kc) {
+              next = kk[j];
+              at = j;
+            }
+          if (!__any(next >= 0)) break;
+          done = at;
+          kc = next;
+          if (kc >= 0) {
+            const double* m = x + 3 * static_cast<int64_t>(kc);
+            c0 = m[0];
+            c1 = m[1];
+            c2 = m[2];
           }
         }
       }
     }
   }
 };
+
+// t of one lane of window samples [i, i + S): P x, or the data, zero outside [lo, hi).  Lanes that
+// lie outside altogether (the window's overhang at a block's ends: whole wavefronts) skip the sums.
+template <int S, bool kFromData, class T>
+__device__ __forceinline__ void gather_lane(const SegmentStreams& win,
+                                            const double* __restrict__ x, int i, int lo, int hi,
+                                            T (&v)[S]) {
+  if (i + S <= lo || i >= hi) {
+#pragma unroll
+    for (int j = 0; j < S; ++j) v[j] = T(0);
+    return;
+  }
+  LanePointing<S, kFromData> lane;
+  lane.load(win, i, lo, hi);
+  lane.resolve(x, v);
+}
 
 }  // namespace mm

@@ -23,6 +23,7 @@
 #include <cmath>
 
 #include "mm_internal.h"
+#include "segment_io.h"
 #include "wave_runs.h"
 
 namespace mm {
@@ -32,16 +33,6 @@ namespace {
 constexpr int kTT = 512;          // threads per workgroup
 constexpr int kStep = 4 * kTT;    // samples per step (4 consecutive per lane)
 constexpr int kCached = 4;        // steps kept in registers
-
-struct TFlush {
-  double* y;
-  __device__ void operator()(int key, const double (&v)[3]) const {
-    double* dst = y + 3 * static_cast<int64_t>(key);
-    unsafeAtomicAdd(dst + 0, v[0]);
-    unsafeAtomicAdd(dst + 1, v[1]);
-    unsafeAtomicAdd(dst + 2, v[2]);
-  }
-};
 
 // Scaled Legendre values T_k = scale_k P_k(x), k < NP, by the three-term recurrence
 // k P_k = (2k - 1) x P_(k-1) - (k - 1) P_(k-2), with 1/k as a constant.
@@ -68,7 +59,7 @@ __device__ __forceinline__ void legendre(double x, const double* scale, double (
 
 // Samples j0 .. j0 + 3 of a baseline: pixel, weights and t = (P x)_s (or the data sample) in
 // FP64; key -1 for gap samples and samples past the end.  A lane whose 4 samples lie inside the
-// baseline at a 16-byte boundary loads its pointing with 16-byte loads, and since scan runs keep
+// baseline loads its pointing with 16-byte loads, and since scan runs keep
 // a pixel for several samples, it loads the pixel values of its first and last samples once
 // each and a third pixel only when one occurs.  The sums are those of the one-sample form.
 template <bool kData>
@@ -80,30 +71,15 @@ __device__ __forceinline__ void load4(const int32_t* __restrict__ lpix,
                                       int j0, int (&key)[4], double (&t)[4], float (&q)[4],
                                       float (&u)[4]) {
   const int64_t g0 = start + j0;
-  const bool vec = j0 + 4 <= len && (g0 & 3) == 0 &&
-                   (!kData || (reinterpret_cast<uintptr_t>(d + g0) & 15u) == 0);
-  if (vec) {
-    const int4 k4 = *reinterpret_cast<const int4*>(lpix + g0);
-    const float4 q4 = *reinterpret_cast<const float4*>(wq + g0);
-    const float4 u4 = *reinterpret_cast<const float4*>(wu + g0);
-    key[0] = k4.x;
-    key[1] = k4.y;
-    key[2] = k4.z;
-    key[3] = k4.w;
-    q[0] = q4.x;
-    q[1] = q4.y;
-    q[2] = q4.z;
-    q[3] = q4.w;
-    u[0] = u4.x;
-    u[1] = u4.y;
-    u[2] = u4.z;
-    u[3] = u4.w;
+  if (j0 + 4 <= len) {
+    load4u(lpix + g0, key);
+    load4u(wq + g0, q);
+    load4u(wu + g0, u);
     if constexpr (kData) {
-      const float4 d4 = *reinterpret_cast<const float4*>(d + g0);
-      t[0] = key[0] < 0 ? 0.0 : static_cast<double>(d4.x);
-      t[1] = key[1] < 0 ? 0.0 : static_cast<double>(d4.y);
-      t[2] = key[2] < 0 ? 0.0 : static_cast<double>(d4.z);
-      t[3] = key[3] < 0 ? 0.0 : static_cast<double>(d4.w);
+      float dd[4];
+      load4u(d + g0, dd);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) t[i] = key[i] < 0 ? 0.0 : static_cast<double>(dd[i]);
     } else {
       const int ka = key[0], kb = key[3];
       double a0 = 0.0, a1 = 0.0, a2 = 0.0, b0 = 0.0, b1 = 0.0, b2 = 0.0;
@@ -205,7 +181,7 @@ __device__ __forceinline__ void subtract_point4(const int (&key)[4], const doubl
     v[i][1] = static_cast<double>(q[i]) * r;
     v[i][2] = static_cast<double>(u[i]) * r;
   }
-  wave_merge_runs<3>(key, v, TFlush{y});
+  wave_merge_runs<3>(key, v, AtomicFlush{y});
 }
 
 template <bool kData, int NP>

@@ -82,7 +82,6 @@ struct LongArgs {
   double* y0;
   int64_t ldx, ldy;
   int ncol;
-  int vec;  // plain: t and u 16-byte aligned; fused rhs: every data column 16-byte aligned
   const Chunk* chunks;
   int n_work;  // segments x columns
   const float4* pq;
@@ -206,103 +205,59 @@ __global__ __launch_bounds__(256) void k_long_table(const float* __restrict__ sp
   T[e] = make_float4(a.x, a.y, b.x, b.y);
 }
 
-// Window samples [g, g + kLane) of one segment (zero outside its block [b0, b1)).
+// Window samples [i, i + kLane) of one segment (zero outside its block's [lo, hi)); the plain form
+// reads its time vector through win.d.
 template <int IO>
-__device__ __forceinline__ void fill_lane(const LongArgs& a, const double* __restrict__ x,
-                                          const float* __restrict__ d, int64_t g, int64_t b0,
-                                          int64_t b1, float (&v)[kLane]) {
-  if (g + kLane <= b0 || g >= b1) {
-#pragma unroll
-    for (int j = 0; j < kLane; ++j) v[j] = 0.0f;
-    return;
-  }
-  const bool inside = g >= b0 && g + kLane <= b1 && (g & 3) == 0;
+__device__ __forceinline__ void fill_lane(const SegmentStreams& win, const double* __restrict__ x,
+                                          int i, int lo, int hi, float (&v)[kLane]) {
   if constexpr (IO == kIoPlain) {
-    if (inside && a.vec) {
-      const float4 lo = *reinterpret_cast<const float4*>(a.t + g);
-      const float4 hi = *reinterpret_cast<const float4*>(a.t + g + 4);
-      v[0] = lo.x; v[1] = lo.y; v[2] = lo.z; v[3] = lo.w;
-      v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
+    if (i >= lo && i + kLane <= hi) {
+      load4u(win.d + static_cast<uint32_t>(i), v);
+      load4u(win.d + static_cast<uint32_t>(i + 4), v + 4);
     } else {
 #pragma unroll
-      for (int j = 0; j < kLane; ++j)
-        v[j] = (g + j >= b0 && g + j < b1) ? a.t[g + j] : 0.0f;
+      for (int j = 0; j < kLane; ++j) v[j] = (i + j >= lo && i + j < hi) ? win.d[i + j] : 0.0f;
     }
   } else {
-    constexpr bool kD = IO == kIoRhs;
-    if (inside && (!kD || a.vec)) {
-      LanePointing<kLane, kD> lane;
-      lane.load(a.lpix, a.wq, a.wu, d, g);
-      lane.resolve(x, v);
-    } else {
-#pragma unroll
-      for (int j = 0; j < kLane; ++j) {
-        const int64_t gj = g + j;
-        v[j] = 0.0f;
-        if (gj >= b0 && gj < b1)
-          v[j] = gather_one<kD>(a.lpix[gj], a.wq[gj], a.wu[gj], x, kD ? d[gj] : 0.0f);
-      }
-    }
+    gather_lane<kLane, IO == kIoRhs>(win, x, i, lo, hi, v);
   }
 }
 
 // Runs listed per wavefront and drain round before their atomics; the list lives in the
 // wavefront's own row pieces of the group buffer, which it has read by then.
 constexpr int kListed = 64;
-static_assert(kListed * (3 * sizeof(double) + sizeof(int)) <= kWaveRows * kS * sizeof(float2),
+static_assert(run_list_bytes<3, kListed>() <= kWaveRows * kS * sizeof(float2),
               "run list must fit the wavefront's row pieces");
 
 // Output samples [o, o + kLane) of a segment (only those in [0, out_len) exist).  The fused
 // form must be reached by whole wavefronts (the run merge exchanges lanes); `list` is the
 // wavefront's LDS for its run list (no other wavefront touches it during the call).
 template <int IO>
-__device__ __forceinline__ void drain_lane(const LongArgs& a, double* __restrict__ y,
-                                           const Chunk& c, int o, const float (&v)[kLane],
-                                           float2* list) {
-  const int64_t go = c.out0 + o;
-  const bool inside = o >= 0 && o + kLane <= c.out_len && (go & 3) == 0;
+__device__ __forceinline__ void drain_lane(const LongArgs& a, const SegmentStreams& win,
+                                           double* __restrict__ y, const Chunk& c, int o,
+                                           float (&v)[kLane], float2* list) {
   if constexpr (IO == kIoPlain) {
-    if (inside && a.vec) {
-      *reinterpret_cast<float4*>(a.u + go) = make_float4(v[0], v[1], v[2], v[3]);
-      *reinterpret_cast<float4*>(a.u + go + 4) = make_float4(v[4], v[5], v[6], v[7]);
+    if (o >= 0 && o + kLane <= c.out_len) {
+      store4u(a.u + c.out0 + o, v[0], v[1], v[2], v[3]);
+      store4u(a.u + c.out0 + o + 4, v[4], v[5], v[6], v[7]);
     } else {
 #pragma unroll
       for (int j = 0; j < kLane; ++j)
-        if (o + j >= 0 && o + j < c.out_len) a.u[go + j] = v[j];
+        if (o + j >= 0 && o + j < c.out_len) a.u[c.out0 + o + j] = v[j];
     }
   } else {
-    int key[kLane];
+    LanePointing<kLane, false> lane;
+    lane.load(win, a.lam + o, a.lam, a.lam + c.out_len);
+    lane.bridge_flags(v);
     double val[kLane][3];
-    if (inside) {
-      LanePointing<kLane, false> lane;
-      lane.load(a.lpix, a.wq, a.wu, nullptr, go);
 #pragma unroll
-      for (int j = 0; j < kLane; ++j) {
-        const double tv = v[j];
-        key[j] = lane.kk[j];
-        val[j][0] = tv;
-        val[j][1] = static_cast<double>(lane.qq[j]) * tv;
-        val[j][2] = static_cast<double>(lane.uu[j]) * tv;
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < kLane; ++j) {
-        key[j] = -1;
-        val[j][0] = val[j][1] = val[j][2] = 0.0;
-        if (o + j >= 0 && o + j < c.out_len) {
-          const int64_t oj = go + j;
-          const double tv = v[j];
-          key[j] = a.lpix[oj];
-          val[j][0] = tv;
-          val[j][1] = static_cast<double>(a.wq[oj]) * tv;
-          val[j][2] = static_cast<double>(a.wu[oj]) * tv;
-        }
-      }
+    for (int j = 0; j < kLane; ++j) {
+      const double tv = v[j];
+      val[j][0] = tv;
+      val[j][1] = static_cast<double>(lane.qq[j]) * tv;
+      val[j][2] = static_cast<double>(lane.uu[j]) * tv;
     }
-    double* sval = reinterpret_cast<double*>(list);
-    int* skey = reinterpret_cast<int*>(sval + 3 * kListed);
-    wave_merge_runs_listed<kLane, 3, kListed, AtomicFlush, true>(key, val, AtomicFlush{y}, skey,
-                                                                 sval);
+    wave_merge_runs_listed<kLane, 3, kListed>(lane.kk, val, AtomicFlush{y}, list);
   }
 }
 
@@ -352,8 +307,10 @@ __global__ __launch_bounds__(kLT) __attribute__((amdgpu_waves_per_eu(4))) void k
     const double* __restrict__ x = IO == kIoApply ? a.x0 + col * a.ldx : nullptr;
     const float* __restrict__ d = IO == kIoRhs ? a.d0 + col * a.ldx : nullptr;
     double* __restrict__ y = IO == kIoPlain ? nullptr : a.y0 + col * a.ldy;
-    const int64_t in0 = c.out0 - a.lam;
-    const int64_t b0 = c.blk_start, b1 = c.blk_start + c.blk_len;
+    const SegmentStreams win =
+        segment_streams(a.lpix, a.wq, a.wu, IO == kIoPlain ? a.t : d, c.out0 - a.lam);
+    int lo, hi;
+    window_range(c, a.lam, NN, lo, hi);
 
     // ---- F1: fill 64 columns, DFT over n1, twiddle, store tile rows ----------------------
 #pragma unroll 1
@@ -363,7 +320,7 @@ __global__ __launch_bounds__(kLT) __attribute__((amdgpu_waves_per_eu(4))) void k
         const int n1 = rr * kFillRows + fr;
         const int w = 2 * (n1 * kN2 + kG * g) + kLane * fq;  // window sample of the lane
         float v[kLane];
-        fill_lane<IO>(a, x, d, in0 + w, b0, b1, v);
+        fill_lane<IO>(win, x, w, lo, hi, v);
         float2* dst = buf + n1 * kS + 4 * fq;
 #pragma unroll
         for (int j = 0; j < kLane / 2; ++j) dst[j] = make_float2(v[2 * j], v[2 * j + 1]);
@@ -445,7 +402,7 @@ __global__ __launch_bounds__(kLT) __attribute__((amdgpu_waves_per_eu(4))) void k
           v[2 * j + 1] = -F.y;
         }
         const int o = 2 * (m1 * kN2 + kG * g) + kLane * fq - a.lam;
-        drain_lane<IO>(a, y, c, o, v, buf + m1w * kS);
+        drain_lane<IO>(a, win, y, c, o, v, buf + m1w * kS);
       }
       __syncthreads();
     }
@@ -515,7 +472,6 @@ mm_status launch_toeplitz_long(Plan* P, const float* t, float* u, float2* tiles,
   LongArgs a = base_args(P, tiles, done);
   a.t = t;
   a.u = u;
-  a.vec = ((reinterpret_cast<uintptr_t>(t) | reinterpret_cast<uintptr_t>(u)) & 15u) == 0;
   a.n_work = P->n_chunks;
   return launch_long<kIoPlain>(P, a, s);
 }
@@ -539,10 +495,7 @@ mm_status launch_apply_long(Plan* P, const double* x, const float* d, int64_t ld
   a.ldy = ldy;
   a.ncol = ncol;
   a.n_work = static_cast<int>(n_work);
-  if (d != nullptr) {
-    a.vec = (reinterpret_cast<uintptr_t>(d) & 15u) == 0 && (ldx & 3) == 0;
-    return launch_long<kIoRhs>(P, a, s);
-  }
+  if (d != nullptr) return launch_long<kIoRhs>(P, a, s);
   return launch_long<kIoApply>(P, a, s);
 }
 

@@ -120,25 +120,31 @@ __device__ __forceinline__ int wave_exclusive_count(int c, int lane, int& total)
   return before;
 }
 
+// LDS of a wavefront's run list: CAP keys, then NV CAP values.
+template <int NV, int CAP>
+constexpr int run_list_bytes() {
+  return CAP * static_cast<int>(sizeof(int) + NV * sizeof(double));
+}
+
 // The same merge, but the runs that the wavefront completes are first listed in LDS (CAP slots
-// of one key and NV values per wavefront, `skey` and `sval`) and then flushed one run per lane:
-// ceil(R / 64) rounds of NV atomics for R runs.  The direct form above issues one round at every
-// lane position where some lane closes a run inside it, which on scans with short runs (a
-// circle clipping pixel corners) means several rounds of nearly idle atomic instructions per
-// wavefront.  Runs beyond CAP are flushed directly.
-//
-// kByComponent flushes the list one value per lane instead (lanes NV r .. NV r + NV - 1 take the
-// NV values of run r, through flush.one(key, component, value)): ceil(NV R / 64) instructions,
-// and the values of one run go out in one instruction.  Where the runs of a wavefront fall on
-// different cache lines (pixel ids far apart along the scan), a run then costs one memory-side
-// atomic request instead of NV.
-template <int SPL, int NV, int CAP, class Flush, bool kByComponent = false>
+// of one key and NV values per wavefront, at `list`, 8-byte aligned) and then flushed one value
+// per lane (lanes NV r .. NV r + NV - 1 take the NV values of run r, through
+// flush.one(key, component, value)): ceil(NV R / 64) instructions for R runs, and the values of
+// one run go out in one instruction.  The direct form above issues one round at every lane
+// position where some lane closes a run inside it, which on scans with short runs (a circle
+// clipping pixel corners) means several rounds of nearly idle atomic instructions per wavefront;
+// and where the runs fall on different cache lines (pixel ids far apart along the scan), a run
+// costs one memory-side atomic request instead of NV.  More than CAP runs are listed and flushed
+// CAP at a time.
+template <int SPL, int NV, int CAP, class Flush>
 __device__ __forceinline__ void wave_merge_runs_listed(const int (&key)[SPL],
                                                        const double (&v)[SPL][NV],
-                                                       const Flush& flush, int* skey,
-                                                       double* sval) {
+                                                       const Flush& flush, void* list) {
   static_assert(SPL >= 2 && SPL <= 9, "inner-run counts must fit the 3-bit wavefront prefix");
   const int lane = static_cast<int>(threadIdx.x & 63u);
+  int* skey = static_cast<int*>(list);
+  double* sval = reinterpret_cast<double*>(skey + CAP);
+  static_assert(CAP % 2 == 0, "8-byte aligned values");
 
   // ---- runs inside the lane: count, then list ---------------------------------------------
   // A run starting at a key change j > 0 lies inside the lane when another change follows.
@@ -154,44 +160,50 @@ __device__ __forceinline__ void wave_merge_runs_listed(const int (&key)[SPL],
   const int in_base = wave_exclusive_count<3>(n_in, lane, r_in);
   wave_lds_sync();  // the previous call's listed runs have been read before slots are reused
 
+  auto put = [&](int slot, int k, const double (&w)[NV]) {
+    skey[slot] = k;
+#pragma unroll
+    for (int c = 0; c < NV; ++c) sval[slot * NV + c] = w[c];
+  };
+  // The lane's walk: lists its inner runs whose slots lie in [first, first + CAP) and leaves its
+  // first run (when it holds more than one) in head and its last in acc.
   double acc[NV];
   double head[NV];
-#pragma unroll
-  for (int c = 0; c < NV; ++c) {
-    acc[c] = v[0][c];
-    head[c] = 0.0;
-  }
-  int cur = key[0];
-  int hk = -1;
+  int hk = -1, tk = -1;
   bool single = true;
-  int slot = in_base;
+  auto walk = [&](int first) {
 #pragma unroll
-  for (int j = 1; j < SPL; ++j) {
-    if (key[j] != cur) {
-      if (single) {
-        hk = cur;
-#pragma unroll
-        for (int c = 0; c < NV; ++c) head[c] = acc[c];
-        single = false;
-      } else if (cur >= 0) {
-        if (slot < CAP) {
-          skey[slot] = cur;
-#pragma unroll
-          for (int c = 0; c < NV; ++c) sval[slot * NV + c] = acc[c];
-        } else {
-          flush(cur, acc);
-        }
-        ++slot;
-      }
-      cur = key[j];
-#pragma unroll
-      for (int c = 0; c < NV; ++c) acc[c] = v[j][c];
-    } else {
-#pragma unroll
-      for (int c = 0; c < NV; ++c) acc[c] += v[j][c];
+    for (int c = 0; c < NV; ++c) {
+      acc[c] = v[0][c];
+      head[c] = 0.0;
     }
-  }
-  const int tk = cur;
+    int cur = key[0];
+    hk = -1;
+    single = true;
+    int slot = in_base - first;
+#pragma unroll
+    for (int j = 1; j < SPL; ++j) {
+      if (key[j] != cur) {
+        if (single) {
+          hk = cur;
+#pragma unroll
+          for (int c = 0; c < NV; ++c) head[c] = acc[c];
+          single = false;
+        } else if (cur >= 0) {
+          if (static_cast<unsigned>(slot) < static_cast<unsigned>(CAP)) put(slot, cur, acc);
+          ++slot;
+        }
+        cur = key[j];
+#pragma unroll
+        for (int c = 0; c < NV; ++c) acc[c] = v[j][c];
+      } else {
+#pragma unroll
+        for (int c = 0; c < NV; ++c) acc[c] += v[j][c];
+      }
+    }
+    tk = cur;
+  };
+  walk(0);
 
   // ---- segmented inclusive scan of the lane tails (as in the direct form) -----------------
   const int prev_tk = __shfl_up(tk, 1);
@@ -223,56 +235,38 @@ __device__ __forceinline__ void wave_merge_runs_listed(const int (&key)[SPL],
   const int next_hk = __shfl_down(hk, 1);
 
   const bool has_head = !single && hk >= 0;
-  if (has_head && lane > 0 && prev_tk == hk) {
+  double H[NV];
 #pragma unroll
-    for (int c = 0; c < NV; ++c) head[c] += prevS[c];
-  }
+  for (int c = 0; c < NV; ++c)
+    H[c] = has_head && lane > 0 && prev_tk == hk ? head[c] + prevS[c] : head[c];
   const bool ends = (lane == 63) || next_start;
   const bool has_tail =
       ends && tk >= 0 && !((lane < 63) && !next_single && next_hk == tk);
   const int n_ht = (has_head ? 1 : 0) + (has_tail ? 1 : 0);
+  const int head_key = hk, tail_key = tk;
   int r_ht = 0;
-  int s2 = r_in + wave_exclusive_count<2>(n_ht, lane, r_ht);
-  if (has_head) {
-    if (s2 < CAP) {
-      skey[s2] = hk;
-#pragma unroll
-      for (int c = 0; c < NV; ++c) sval[s2 * NV + c] = head[c];
-    } else {
-      flush(hk, head);
-    }
-    ++s2;
-  }
-  if (has_tail) {
-    if (s2 < CAP) {
-      skey[s2] = tk;
-#pragma unroll
-      for (int c = 0; c < NV; ++c) sval[s2 * NV + c] = S[c];
-    } else {
-      flush(tk, S);
-    }
-  }
+  const int s_head = r_in + wave_exclusive_count<2>(n_ht, lane, r_ht);
+  const int s_tail = s_head + (has_head ? 1 : 0);
+  const int total = r_in + r_ht;
 
-  // ---- one listed run (or one value of one) per lane ---------------------------------------
-  wave_lds_sync();  // runs listed by other lanes of the wavefront are visible
-  const int listed = r_in + r_ht < CAP ? r_in + r_ht : CAP;
-  if constexpr (kByComponent) {
-    const int n = listed * NV;
+  // ---- list heads and tails, flush one value of one listed run per lane --------------------
+  for (int first = 0;;) {
+    if (has_head && static_cast<unsigned>(s_head - first) < static_cast<unsigned>(CAP))
+      put(s_head - first, head_key, H);
+    if (has_tail && static_cast<unsigned>(s_tail - first) < static_cast<unsigned>(CAP))
+      put(s_tail - first, tail_key, S);
+    wave_lds_sync();  // runs listed by other lanes of the wavefront are visible
+    const int n = min(total - first, CAP) * NV;
     for (int e = lane; e - lane < n; e += 64) {
       if (e < n) {
         const int r = e / NV;
         flush.one(skey[r], e - r * NV, sval[e]);
       }
     }
-  } else {
-    for (int r = lane; r - lane < listed; r += 64) {
-      if (r < listed) {
-        double w[NV];
-#pragma unroll
-        for (int c = 0; c < NV; ++c) w[c] = sval[r * NV + c];
-        flush(skey[r], w);
-      }
-    }
+    first += CAP;
+    if (first >= total) break;  // wavefront-uniform
+    wave_lds_sync();  // the listed runs have been read before their slots are reused
+    if (first < r_in) walk(first);
   }
 }
 

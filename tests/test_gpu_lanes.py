@@ -1,0 +1,95 @@
+"""GPU gather and scatter lanes: windows that start at any sample, flagged samples inside a lane,
+and runs of every length, against the FP64 oracle.
+
+A lane holds 8 consecutive samples.  Cases: one to nine samples per pixel (a lane then sees one to
+eight pixels, and a wavefront completes up to 512 runs, eight times the 64 that its list holds);
+many flags (lanes that begin, end or consist of flagged samples) with NaN weights at the flagged
+samples, whose values are nowhere used; odd detector lengths and intervals, so that windows start
+at every alignment; bands short enough for the scatter's last list to reach past the window.
+
+Tolerances: P x within one FP32 ulp; P^T u 1e-12 relative; A x and b of the mixed-precision
+products relative L2 3e-6 (FP32 time domain and transform); of FP64 plans 1e-12 of the norm of
+|P|^T |N^-1| |P| |x|, whose elements bound the sums that form each result.
+"""
+
+import dataclasses
+
+import numpy as np
+import pytest
+
+import oracle as O
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+
+
+def _rel(a, b):
+    return np.linalg.norm(np.asarray(a, np.float64) - b) / np.linalg.norm(b)
+
+
+def _problem(dwell, lam, flag_frac, n_dets=3, per_det=30011, interval=9001, side=20):
+    prob = synth.make_ground(cfg_id=700 + 10 * dwell + n_dets, n_dets=n_dets,
+                             samples_per_det=per_det, interval=interval, side=side, dwell=dwell,
+                             lam=lam, flag_frac=flag_frac)
+    ref = O.plan_from_problem(prob)
+    skip = prob.pix < 0
+    gpu = dataclasses.replace(prob, wq=np.where(skip, np.float32("nan"), prob.wq),
+                              wu=np.where(skip, np.float32("nan"), prob.wu))
+    return gpu, ref
+
+
+@pytest.mark.parametrize("dwell", [1, 2, 4, 7, 9])
+@pytest.mark.parametrize("flag_frac", [0.02, 0.6])
+def test_lanes_scan_and_bin(gpu_lib, dwell, flag_frac):
+    prob, ref = _problem(dwell, 40, flag_frac)
+    plan = gpu_lib.Plan.from_problem(prob)
+    g = np.random.default_rng(dwell)
+    x = g.standard_normal((ref.n_kept, 3))
+    import torch
+    for shift in (0, 1, 3):  # time streams at any float address
+        t = torch.empty(prob.n_samples + 4, device="cuda")[shift:shift + prob.n_samples]
+        got = plan.unpoint(_dev(x), t=t).cpu().numpy()
+        want = O.unpoint(ref, x)
+        assert np.all(np.abs(got - want) <= 2.0 ** -23 * np.abs(want) + 1e-30)
+        u = g.standard_normal(prob.n_samples + 4).astype(np.float32)
+        du = _dev(u)[shift:shift + prob.n_samples]
+        y = plan.point(du).cpu().numpy()
+        assert _rel(y, O.point(ref, u[shift:shift + prob.n_samples].astype(np.float64))) <= 1e-12
+
+
+# every product kernel: LDS (one wavefront per segment .. 16), register, long; and bands so short
+# that a wavefront's outputs start within 256 samples of the window's end
+PRODUCTS = [(300, 0), (40, 2048), (1, 2048), (85, 2048), (900, 0), (85, 4096), (2000, 0),
+            (200, 8192), (3000, 0), (5000, 0), (8192, 0), (9000, 0), (12001, 65536),
+            (20001, 131072)]
+
+
+@pytest.mark.parametrize("dwell,flag_frac", [(1, 0.02), (3, 0.3), (7, 0.02)])
+@pytest.mark.parametrize("lam,fft_size", PRODUCTS)
+def test_lanes_system_product(gpu_lib, lam, fft_size, dwell, flag_frac):
+    prob, ref = _problem(dwell, lam, flag_frac, n_dets=2, per_det=60013, interval=20011)
+    plan = gpu_lib.Plan.from_problem(prob, toeplitz_algo=gpu_lib.TOEPLITZ_FFT, fft_size=fft_size)
+    x = np.random.default_rng(lam).standard_normal((ref.n_kept, 3))
+    assert _rel(plan.apply_A(_dev(x)).cpu().numpy(), O.apply_A(ref, x)) <= 3e-6
+    n = prob.n_samples
+    d = np.concatenate([np.zeros(1, np.float32), prob.d[0]])
+    b = plan.rhs(_dev(d)[1:1 + n]).cpu().numpy()  # data at an odd float address
+    assert _rel(b, O.rhs(ref, prob.d[0])) <= 3e-6
+
+
+@pytest.mark.parametrize("dwell,flag_frac", [(1, 0.02), (3, 0.3), (7, 0.02)])
+@pytest.mark.parametrize("lam", [12, 600, 1025, 4096, 8192, 20001])
+def test_lanes_fp64_product(gpu_lib, lam, dwell, flag_frac):
+    prob, ref = _problem(dwell, lam, flag_frac, n_dets=2, per_det=60013, interval=20011)
+    plan = gpu_lib.Plan.from_problem(prob, precision=gpu_lib.PRECISION_FP64)
+    x = np.random.default_rng(lam).standard_normal((ref.n_kept, 3))
+    absref = dataclasses.replace(ref, bands=[np.abs(b) for b in ref.bands],
+                                 wq=np.abs(ref.wq), wu=np.abs(ref.wu))
+    scale = np.linalg.norm(O.apply_A(absref, np.abs(x)))
+    got = plan.apply_A(_dev(x)).cpu().numpy()
+    assert np.linalg.norm(got - O.apply_A(ref, x)) <= 1e-12 * scale
