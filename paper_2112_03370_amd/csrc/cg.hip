@@ -45,11 +45,46 @@ __device__ __forceinline__ double reduce_partials(const double* p, int n, double
   return block_sum(v, sh);
 }
 
-// Scalars of the recurrence: every workgroup of the kernel that needs alpha or beta sums the
+// Sum of partials[0..n) by one wavefront in a fixed order, the same value in every lane.
+__device__ __forceinline__ double wave_total(const double* p, int n) {
+  double v = 0.0;
+  for (int i = static_cast<int>(threadIdx.x & 63u); i < n; i += 64) v += p[i];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
+}
+
+// The same for the whole workgroup.  A wavefront that sums all of a few partials itself needs no
+// barrier; with many, the four wavefronts share them (at 512 partials the direction kernel takes
+// 9.8 us with each wavefront summing all, 7.0 us shared).
+__device__ __forceinline__ double group_total(const double* p, int n, double* sh) {
+  if (n <= 128) return wave_total(p, n);
+  double v = 0.0;
+  for (int i = threadIdx.x; i < n; i += kThreads) v += p[i];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double s = 0.0;
+#pragma unroll
+  for (int i = 0; i < kThreads / 64; ++i) s += sh[i];
+  return s;
+}
+
+// Keeps a loaded value above the code that follows: the loads of a kernel then all travel behind
+// one wait, instead of sinking below the tests they do not depend on.
+__device__ __forceinline__ void pin(double& v) { asm volatile("" : "+v"(v)); }
+
+// Scalars of the recurrence: every wavefront of the kernel that needs alpha or beta sums the
 // previous kernel's per-workgroup partials itself, in the same fixed order, so all of them hold
-// the same value (the kernel boundary makes the partials visible; no fence or counter).
+// the same value (the kernel boundary makes the partials visible; no fence, counter or barrier).
 // Workgroup 0 alone records the scalars in the state; the state fields that the other
 // workgroups read in that kernel were written one kernel earlier.
+//
+// On small maps these kernels are bound by latency, not bytes (a 64 x 64 map's vectors are 100 KB
+// each): a pixel per thread, its loads issued together with those of the partials and of the
+// state.  At 4,096 pixels, us per launch: <p, q> 4.7 -> 4.2, update 8.5 -> 4.4, direction 5.4
+// -> 3.8 against four workgroups that walked four pixels a thread behind the scalars.
 
 // z = M_BD r for pixel i of a [*, n_kept, 3] layout (minv shared across columns).
 __device__ __forceinline__ void bj_apply(const double* __restrict__ m6, const double* r,
@@ -147,14 +182,68 @@ __global__ __launch_bounds__(kThreads) void k_dot_pq(const double* __restrict__ 
                                                      double* partial, const CgState* st,
                                                      int nrb) {
   __shared__ double sh[kThreads / 64];
-  if (st->done) return;
+  constexpr int kBatch = 3;  // a pixel's worth of elements per thread and round
+  const int done = st->done;
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
   double v = 0.0;
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; i < n;
-       i += static_cast<int64_t>(gridDim.x) * kThreads)
-    v += p[i] * q[i];
+       i += kBatch * stride) {
+    double a[kBatch], b[kBatch];
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) {
+      const bool in = i + k * stride < n;
+      a[k] = in ? p[i + k * stride] : 0.0;
+      b[k] = in ? q[i + k * stride] : 0.0;
+    }
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) {
+      pin(a[k]);
+      pin(b[k]);
+    }
+    if (done) return;
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) v += a[k] * b[k];
+  }
   const double s = block_sum(v, sh);
-  if (threadIdx.x == 0) partial[2 * nrb + blockIdx.x] = s;
+  if (threadIdx.x == 0 && !done) partial[2 * nrb + blockIdx.x] = s;
 }
+
+// One pixel's part of the update.
+struct UpdatePixel {
+  double x[3], p[3], q[3], r[3], m6[6];
+
+  __device__ __forceinline__ void load(const double* minv, const double* xg, const double* pg,
+                                       const double* qg, const double* rg, int64_t i) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      x[c] = xg[3 * i + c];
+      p[c] = pg[3 * i + c];
+      q[c] = qg[3 * i + c];
+      r[c] = rg[3 * i + c];
+    }
+#pragma unroll
+    for (int c = 0; c < 6; ++c) m6[c] = minv[6 * i + c];
+  }
+
+  __device__ __forceinline__ void apply(double alpha, double* xg, double* rg, double* zg,
+                                        double* qg, int64_t i, double& rr, double& rz) {
+    double rv[3], zv[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      xg[3 * i + c] = x[c] + alpha * p[c];
+      rv[c] = r[c] - alpha * q[c];
+      qg[3 * i + c] = 0.0;
+      rg[3 * i + c] = rv[c];
+      rr += rv[c] * rv[c];
+    }
+    bj_apply(m6, rv, zv);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      zg[3 * i + c] = zv[c];
+      rz += rv[c] * zv[c];
+    }
+  }
+};
 
 // alpha = <r, z> / <p, q> from the <p, q> partials, then x += alpha p, r -= alpha q,
 // z = M_BD r, q = 0, with the partials of ||r||^2 and <r, z>.
@@ -163,13 +252,23 @@ __global__ __launch_bounds__(kThreads) void k_update(const double* __restrict__ 
                                                      const double* __restrict__ p, double* q,
                                                      int64_t n_kept, double* partial, int nrb,
                                                      CgState* st) {
-  __shared__ double sh[kThreads / 64];
-  __shared__ double s_pq;
-  if (st->done) return;
-  const double pq0 = reduce_partials(partial + 2 * nrb, nrb, sh);
-  if (threadIdx.x == 0) s_pq = pq0;
-  __syncthreads();
-  const double pq = s_pq;
+  __shared__ double sh[kThreads / 64], sh_pq[kThreads / 64];
+  int64_t i = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
+  UpdatePixel px{};
+  if (i < n_kept) px.load(minv, x, p, q, r, i);
+  const int done = st->done;
+  const double rz_old = st->rz;
+  const double pq = group_total(partial + 2 * nrb, nrb, sh_pq);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    pin(px.x[c]);
+    pin(px.p[c]);
+    pin(px.q[c]);
+    pin(px.r[c]);
+    pin(px.m6[c]);
+    pin(px.m6[3 + c]);
+  }
+  if (done) return;
   if (!(pq > 0.0)) {  // the same test in every workgroup
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       st->pq = pq;
@@ -177,30 +276,19 @@ __global__ __launch_bounds__(kThreads) void k_update(const double* __restrict__ 
     }
     return;
   }
-  const double alpha = st->rz / pq;
+  const double alpha = rz_old / pq;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     st->pq = pq;
     st->alpha = alpha;
-    st->rz_prev = st->rz;
+    st->rz_prev = rz_old;
     st->iter_next = st->iter + 1;
   }
   double rr = 0.0, rz = 0.0;
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; i < n_kept;
-       i += static_cast<int64_t>(gridDim.x) * kThreads) {
-    double rv[3], zv[3];
-    for (int c = 0; c < 3; ++c) {
-      const int64_t j = 3 * i + c;
-      x[j] += alpha * p[j];
-      rv[c] = r[j] - alpha * q[j];
-      q[j] = 0.0;
-      r[j] = rv[c];
-      rr += rv[c] * rv[c];
-    }
-    bj_apply(minv + 6 * i, rv, zv);
-    for (int c = 0; c < 3; ++c) {
-      z[3 * i + c] = zv[c];
-      rz += rv[c] * zv[c];
-    }
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
+  while (i < n_kept) {
+    px.apply(alpha, x, r, z, q, i, rr, rz);
+    i += stride;
+    if (i < n_kept) px.load(minv, x, p, q, r, i);
   }
   const double s0 = block_sum(rr, sh);
   const double s1 = block_sum(rz, sh);
@@ -216,27 +304,40 @@ __global__ __launch_bounds__(kThreads) void k_update(const double* __restrict__ 
 __global__ __launch_bounds__(kThreads) void k_direction(const double* __restrict__ z, double* p,
                                                         int64_t n, const double* partial,
                                                         int nrb, CgState* st) {
-  __shared__ double sh[kThreads / 64];
-  __shared__ double s_rr, s_rz;
-  if (st->done) return;
-  const double rr0 = reduce_partials(partial, nrb, sh);
-  const double rz0 = reduce_partials(partial + nrb, nrb, sh);
-  if (threadIdx.x == 0) {
-    s_rr = rr0;
-    s_rz = rz0;
+  constexpr int kBatch = 3;
+  __shared__ double sh_rr[kThreads / 64], sh_rz[kThreads / 64];
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
+  int64_t i = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
+  double zv[kBatch], pv[kBatch];
+  auto load = [&]() {
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) {
+      const bool in = i + k * stride < n;
+      zv[k] = in ? z[i + k * stride] : 0.0;
+      pv[k] = in ? p[i + k * stride] : 0.0;
+    }
+  };
+  load();
+  const int was_done = st->done;
+  const double tol2bb = st->tol2bb, rz_prev = st->rz_prev;
+  const int iter = st->iter_next, max_iter = st->max_iter;
+  const double rr = group_total(partial, nrb, sh_rr);
+  const double rz = group_total(partial + nrb, nrb, sh_rz);
+#pragma unroll
+  for (int k = 0; k < kBatch; ++k) {
+    pin(zv[k]);
+    pin(pv[k]);
   }
-  __syncthreads();
-  const double rr = s_rr, rz = s_rz;
-  const int iter = st->iter_next;
+  if (was_done) return;
   int done = 0;
-  if (rr < st->tol2bb) {
+  if (rr < tol2bb) {
     done = 1;
-  } else if (iter >= st->max_iter) {
+  } else if (iter >= max_iter) {
     done = 3;
   } else if (!(rz > 0.0)) {
     done = 2;
   }
-  const double beta = done ? 0.0 : rz / st->rz_prev;
+  const double beta = done ? 0.0 : rz / rz_prev;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     st->iter = iter;
     st->rr = rr;
@@ -248,9 +349,13 @@ __global__ __launch_bounds__(kThreads) void k_direction(const double* __restrict
     }
   }
   if (done) return;
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; i < n;
-       i += static_cast<int64_t>(gridDim.x) * kThreads)
-    p[i] = z[i] + beta * p[i];
+  while (i < n) {
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k)
+      if (i + k * stride < n) p[i + k * stride] = zv[k] + beta * pv[k];
+    i += kBatch * stride;
+    if (i < n) load();
+  }
 }
 
 // partial = ||b - y||^2 per block
