@@ -9,7 +9,9 @@
 // drops directions below 1e-12 of the largest eigenvalue, a safeguard against the rank loss of
 // the search block (the paper's Cholesky square root has none).  Converged columns leave the
 // block (their X is final).  The t x t algebra runs on the host in FP64; the tall-skinny Gram
-// products, updates and the block-Jacobi apply run in the kernels below, in FP64.
+// products, updates and the block-Jacobi apply run in the kernels below, in FP64.  An iteration
+// meets the host once: G and H1 come back (with the outcome of the previous iteration's stop
+// tests, which the device has already applied to Z), a1 and G^+ go out.
 //
 // Block size: opts->block >= 2 fixes t; opts->block < 0 tunes it: the first column groups are
 // solved with t = 1 (8 columns, each alone by Alg. 1), 8, 16, 32 in turn (real work, not a
@@ -35,87 +37,108 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kMaxT = 32;
 
-// Gram partials partial[x][i * tv + j] = sum over workgroup x's rows of U_i[r] V_j[r], streamed:
-// workgroup (x, y) takes the 8 x 8 block y of column pairs and
-// a grid-stride share of the rows; each thread keeps its 64 pair sums in registers over all its
-// rows (8 + 8 coalesced loads and 64 FMAs per row, no barrier in the loop), then the workgroup
-// reduces them once (wavefront shuffles, then LDS across the 4 wavefronts) in a fixed order.
-// (A tiled form that staged 64-row tiles of U and V in LDS waited on memory at every tile and
-// took ~160 us per call for t = 8.)
-constexpr int kGB = 8;
+// Gram partials of U^T V1 (tu x tv1) and U^T V2 (tu x tv2; tv2 = 0: one product), summed over
+// workgroup x's rows, on the FP64 matrix cores: workgroup (x, y) takes block y of 16 columns of U
+// by 16 columns of [V1 | V2] and a grid-stride share of the rows, each wavefront 32 rows a step.
+// A lane loads 8 consecutive rows of one column of each operand (64 contiguous bytes) and feeds
+// them to eight 16 x 16 x 4 products: which four rows meet in one product does not matter as long
+// as both operands agree.  The four wavefronts' blocks are added in LDS in a fixed order.
+// partial[x] holds the tu x tv1 entries, then the tu x tv2 entries.
+//
+// The kernel is bound by its latency (3 MB a column at 16,384 pixels): a form with 64 sums per
+// thread needed 384 shuffles to reduce them, so it could only afford 12 workgroups there, 30 us
+// for eight columns against 5 us with a workgroup per 128 rows.
+constexpr int kGB = 16;        // block of column pairs
+constexpr int kGRows = 8;      // consecutive rows per lane and step
+constexpr int kGStep = 4 * kGRows;  // rows per wavefront and step
+constexpr int kWaves = kThreads / 64;
 
-// Two products against the same U in one launch: pair blocks y < nb1 belong to U^T V1, the
-// rest to U^T V2 (tv2 = 0: one product); partial[x] holds the tu x tv1 entries, then the
-// tu x tv2 entries.
-__global__ __launch_bounds__(kThreads) void k_gram_rb(const double* __restrict__ U, int tu,
-                                                      int64_t ldu, const double* __restrict__ V1,
-                                                      int tv1, const double* __restrict__ V2,
-                                                      int tv2, int64_t ldv, int64_t n,
-                                                      double* __restrict__ partial) {
-  __shared__ double red[kThreads / 64][kGB * kGB];
-  const int nbu = (tu + kGB - 1) / kGB;
-  const int nb1 = nbu * ((tv1 + kGB - 1) / kGB);
-  const bool second = static_cast<int>(blockIdx.y) >= nb1;
-  const double* __restrict__ V = second ? V2 : V1;
-  const int tv = second ? tv2 : tv1;
-  const int yb = second ? static_cast<int>(blockIdx.y) - nb1 : static_cast<int>(blockIdx.y);
-  const int64_t off = second ? static_cast<int64_t>(tu) * tv1 : 0;
-  const int nbv = (tv + kGB - 1) / kGB;
-  const int i0 = (yb / nbv) * kGB, j0 = (yb % nbv) * kGB;
-  const int nu = min(kGB, tu - i0), nv = min(kGB, tv - j0);
-  double acc[kGB][kGB];
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+// Rows [r, r + kGRows) of a column (null: zeros), zero past its end.
+__device__ __forceinline__ void gram_rows(const double* __restrict__ col, int64_t r, int64_t n,
+                                          double (&a)[kGRows]) {
 #pragma unroll
-  for (int a = 0; a < kGB; ++a)
+  for (int k = 0; k < kGRows; ++k) a[k] = 0.0;
+  if (col == nullptr) return;
+  if (r + kGRows <= n) {
 #pragma unroll
-    for (int b = 0; b < kGB; ++b) acc[a][b] = 0.0;
-  for (int64_t r = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; r < n;
-       r += static_cast<int64_t>(gridDim.x) * kThreads) {
-    double u[kGB], v[kGB];
+    for (int k = 0; k < kGRows; ++k) a[k] = col[r + k];
+  } else {
 #pragma unroll
-    for (int a = 0; a < kGB; ++a) u[a] = a < nu ? U[(i0 + a) * ldu + r] : 0.0;
-#pragma unroll
-    for (int b = 0; b < kGB; ++b) v[b] = b < nv ? V[(j0 + b) * ldv + r] : 0.0;
-#pragma unroll
-    for (int a = 0; a < kGB; ++a)
-#pragma unroll
-      for (int b = 0; b < kGB; ++b) acc[a][b] = fma(u[a], v[b], acc[a][b]);
+    for (int k = 0; k < kGRows; ++k)
+      if (r + k < n) a[k] = col[r + k];
   }
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+}
+
+__global__ __launch_bounds__(kThreads) void k_gram(const double* __restrict__ U, int tu,
+                                                   const double* __restrict__ V1, int tv1,
+                                                   const double* __restrict__ V2, int tv2,
+                                                   int64_t n, double* __restrict__ partial) {
+  __shared__ double red[kWaves][kGB * kGB];
+  const int tv = tv1 + tv2, nbv = (tv + kGB - 1) / kGB;
+  const int i0 = (static_cast<int>(blockIdx.y) / nbv) * kGB;
+  const int j0 = (static_cast<int>(blockIdx.y) % nbv) * kGB;
+  const int lane = static_cast<int>(threadIdx.x & 63u);
+  const int wave = static_cast<int>(threadIdx.x >> 6);
+  const int c = lane & 15, q = lane >> 4;
+  const int i = i0 + c, j = j0 + c;
+  const double* u = i < tu ? U + static_cast<int64_t>(i) * n : nullptr;
+  const double* v = j < tv1   ? V1 + static_cast<int64_t>(j) * n
+                    : j < tv ? V2 + static_cast<int64_t>(j - tv1) * n
+                             : nullptr;
+  v4d acc = {0.0, 0.0, 0.0, 0.0};
+  for (int64_t r0 = (static_cast<int64_t>(blockIdx.x) * kWaves + wave) * kGStep; r0 < n;
+       r0 += static_cast<int64_t>(gridDim.x) * kWaves * kGStep) {
+    const int64_t r = r0 + kGRows * q;
+    double a[kGRows], b[kGRows];
+    gram_rows(u, r, n, a);
+    gram_rows(v, r, n, b);
 #pragma unroll
-  for (int a = 0; a < kGB; ++a)
+    for (int k = 0; k < kGRows; ++k)
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[k], b[k], acc, 0, 0, 0);
+  }
+  // lane (q, c) holds entries (q + 4 k, c) of the block
 #pragma unroll
-    for (int b = 0; b < kGB; ++b) {
-      double x = acc[a][b];
-      for (int o = 32; o > 0; o >>= 1) x += __shfl_down(x, o);
-      if (lane == 0) red[wv][a * kGB + b] = x;
-    }
+  for (int k = 0; k < 4; ++k) red[wave][(q + 4 * k) * kGB + c] = acc[k];
   __syncthreads();
-  if (threadIdx.x < kGB * kGB) {
-    const int a = threadIdx.x / kGB, b = threadIdx.x % kGB;
-    if (a < nu && b < nv) {
-      double x = 0.0;
+  const int bi = i0 + static_cast<int>(threadIdx.x) / kGB;
+  const int bj = j0 + static_cast<int>(threadIdx.x) % kGB;
+  if (bi < tu && bj < tv) {
+    double x = 0.0;
 #pragma unroll
-      for (int w = 0; w < kThreads / 64; ++w) x += red[w][threadIdx.x];
-      partial[static_cast<int64_t>(blockIdx.x) * tu * (tv1 + tv2) + off + (i0 + a) * tv +
-              (j0 + b)] = x;
-    }
+    for (int w = 0; w < kWaves; ++w) x += red[w][threadIdx.x];
+    const int at = bj < tv1 ? bi * tv1 + bj : tu * tv1 + bi * tv2 + (bj - tv1);
+    partial[static_cast<int64_t>(blockIdx.x) * tu * tv + at] = x;
   }
 }
 
 // out[e] = sum_w partial[w][e] in a fixed order: kRedEntries entries per workgroup, 16 threads
 // per entry each summing every 16th partial, then a fixed tree over the 16 sums (one thread per
-// entry walking all partials serially took ~150 us for 512 partials)
+// entry walking all partials serially took ~150 us for 512 partials).  Entries from count on come
+// from a second array (partial2, nwg2 rows of count2) and go to out2.
 constexpr int kRedEntries = kThreads / 16;
 
 __global__ __launch_bounds__(kThreads) void k_gram_reduce(const double* __restrict__ partial,
                                                           int nwg, int count,
-                                                          double* __restrict__ out) {
+                                                          double* __restrict__ out,
+                                                          const double* __restrict__ partial2,
+                                                          int nwg2, int count2,
+                                                          double* __restrict__ out2) {
   __shared__ double red[kThreads];
   const int le = threadIdx.x >> 4, lw = threadIdx.x & 15;
-  const int e = blockIdx.x * kRedEntries + le;
+  int e = blockIdx.x * kRedEntries + le;
+  const bool second = e >= count;
+  if (second) {
+    e -= count;
+    partial = partial2;
+    nwg = nwg2;
+    out = out2;
+  }
+  const int stride = second ? count2 : count;
   double s = 0.0;
-  if (e < count)
-    for (int w = lw; w < nwg; w += 16) s += partial[static_cast<int64_t>(w) * count + e];
+  if (e < stride)
+    for (int w = lw; w < nwg; w += 16) s += partial[static_cast<int64_t>(w) * stride + e];
   red[threadIdx.x] = s;
   __syncthreads();
 #pragma unroll
@@ -123,7 +146,7 @@ __global__ __launch_bounds__(kThreads) void k_gram_reduce(const double* __restri
     if (lw < h) red[threadIdx.x] += red[threadIdx.x + h];
     __syncthreads();
   }
-  if (lw == 0 && e < count) out[e] = red[threadIdx.x];
+  if (lw == 0 && e < stride) out[e] = red[threadIdx.x];
 }
 
 inline unsigned reduce_grid(int count) {
@@ -137,15 +160,20 @@ __device__ __forceinline__ const double* row_coefs(const double* p) {
   return p;
 }
 
-// X_cols[j] += sum_i Z_i a1[i][j];  R_j -= sum_i W_i a1[i][j];  rr partial of ||R_j||^2
+// X_cols[j] += sum_i Z_i a1[i][j];  R_j -= sum_i W_i a1[i][j];  rr partial of ||R_j||^2, for the
+// t columns of the block (TM >= t).  The rows of X (and of R) are loaded eight columns at a time
+// ahead of their stores: the compiler cannot tell the columns apart, and would wait for each
+// column's load behind the previous column's store (16 us against 12 us for eight columns at
+// 16,384 pixels).
 template <int TM>
 __global__ __launch_bounds__(kThreads) void k_block_update(
-    const double* __restrict__ Z, const double* __restrict__ W, int tz, double* __restrict__ R,
-    int ta, int64_t nu, double* __restrict__ x, const int32_t* __restrict__ cols,
+    const double* __restrict__ Z, const double* __restrict__ W, double* __restrict__ R, int t,
+    int64_t nu, double* __restrict__ x, const int32_t* __restrict__ cols,
     const double* __restrict__ a1, double* __restrict__ rr_partial) {
+  constexpr int kBatch = 8;
   __shared__ double sa[kMaxT * kMaxT];
   __shared__ double red[kThreads / 64][TM];
-  for (int e = threadIdx.x; e < tz * ta; e += kThreads) sa[e] = a1[e];
+  for (int e = threadIdx.x; e < t * t; e += kThreads) sa[e] = a1[e];
   __syncthreads();
   double rr[TM];
 #pragma unroll
@@ -155,34 +183,47 @@ __global__ __launch_bounds__(kThreads) void k_block_update(
     {  // X += Z a1 (one row of Z live at a time)
       double z[TM];
 #pragma unroll
-      for (int i = 0; i < TM; ++i) z[i] = i < tz ? Z[i * nu + r] : 0.0;
+      for (int i = 0; i < TM; ++i) z[i] = i < t ? Z[i * nu + r] : 0.0;
       const double* c = row_coefs(sa);
 #pragma unroll
-      for (int j = 0; j < TM; ++j) {
-        if (j < ta) {
-          double dx = 0.0;
+      for (int j0 = 0; j0 < TM; j0 += kBatch) {
+        double xv[kBatch];
 #pragma unroll
-          for (int i = 0; i < TM; ++i)
-            if (i < tz) dx += z[i] * c[i * ta + j];
-          x[static_cast<int64_t>(cols[j]) * nu + r] += dx;
+        for (int j = 0; j < kBatch; ++j)
+          xv[j] = j0 + j < t ? x[static_cast<int64_t>(cols[j0 + j]) * nu + r] : 0.0;
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+          if (j0 + j < t) {
+            double dx = 0.0;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+              if (i < t) dx += z[i] * c[i * t + j0 + j];
+            x[static_cast<int64_t>(cols[j0 + j]) * nu + r] = xv[j] + dx;
+          }
         }
       }
     }
     {  // R -= W a1, with the norms
       double w[TM];
 #pragma unroll
-      for (int i = 0; i < TM; ++i) w[i] = i < tz ? W[i * nu + r] : 0.0;
+      for (int i = 0; i < TM; ++i) w[i] = i < t ? W[i * nu + r] : 0.0;
       const double* c = row_coefs(sa);
 #pragma unroll
-      for (int j = 0; j < TM; ++j) {
-        if (j < ta) {
-          double dr = 0.0;
+      for (int j0 = 0; j0 < TM; j0 += kBatch) {
+        double rv[kBatch];
 #pragma unroll
-          for (int i = 0; i < TM; ++i)
-            if (i < tz) dr += w[i] * c[i * ta + j];
-          const double rn = R[j * nu + r] - dr;
-          R[j * nu + r] = rn;
-          rr[j] += rn * rn;
+        for (int j = 0; j < kBatch; ++j) rv[j] = j0 + j < t ? R[(j0 + j) * nu + r] : 0.0;
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+          if (j0 + j < t) {
+            double dr = 0.0;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+              if (i < t) dr += w[i] * c[i * t + j0 + j];
+            const double rn = rv[j] - dr;
+            R[(j0 + j) * nu + r] = rn;
+            rr[j0 + j] += rn * rn;
+          }
         }
       }
     }
@@ -195,36 +236,67 @@ __global__ __launch_bounds__(kThreads) void k_block_update(
     if (lane == 0) red[wv][j] = v;
   }
   __syncthreads();
-  if (threadIdx.x < ta) {
+  if (threadIdx.x < t) {
     double s = 0.0;
     for (int q = 0; q < kThreads / 64; ++q) s += red[q][threadIdx.x];
-    rr_partial[static_cast<int64_t>(blockIdx.x) * ta + threadIdx.x] = s;
+    rr_partial[static_cast<int64_t>(blockIdx.x) * t + threadIdx.x] = s;
   }
 }
 
-// Z_j <- MR_j - sum_i Z_i a2[i][j]  for j < tn (in place: each row reads all old Z first)
+// After an update: act[j] = 1 while column j's ||R_j||^2 has not passed under its limit, *done
+// once none is left, and a2 = G^+ H2 (t x t).  One workgroup.
+__global__ __launch_bounds__(kThreads) void k_block_coef(int t, const double* __restrict__ rr,
+                                                         const double* __restrict__ limit,
+                                                         const double* __restrict__ gi,
+                                                         const double* __restrict__ h2,
+                                                         double* __restrict__ a2,
+                                                         double* __restrict__ act,
+                                                         int32_t* __restrict__ done) {
+  const int j = threadIdx.x;
+  const bool live = j < t && !(rr[j] < limit[j]);
+  if (j < t) act[j] = live ? 1.0 : 0.0;
+  const int left = __syncthreads_count(live);
+  if (threadIdx.x == 0 && left == 0) *done = 1;
+  for (int e = threadIdx.x; e < t * t; e += kThreads) {
+    const int row = e / t, col = e % t;
+    double s = 0.0;
+    for (int k = 0; k < t; ++k) s += gi[row * t + k] * h2[k * t + col];
+    a2[e] = s;
+  }
+}
+
+// Z_j <- MR_j - sum_i Z_i a2[i][j]  for the columns still in the block, 0 for those that have
+// left it (in place: each row reads all old Z first)
 template <int TM>
-__global__ __launch_bounds__(kThreads) void k_block_direction(double* __restrict__ Z, int tz,
+__global__ __launch_bounds__(kThreads) void k_block_direction(double* __restrict__ Z, int t,
                                                               const double* __restrict__ MR,
-                                                              int tn, int64_t nu,
-                                                              const double* __restrict__ a2) {
+                                                              int64_t nu,
+                                                              const double* __restrict__ a2,
+                                                              const double* __restrict__ act) {
+  constexpr int kBatch = 8;
   __shared__ double sa[kMaxT * kMaxT];
-  for (int e = threadIdx.x; e < tz * tn; e += kThreads) sa[e] = a2[e];
+  for (int e = threadIdx.x; e < t * t; e += kThreads) sa[e] = a2[e];
   __syncthreads();
   for (int64_t r = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; r < nu;
        r += static_cast<int64_t>(gridDim.x) * kThreads) {
     double z[TM];
 #pragma unroll
-    for (int i = 0; i < TM; ++i) z[i] = i < tz ? Z[i * nu + r] : 0.0;
+    for (int i = 0; i < TM; ++i) z[i] = i < t ? Z[i * nu + r] : 0.0;
     const double* c = row_coefs(sa);
 #pragma unroll
-    for (int j = 0; j < TM; ++j) {
-      if (j < tn) {
-        double s = MR[j * nu + r];
+    for (int j0 = 0; j0 < TM; j0 += kBatch) {
+      double mr[kBatch];
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-          if (i < tz) s -= z[i] * c[i * tn + j];
-        Z[j * nu + r] = s;
+      for (int j = 0; j < kBatch; ++j) mr[j] = j0 + j < t ? MR[(j0 + j) * nu + r] : 0.0;
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j) {
+        if (j0 + j < t) {
+          double s = mr[j];
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+            if (i < t) s -= z[i] * c[i * t + j0 + j];
+          Z[(j0 + j) * nu + r] = act[j0 + j] != 0.0 ? s : 0.0;
+        }
       }
     }
   }
@@ -301,17 +373,26 @@ struct BlockWs {
   double* Z = nullptr;
   double* W = nullptr;
   double* MR = nullptr;
-  double* small = nullptr;    // t x t matrices
-  double* partial = nullptr;  // Gram / norm partials
-  int32_t* cols = nullptr;
+  double* small = nullptr;    // scalars and t x t matrices (k* offsets below)
+  double* partial = nullptr;  // Gram partials
+  double* rr_partial = nullptr;
+  int32_t* cols = nullptr;    // user column of each slot, then the done flag
   int cap = 0;
-  int nwg = 0;
 };
 
-// Rows per workgroup of the streamed Gram kernel: enough rows per thread that the final
-// reduction is a small share of the work.
-int gram_rb_grid(int64_t nu) {
-  int64_t g = (nu + 16 * kThreads - 1) / (16 * kThreads);
+// Layout of BlockWs::small (doubles).  An iteration reads [0, kG + 2 t^2) back in one copy: the
+// last update's norms and activity and the new Gram matrices; and writes [kA1, kA1 + 2 t^2).
+constexpr int kMat = kMaxT * kMaxT;
+constexpr int kRr = 0, kAct = kMaxT, kG = 2 * kMaxT;           // G, then H1
+constexpr int kA1 = kG + 2 * kMat;                             // a1, then G^+
+constexpr int kH2 = kA1 + 2 * kMat, kA2 = kH2 + kMat, kLimit = kA2 + kMat;
+constexpr int kSmall = kLimit + kMaxT;
+static_assert(kSmall + kMaxT <= kBlockHost, "pinned transfer area");
+
+// Workgroups of the Gram kernel: one step of each wavefront, at most one workgroup per CU and
+// column block (more partials would cost the reduction what they hide).
+int gram_grid(int64_t nu) {
+  const int64_t g = (nu + kWaves * kGStep - 1) / (kWaves * kGStep);
   return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(g, 256)));
 }
 
@@ -320,12 +401,13 @@ int rows_grid(int64_t nu) {
   return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(g, 1024)));
 }
 
-mm_status ensure_ws(Plan* P, BlockWs& ws, int t) {
+mm_status ensure_ws(Plan* P, Work& Wk, BlockWs& ws, int t) {
   if (ws.cap >= t) return MM_OK;
   const int64_t nu = 3 * P->n_kept;
   for (void* p : {static_cast<void*>(ws.R), static_cast<void*>(ws.Z), static_cast<void*>(ws.W),
                   static_cast<void*>(ws.MR), static_cast<void*>(ws.small),
-                  static_cast<void*>(ws.partial), static_cast<void*>(ws.cols)})
+                  static_cast<void*>(ws.partial), static_cast<void*>(ws.rr_partial),
+                  static_cast<void*>(ws.cols)})
     dev_free(p);
   ws = BlockWs{};
   auto alloc = [&](void** p, size_t bytes) -> mm_status {
@@ -340,11 +422,17 @@ mm_status ensure_ws(Plan* P, BlockWs& ws, int t) {
   MM_TRY(alloc(reinterpret_cast<void**>(&ws.Z), vec));
   MM_TRY(alloc(reinterpret_cast<void**>(&ws.W), vec));
   MM_TRY(alloc(reinterpret_cast<void**>(&ws.MR), vec));
-  MM_TRY(alloc(reinterpret_cast<void**>(&ws.small), sizeof(double) * 4 * kMaxT * kMaxT));
-  ws.nwg = std::max(gram_rb_grid(nu), rows_grid(nu));
+  MM_TRY(alloc(reinterpret_cast<void**>(&ws.small), sizeof(double) * kSmall));
   MM_TRY(alloc(reinterpret_cast<void**>(&ws.partial),
-               sizeof(double) * static_cast<size_t>(ws.nwg) * kMaxT * kMaxT));
-  MM_TRY(alloc(reinterpret_cast<void**>(&ws.cols), sizeof(int32_t) * kMaxT));
+               sizeof(double) * static_cast<size_t>(gram_grid(nu)) * 2 * kMat));
+  MM_TRY(alloc(reinterpret_cast<void**>(&ws.rr_partial),
+               sizeof(double) * static_cast<size_t>(rows_grid(nu)) * kMaxT));
+  MM_TRY(alloc(reinterpret_cast<void**>(&ws.cols), sizeof(int32_t) * (kMaxT + 1)));
+  if (Wk.h_block == nullptr) {
+    std::unique_lock<std::shared_mutex> lock(alloc_gate());
+    MM_HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&Wk.h_block), sizeof(double) * kBlockHost,
+                             hipHostMallocDefault));
+  }
   ws.cap = t;
   return MM_OK;
 }
@@ -352,64 +440,38 @@ mm_status ensure_ws(Plan* P, BlockWs& ws, int t) {
 void free_ws(BlockWs& ws) {
   for (void* p : {static_cast<void*>(ws.R), static_cast<void*>(ws.Z), static_cast<void*>(ws.W),
                   static_cast<void*>(ws.MR), static_cast<void*>(ws.small),
-                  static_cast<void*>(ws.partial), static_cast<void*>(ws.cols)})
+                  static_cast<void*>(ws.partial), static_cast<void*>(ws.rr_partial),
+                  static_cast<void*>(ws.cols)})
     dev_free(p);
   ws = BlockWs{};
 }
 
-// Gram U^T V (tu x tv, row-major) to the host.
-void launch_gram(const double* U, int tu, const double* V1, int tv1, const double* V2, int tv2,
-                 int64_t nu, double* partial, int g, hipStream_t s) {
-  const int nbu = (tu + kGB - 1) / kGB;
-  const int nb = nbu * ((tv1 + kGB - 1) / kGB) + nbu * ((tv2 + kGB - 1) / kGB);
-  hipLaunchKernelGGL(k_gram_rb, dim3(static_cast<unsigned>(g), static_cast<unsigned>(nb)),
-                     dim3(kThreads), 0, s, U, tu, nu, V1, tv1, V2, tv2, nu, nu, partial);
+// Gram partials of U^T V1 and U^T V2 (tv2 = 0: one product); returns their number.
+int launch_gram(const double* U, int tu, const double* V1, int tv1, const double* V2, int tv2,
+                int64_t nu, double* partial, hipStream_t s) {
+  const int g = gram_grid(nu);
+  const int nb = ((tu + kGB - 1) / kGB) * ((tv1 + tv2 + kGB - 1) / kGB);
+  hipLaunchKernelGGL(k_gram, dim3(static_cast<unsigned>(g), static_cast<unsigned>(nb)),
+                     dim3(kThreads), 0, s, U, tu, V1, tv1, V2, tv2, nu, partial);
+  return g;
 }
 
-mm_status gram(const double* U, int tu, const double* V, int tv, int64_t nu, BlockWs& ws,
-               std::vector<double>& out, hipStream_t s) {
-  const int g = gram_rb_grid(nu);
-  launch_gram(U, tu, V, tv, nullptr, 0, nu, ws.partial, g, s);
-  const int count = tu * tv;
-  hipLaunchKernelGGL(k_gram_reduce, dim3(reduce_grid(count)), dim3(kThreads), 0, s, ws.partial, g,
-                     count, ws.small);
-  MM_HIP_TRY(hipGetLastError());
-  out.resize(count);
-  MM_HIP_TRY(hipMemcpyAsync(out.data(), ws.small, sizeof(double) * count, hipMemcpyDeviceToHost, s));
-  MM_HIP_TRY(hipStreamSynchronize(s));
-  return MM_OK;
-}
-
-// U^T V1 and U^T V2 to the host, one launch, one reduction and one synchronization.
-mm_status gram_pair(const double* U, int tu, const double* V1, int tv1, const double* V2, int tv2,
-                    int64_t nu, BlockWs& ws, std::vector<double>& out1, std::vector<double>& out2,
-                    hipStream_t s) {
-  const int g = gram_rb_grid(nu);
-  const int c1 = tu * tv1, c2 = tu * tv2;
-  launch_gram(U, tu, V1, tv1, V2, tv2, nu, ws.partial, g, s);
-  hipLaunchKernelGGL(k_gram_reduce, dim3(reduce_grid(c1 + c2)), dim3(kThreads), 0, s, ws.partial,
-                     g, c1 + c2, ws.small);
-  MM_HIP_TRY(hipGetLastError());
-  std::vector<double> both(c1 + c2);
-  MM_HIP_TRY(hipMemcpyAsync(both.data(), ws.small, sizeof(double) * (c1 + c2),
-                            hipMemcpyDeviceToHost, s));
-  MM_HIP_TRY(hipStreamSynchronize(s));
-  out1.assign(both.begin(), both.begin() + c1);
-  out2.assign(both.begin() + c1, both.end());
-  return MM_OK;
+void launch_reduce(const double* partial, int nwg, int count, double* out, const double* partial2,
+                   int nwg2, int count2, double* out2, hipStream_t s) {
+  hipLaunchKernelGGL(k_gram_reduce, dim3(reduce_grid(count + count2)), dim3(kThreads), 0, s,
+                     partial, nwg, count, out, partial2, nwg2, count2, out2);
 }
 
 // Per-column ||B_j - Y_j||^2 (Y may be null) to the host.
 mm_status col_norms(const double* B, const double* Y, int t, int64_t nu, BlockWs& ws,
-                    std::vector<double>& out, hipStream_t s) {
+                    double* host, std::vector<double>& out, hipStream_t s) {
   const int g = rows_grid(nu);
-  MM_TM_DISPATCH(k_col_norms, t, g, s, B, t, Y, nu, ws.partial);
-  hipLaunchKernelGGL(k_gram_reduce, dim3(reduce_grid(t)), dim3(kThreads), 0, s, ws.partial, g, t,
-                     ws.small);
+  MM_TM_DISPATCH(k_col_norms, t, g, s, B, t, Y, nu, ws.rr_partial);
+  launch_reduce(ws.rr_partial, g, t, ws.small + kRr, nullptr, 0, 0, nullptr, s);
   MM_HIP_TRY(hipGetLastError());
-  out.resize(t);
-  MM_HIP_TRY(hipMemcpyAsync(out.data(), ws.small, sizeof(double) * t, hipMemcpyDeviceToHost, s));
+  MM_HIP_TRY(hipMemcpyAsync(host, ws.small + kRr, sizeof(double) * t, hipMemcpyDeviceToHost, s));
   MM_HIP_TRY(hipStreamSynchronize(s));
+  out.assign(host, host + t);
   return MM_OK;
 }
 
@@ -419,7 +481,8 @@ mm_status solve_group(Plan* P, Work& Wk, const float* d, int64_t ld_d, double* x
                       mm_solve_info* info, int block_used, BlockWs& ws, hipStream_t s) {
   const int t = static_cast<int>(cols.size());
   const int64_t nu = 3 * P->n_kept;
-  MM_TRY(ensure_ws(P, ws, t));
+  MM_TRY(ensure_ws(P, Wk, ws, t));
+  double* const host = Wk.h_block;
   auto ev = std::chrono::steady_clock::now();
 
   // R_j = b_j = P^T N^-1 d_j, X_j = 0
@@ -427,7 +490,7 @@ mm_status solve_group(Plan* P, Work& Wk, const float* d, int64_t ld_d, double* x
   hipLaunchKernelGGL(k_zero_cols, dim3(rows_grid(t * nu)), dim3(kThreads), 0, s, x, ws.cols, t, nu);
   for (int j = 0; j < t; ++j) MM_TRY(compute_rhs(P, Wk, d + cols[j] * ld_d, ws.R + j * nu, s));
   std::vector<double> bb;
-  MM_TRY(col_norms(ws.R, nullptr, t, nu, ws, bb, s));
+  MM_TRY(col_norms(ws.R, nullptr, t, nu, ws, host, bb, s));
   std::vector<double> bnorm(t);
   for (int j = 0; j < t; ++j) bnorm[j] = std::sqrt(bb[j]);
 
@@ -448,78 +511,111 @@ mm_status solve_group(Plan* P, Work& Wk, const float* d, int64_t ld_d, double* x
     }
   }
   int ta = static_cast<int>(act.size());
-  int tz = ta;
+  int32_t* const done = ws.cols + kMaxT;
+  // Slot tables (user columns, limits of ||R_j||^2, the done flag cleared): at the start and
+  // whenever columns have left.  They travel through their own part of the pinned area, which
+  // is read before the stream is next synchronized.
+  auto upload_slots = [&]() -> mm_status {
+    double* lim = host + kLimit;
+    int32_t* tab = reinterpret_cast<int32_t*>(host + kSmall);
+    for (int i = 0; i < ta; ++i) {
+      const double l = tol * bnorm[slot_of[i]];
+      lim[i] = l * l;
+      tab[i] = act[i];
+    }
+    tab[kMaxT] = 0;
+    MM_HIP_TRY(hipMemcpyAsync(ws.small + kLimit, lim, sizeof(double) * ta, hipMemcpyHostToDevice, s));
+    MM_HIP_TRY(hipMemcpyAsync(ws.cols, tab, sizeof(int32_t) * (kMaxT + 1), hipMemcpyHostToDevice, s));
+    return MM_OK;
+  };
+  // The last update's outcome, already on the host: norms, and the slots still in the block.
+  std::vector<int> keep;
+  auto settle = [&](int k) {
+    keep.clear();
+    for (int i = 0; i < ta; ++i) {
+      const int j = slot_of[i];
+      relres[j] = std::sqrt(std::max(host[kRr + i], 0.0)) / bnorm[j];
+      iters[j] = k;
+      if (host[kAct + i] != 0.0)
+        keep.push_back(i);
+      else
+        conv[j] = 1;
+    }
+  };
   std::vector<double> G, H, Gi, A;
   if (ta > 0) {
+    MM_TRY(upload_slots());
     MM_TRY(launch_precond_multi(P, ws.R, ws.Z, ta, s));  // Z = M R
   }
   int k = 0;
   while (ta > 0 && k < max_iter) {
-    MM_TRY(apply_A_multi(P, Wk, ws.Z, nu, ws.W, nu, tz, s));  // W = A Z
-    MM_TRY(gram_pair(ws.Z, tz, ws.W, tz, ws.R, ta, nu, ws, G, H, s));  // G = Z^T W, H1 = Z^T R
-    sym_pinv(G, tz, 1e-12, Gi);
-    matmul(Gi, H, tz, ta, A);                              // a1 = G^+ H1  (tz x ta)
-    MM_HIP_TRY(hipMemcpyAsync(ws.cols, act.data(), sizeof(int32_t) * ta, hipMemcpyHostToDevice, s));
-    MM_HIP_TRY(hipMemcpyAsync(ws.small + kMaxT * kMaxT, A.data(), sizeof(double) * A.size(),
-                              hipMemcpyHostToDevice, s));
-    const int g = rows_grid(nu);
-    MM_TM_DISPATCH(k_block_update, tz, g, s, ws.Z, ws.W, tz, ws.R, ta, nu, x, ws.cols,
-                   ws.small + kMaxT * kMaxT, ws.partial);
-    // ||R_j||^2, then MR = M R and H2 = W^T MR for every column still in the block, read back
-    // together behind one synchronization
-    constexpr int kRrOff = 2 * kMaxT * kMaxT, kH2Off = kRrOff + kMaxT;
-    hipLaunchKernelGGL(k_gram_reduce, dim3(reduce_grid(ta)), dim3(kThreads), 0, s, ws.partial, g,
-                       ta, ws.small + kRrOff);
-    MM_TRY(launch_precond_multi(P, ws.R, ws.MR, ta, s));
-    const int gg = gram_rb_grid(nu);
-    launch_gram(ws.W, tz, ws.MR, ta, nullptr, 0, nu, ws.partial, gg, s);
-    hipLaunchKernelGGL(k_gram_reduce, dim3(reduce_grid(tz * ta)), dim3(kThreads), 0, s,
-                       ws.partial, gg, tz * ta, ws.small + kH2Off);
+    // W = A Z; G = Z^T W, H1 = Z^T R.  Columns that left in the last update have Z = 0 (and rows
+    // and columns of zeros in G); with none left the product exits at once.
+    MM_TRY(apply_A_multi(P, Wk, ws.Z, nu, ws.W, nu, ta, s, done));
+    const int ng = launch_gram(ws.Z, ta, ws.W, ta, ws.R, ta, nu, ws.partial, s);
+    launch_reduce(ws.partial, ng, 2 * ta * ta, ws.small + kG, nullptr, 0, 0, nullptr, s);
     MM_HIP_TRY(hipGetLastError());
-    std::vector<double> back(kMaxT + static_cast<size_t>(tz) * ta);
-    MM_HIP_TRY(hipMemcpyAsync(back.data(), ws.small + kRrOff, sizeof(double) * back.size(),
+    MM_HIP_TRY(hipMemcpyAsync(host, ws.small, sizeof(double) * (kG + 2 * ta * ta),
                               hipMemcpyDeviceToHost, s));
     MM_HIP_TRY(hipStreamSynchronize(s));
-    ++k;
-    // stop test per column; compact R and MR to the remaining columns
-    std::vector<int32_t> nact;
-    std::vector<int> nslot, keep_idx;
-    for (int i = 0; i < ta; ++i) {
-      const int j = slot_of[i];
-      const double rel = std::sqrt(std::max(back[i], 0.0)) / bnorm[j];
-      relres[j] = rel;
-      iters[j] = k;
-      if (rel < tol) {
-        conv[j] = 1;
-      } else {
-        if (static_cast<int>(nact.size()) != i) {
-          MM_HIP_TRY(hipMemcpyAsync(ws.R + nact.size() * nu, ws.R + i * nu, sizeof(double) * nu,
-                                    hipMemcpyDeviceToDevice, s));
-          MM_HIP_TRY(hipMemcpyAsync(ws.MR + nact.size() * nu, ws.MR + i * nu,
-                                    sizeof(double) * nu, hipMemcpyDeviceToDevice, s));
-        }
-        nact.push_back(act[i]);
-        nslot.push_back(j);
-        keep_idx.push_back(i);
-      }
-    }
-    const int tn = static_cast<int>(nact.size());
-    if (tn == 0) {
+    const int told = ta;
+    if (k > 0) settle(k);
+    if (k > 0 && keep.empty()) {
       ta = 0;
       break;
     }
-    H.assign(static_cast<size_t>(tz) * tn, 0.0);  // H2 = W^T MR on the remaining columns
-    for (int i = 0; i < tz; ++i)
-      for (int jj = 0; jj < tn; ++jj) H[i * tn + jj] = back[kMaxT + i * ta + keep_idx[jj]];
-    matmul(Gi, H, tz, tn, A);                              // a2 = G^+ H2  (tz x tn)
-    MM_HIP_TRY(hipMemcpyAsync(ws.small + kMaxT * kMaxT, A.data(), sizeof(double) * A.size(),
+    if (k > 0 && static_cast<int>(keep.size()) < told) {
+      // compact Z, W and R to the remaining columns
+      const int tn = static_cast<int>(keep.size());
+      for (int i = 0; i < tn; ++i) {
+        if (keep[i] != i)
+          for (double* v : {ws.Z, ws.W, ws.R})
+            MM_HIP_TRY(hipMemcpyAsync(v + i * nu, v + keep[i] * nu, sizeof(double) * nu,
+                                      hipMemcpyDeviceToDevice, s));
+        act[i] = act[keep[i]];
+        slot_of[i] = slot_of[keep[i]];
+      }
+      ta = tn;
+      act.resize(ta);
+      slot_of.resize(ta);
+      MM_TRY(upload_slots());
+    } else if (k == 0) {
+      keep.resize(ta);
+      std::iota(keep.begin(), keep.end(), 0);
+    }
+    G.resize(static_cast<size_t>(ta) * ta);
+    H.resize(static_cast<size_t>(ta) * ta);
+    for (int i = 0; i < ta; ++i)
+      for (int j = 0; j < ta; ++j) {
+        G[i * ta + j] = host[kG + keep[i] * told + keep[j]];
+        H[i * ta + j] = host[kG + told * told + keep[i] * told + keep[j]];
+      }
+    sym_pinv(G, ta, 1e-12, Gi);
+    matmul(Gi, H, ta, ta, A);  // a1 = G^+ H1
+    std::copy(A.begin(), A.end(), host + kA1);
+    std::copy(Gi.begin(), Gi.end(), host + kA1 + ta * ta);
+    MM_HIP_TRY(hipMemcpyAsync(ws.small + kA1, host + kA1, sizeof(double) * 2 * ta * ta,
                               hipMemcpyHostToDevice, s));
-    MM_TM_DISPATCH(k_block_direction, tz, g, s, ws.Z, tz, ws.MR, tn, nu,
-                   ws.small + kMaxT * kMaxT);
+    const int g = rows_grid(nu);
+    MM_TM_DISPATCH(k_block_update, ta, g, s, ws.Z, ws.W, ws.R, ta, nu, x, ws.cols,
+                   ws.small + kA1, ws.rr_partial);
+    // MR = M R, H2 = W^T MR and ||R_j||^2; a2 = G^+ H2 and the stop tests; Z <- MR - Z a2.  The
+    // host reads the norms with the next iteration's Gram matrices.
+    MM_TRY(launch_precond_multi(P, ws.R, ws.MR, ta, s));
+    const int nh = launch_gram(ws.W, ta, ws.MR, ta, nullptr, 0, nu, ws.partial, s);
+    launch_reduce(ws.partial, nh, ta * ta, ws.small + kH2, ws.rr_partial, g, ta, ws.small + kRr, s);
+    hipLaunchKernelGGL(k_block_coef, dim3(1), dim3(kThreads), 0, s, ta, ws.small + kRr,
+                       ws.small + kLimit, ws.small + kA1 + ta * ta, ws.small + kH2,
+                       ws.small + kA2, ws.small + kAct, done);
+    MM_TM_DISPATCH(k_block_direction, ta, g, s, ws.Z, ta, ws.MR, nu, ws.small + kA2,
+                   ws.small + kAct);
     MM_HIP_TRY(hipGetLastError());
-    act.swap(nact);
-    slot_of.swap(nslot);
-    ta = tz = tn;
+    ++k;
+  }
+  if (ta > 0) {  // stopped by max_iter: the last update's outcome
+    MM_HIP_TRY(hipMemcpyAsync(host, ws.small, sizeof(double) * kG, hipMemcpyDeviceToHost, s));
+    MM_HIP_TRY(hipStreamSynchronize(s));
+    if (k > 0) settle(k);
   }
 
   // true residuals ||b - A x|| (W = A X, R = b)
@@ -529,7 +625,7 @@ mm_status solve_group(Plan* P, Work& Wk, const float* d, int64_t ld_d, double* x
     MM_TRY(compute_rhs(P, Wk, d + cols[j] * ld_d, ws.R + j * nu, s));
     MM_TRY(apply_A(P, Wk, x + static_cast<int64_t>(cols[j]) * nu, ws.W + j * nu, nullptr, s));
   }
-  MM_TRY(col_norms(ws.R, ws.W, t, nu, ws, tr, s));
+  MM_TRY(col_norms(ws.R, ws.W, t, nu, ws, host, tr, s));
   const double ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - ev).count();
   for (int j = 0; j < t; ++j) {
     mm_solve_info& in = info[cols[j]];
@@ -556,14 +652,19 @@ void sym_pinv(const std::vector<double>& G, int n, double rtol, std::vector<doub
               SymPinvInfo* info) {
   std::vector<double> a(G), v(static_cast<size_t>(n) * n, 0.0);
   for (int i = 0; i < n; ++i) v[i * n + i] = 1.0;
+  // The rotations annihilate the upper triangle.  G = Z^T A Z of a single-precision operator is
+  // symmetric to ~1e-8 only, and what asymmetry it has stays below the diagonal: the upper
+  // triangle alone says when the sweeps are done (one more follows, to full precision).
+  bool last = false;
   for (int sweep = 0; sweep < 100; ++sweep) {
     double off = 0.0, tot = 0.0;
     for (int i = 0; i < n; ++i)
       for (int j = 0; j < n; ++j) {
         tot += a[i * n + j] * a[i * n + j];
-        if (i != j) off += a[i * n + j] * a[i * n + j];
+        if (i < j) off += a[i * n + j] * a[i * n + j];
       }
-    if (off <= 1e-30 * tot || tot == 0.0) break;
+    if (last || tot == 0.0) break;
+    last = off <= 1e-30 * tot;
     for (int p = 0; p < n - 1; ++p)
       for (int q = p + 1; q < n; ++q) {
         const double apq = a[p * n + q];

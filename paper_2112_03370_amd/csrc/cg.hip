@@ -505,7 +505,7 @@ mm_status apply_A(Plan* P, Work& W, const double* x, double* y, const int32_t* d
 }
 
 mm_status apply_A_multi(Plan* P, Work& W, const double* x, int64_t ldx, double* y, int64_t ldy,
-                        int32_t ncol, hipStream_t s) {
+                        int32_t ncol, hipStream_t s, const int32_t* done) {
   if (ncol <= 0 || P->n_kept == 0) return MM_OK;
   if (P->lambda_max != 0 && P->algo == MM_TOEPLITZ_FFT && P->fused &&
       P->precision == MM_PRECISION_MIXED) {
@@ -514,9 +514,9 @@ mm_status apply_A_multi(Plan* P, Work& W, const double* x, int64_t ldx, double* 
     } else {
       for (int32_t j = 0; j < ncol; ++j) MM_TRY(launch_zero(y + j * ldy, 3 * P->n_kept, s));
     }
-    return launch_apply_fused(P, x, nullptr, y, nullptr, s, W.scratch, ncol, ldx, ldy);
+    return launch_apply_fused(P, x, nullptr, y, done, s, W.scratch, ncol, ldx, ldy);
   }
-  for (int32_t j = 0; j < ncol; ++j) MM_TRY(apply_A(P, W, x + j * ldx, y + j * ldy, nullptr, s));
+  for (int32_t j = 0; j < ncol; ++j) MM_TRY(apply_A(P, W, x + j * ldx, y + j * ldy, done, s));
   return MM_OK;
 }
 

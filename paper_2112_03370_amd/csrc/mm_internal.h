@@ -126,6 +126,8 @@ struct GraphSlot {
 };
 constexpr int kGraphSlots = 8;
 
+constexpr int kBlockHost = 6400;  // doubles in Work::h_block
+
 struct Work {
   float* t = nullptr;           // [n_samples] (only when the product is not fused)
   float* u = nullptr;
@@ -139,6 +141,7 @@ struct Work {
   int32_t nrb = 0;
   CgState* state = nullptr;
   CgState* h_state = nullptr;   // pinned host mirror
+  double* h_block = nullptr;    // pinned transfer area of stacked solves (on their first use)
   int64_t bytes = 0;
   // Iteration graphs kept across solves (workspaces from work_alloc; they are destroyed with
   // the workspace).  A workspace runs one solve at a time, always with the same plan.
@@ -320,9 +323,9 @@ mm_status compute_rhs(Plan* P, Work& W, const float* d, double* b, hipStream_t s
 // A x -> y (y overwritten), done-gated.
 mm_status apply_A(Plan* P, Work& W, const double* x, double* y, const int32_t* done,
                   hipStream_t s);
-// A X -> Y for ncol columns with leading dimensions ldx, ldy (Y overwritten).
+// A X -> Y for ncol columns with leading dimensions ldx, ldy (Y overwritten), done-gated.
 mm_status apply_A_multi(Plan* P, Work& W, const double* x, int64_t ldx, double* y, int64_t ldy,
-                        int32_t ncol, hipStream_t s);
+                        int32_t ncol, hipStream_t s, const int32_t* done = nullptr);
 // Stacked right-hand sides by the enlarged-CG recurrences (block.hip).
 mm_status block_solve(Plan* P, Work& W, const float* d, int32_t k, int64_t ld_d, double* x,
                       const mm_solve_opts* o, mm_solve_info* info, hipStream_t s);

@@ -760,9 +760,10 @@ void work_free(Work* W) {
   }
   void* ptrs[] = {W->t, W->u, W->scratch, W->r, W->z, W->p, W->q, W->b, W->partial, W->state};
   for (void* p : ptrs) dev_free(p);
-  if (W->h_state) {
+  if (W->h_state || W->h_block) {
     std::unique_lock<std::shared_mutex> lock(alloc_gate());
-    (void)hipHostFree(W->h_state);
+    if (W->h_state) (void)hipHostFree(W->h_state);
+    if (W->h_block) (void)hipHostFree(W->h_block);
   }
   *W = Work{};
 }

@@ -169,3 +169,25 @@ def test_block_rejects_restart(gpu_lib):
     x = plan.pcg_solve(_dev(prob.d[:2]), block=2)[0]
     with pytest.raises(RuntimeError):
         plan.pcg_solve(_dev(prob.d[:2]), x=x, use_x0=True, block=2)
+
+
+@pytest.mark.parametrize("t", [2, 7, 8, 9, 16, 17, 31, 32])
+def test_block_sizes_around_the_gram_tiles(gpu_lib, t):
+    """Block sizes around the 16-column tiles of the Gram products (two products share their
+    columns: t + t of them), independent columns that leave the block at different iterations
+    (one without noise), and an iteration limit.  Each column's iterate solves its system to
+    relative residual 1e-8: maps within 1e-6 of the oracle's."""
+    prob = synth.make_raster(cfg_id=60, n_dets=3, side=18, dwell=8, lam=200)
+    ref = O.plan_from_problem(prob)
+    plan = gpu_lib.Plan.from_problem(prob)
+    d = np.random.default_rng(t).standard_normal((t, prob.n_samples)).astype(np.float32)
+    d[t // 2] = 100.0
+    x, infos = plan.pcg_solve(_dev(d), tol=1e-8, block=t)
+    x = x.cpu().numpy()
+    for j in {0, 1, t // 2, t - 1}:
+        want = O.pcg(ref, O.rhs(ref, d[j]), tol=1e-8).x
+        assert infos[j]["converged"] == 1 and infos[j]["relres"] < 1e-8
+        assert _rel(x[j], want) <= 1e-6, (j, _rel(x[j], want))
+    _, short = plan.pcg_solve(_dev(d), tol=1e-8, block=t, max_iter=3, raise_on_error=False)
+    assert [i["iterations"] for i in short] == [3] * t
+    assert all(i["converged"] == 0 and 1e-8 < i["relres"] < 1.0 for i in short)
