@@ -17,9 +17,9 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libmm.so")
 OBJDIR = os.path.join(os.path.dirname(HERE), "_build")
-SOURCES = ["api.hip", "plan.hip", "pointing.hip", "toeplitz.hip", "toeplitz_long.hip",
-           "apply_fused.hip", "apply_reg.hip", "cg.hip", "block.hip", "server.hip",
-           "deflation.hip", "exact.hip", "templates.hip", "noalloc.hip"]
+SOURCES = ["api.hip", "plan.hip", "pointing.hip", "toeplitz.hip", "direct.hip",
+           "toeplitz_long.hip", "apply_fused.hip", "apply_reg.hip", "cg.hip", "block.hip",
+           "server.hip", "deflation.hip", "exact.hip", "templates.hip", "noalloc.hip"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -419,6 +419,8 @@ mm_status iteration(Plan* P, Work& W, double* x, bool two_level, hipStream_t s) 
     MM_TRY(exact_product(P, W.p, nullptr, W.q, s));
   } else if (P->algo == MM_TOEPLITZ_FFT && P->fused) {
     MM_TRY(launch_apply_fused(P, W.p, nullptr, W.q, done, s, W.scratch));
+  } else if (P->fused) {
+    MM_TRY(launch_apply_direct(P, W.p, nullptr, W.q, done, s));
   } else {
     MM_TRY(launch_unpoint(P, W.p, W.t, done, s));
     MM_TRY(launch_noise_weight(P, W.t, W.u, W.scratch, done, s));
@@ -474,8 +476,9 @@ mm_status compute_rhs(Plan* P, Work& W, const float* d, double* b, hipStream_t s
     return launch_diag_apply(P, nullptr, d, b, nullptr, s);
   }
   if (P->precision == MM_PRECISION_FP64) return exact_product(P, nullptr, d, b, s);
-  if (P->algo == MM_TOEPLITZ_FFT && P->fused) {
+  if (P->fused) {
     MM_TRY(launch_zero(b, 3 * P->n_kept, s));
+    if (P->algo != MM_TOEPLITZ_FFT) return launch_apply_direct(P, nullptr, d, b, nullptr, s);
     return launch_apply_fused(P, nullptr, d, b, nullptr, s, W.scratch);
   }
   MM_TRY(launch_mask_data(P, d, W.t, s));
@@ -494,8 +497,9 @@ mm_status apply_A(Plan* P, Work& W, const double* x, double* y, const int32_t* d
     return launch_diag_apply(P, x, nullptr, y, done, s);
   }
   if (P->precision == MM_PRECISION_FP64) return exact_product(P, x, nullptr, y, s);
-  if (P->algo == MM_TOEPLITZ_FFT && P->fused) {
+  if (P->fused) {
     MM_TRY(launch_zero(y, 3 * P->n_kept, s));
+    if (P->algo != MM_TOEPLITZ_FFT) return launch_apply_direct(P, x, nullptr, y, done, s);
     return launch_apply_fused(P, x, nullptr, y, done, s, W.scratch);
   }
   MM_TRY(launch_unpoint(P, x, W.t, done, s));
@@ -507,13 +511,14 @@ mm_status apply_A(Plan* P, Work& W, const double* x, double* y, const int32_t* d
 mm_status apply_A_multi(Plan* P, Work& W, const double* x, int64_t ldx, double* y, int64_t ldy,
                         int32_t ncol, hipStream_t s, const int32_t* done) {
   if (ncol <= 0 || P->n_kept == 0) return MM_OK;
-  if (P->lambda_max != 0 && P->algo == MM_TOEPLITZ_FFT && P->fused &&
-      P->precision == MM_PRECISION_MIXED) {
+  if (P->lambda_max != 0 && P->fused && P->precision == MM_PRECISION_MIXED) {
     if (ldy == 3 * P->n_kept) {
       MM_TRY(launch_zero(y, ncol * ldy, s));  // the columns are contiguous: one launch
     } else {
       for (int32_t j = 0; j < ncol; ++j) MM_TRY(launch_zero(y + j * ldy, 3 * P->n_kept, s));
     }
+    if (P->algo != MM_TOEPLITZ_FFT)
+      return launch_apply_direct(P, x, nullptr, y, done, s, ncol, ldx, ldy);
     return launch_apply_fused(P, x, nullptr, y, done, s, W.scratch, ncol, ldx, ldy);
   }
   for (int32_t j = 0; j < ncol; ++j) MM_TRY(apply_A(P, W, x + j * ldx, y + j * ldy, done, s));

@@ -170,7 +170,7 @@ struct Deflation {
 };
 
 struct Plan;
-// Time-domain work vectors are needed by unfused and direct products (plan.hip).
+// Time-domain work vectors are needed by unfused products (plan.hip).
 bool needs_time_buffers(const Plan* P);
 // Workgroups of the pixel-domain reductions for n_kept pixels (the partials hold 4 x that).
 int32_t reduction_blocks(int64_t n_kept);
@@ -221,12 +221,13 @@ struct Plan {
   float4* long_pq = nullptr;    // spectrum-step coefficient pairs in the long kernel's read order
   float2* tw0 = nullptr;        // fine twiddles exp(-2 pi i m / fft_n), m < 128
   float2* tw1 = nullptr;        // coarse twiddles exp(-2 pi i 128 m / fft_n)
-  Chunk* chunks = nullptr;      // FFT segments or direct tiles
+  Chunk* chunks = nullptr;      // FFT segments or direct tiles (then n_id_chunks identity tiles)
+  int32_t n_id_chunks = 0;      // direct plans: tiles of samples outside every block (band -1)
   Tile* tiles = nullptr;        // <= 4096-sample tiles with their diagonal weight c_0
   int32_t n_tiles = 0;
   Tile* id_tiles = nullptr;     // the tiles of samples outside every block (weight 1)
   int32_t n_id_tiles = 0;
-  bool fused = true;            // FFT path: gather + Toeplitz + scatter in one kernel
+  bool fused = true;            // gather + Toeplitz + scatter in one kernel
   bool reg_fft = false;         // fused 2^15 segments in the register-resident kernel
   int32_t n_cu = 0;             // compute units of the plan's device
   std::atomic<int32_t> tuned_block{0};  // block size chosen by a tuned stacked solve (0: none)
@@ -395,7 +396,16 @@ mm_status residual_norm2(Plan* P, Work& W, const double* x, double* rr, hipStrea
 // FFT sizing helpers (toeplitz.hip).
 int32_t choose_fft_size(int32_t lambda_max);
 bool fft_size_supported(int32_t n);
+// Direct products (direct.hip): tiles of at most direct_tile() outputs, lambda up to
+// max_direct_lambda(); the fused form covers the identity tiles too (layout as
+// launch_apply_fused).
 int32_t max_direct_lambda();
+int32_t direct_tile();
+mm_status launch_toeplitz_direct(Plan* P, const float* t, float* u, const int32_t* done,
+                                 hipStream_t s);
+mm_status launch_apply_direct(Plan* P, const double* x, const float* d, double* y,
+                              const int32_t* done, hipStream_t s, int32_t ncol = 1,
+                              int64_t ldx = 0, int64_t ldy = 0);
 // Long segments (toeplitz_long.hip): N = 2^16, 2^17 through a global tile per segment.
 bool long_fft_size(int32_t n);
 int32_t long_fine_size();

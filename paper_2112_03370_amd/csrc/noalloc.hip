@@ -68,7 +68,8 @@ mm_status mm_pcg_solve_noalloc(const mm_plan_t* plan, const float* d, int32_t k,
     return fail(MM_ERR_UNSUPPORTED,
                 "the allocation-free solve runs block-Jacobi PCG per column only (block 0/1, "
                 "precond 0, no refinement or FP64 check)");
-  if (needs_time_buffers(P) || P->precision != MM_PRECISION_MIXED || P->n_poly > 0 ||
+  if (needs_time_buffers(P) || (P->lambda_max > 0 && P->algo != MM_TOEPLITZ_FFT) ||
+      P->precision != MM_PRECISION_MIXED || P->n_poly > 0 ||
       (P->algo == MM_TOEPLITZ_FFT && long_fft_size(P->fft_n)))
     return fail(MM_ERR_UNSUPPORTED,
                 "the allocation-free solve needs a plan whose product keeps the time domain on "

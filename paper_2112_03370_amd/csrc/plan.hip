@@ -684,7 +684,7 @@ void dev_free(void* p) {
 }
 
 bool needs_time_buffers(const Plan* P) {
-  return P->lambda_max > 0 && !(P->algo == MM_TOEPLITZ_FFT && P->fused);
+  return P->lambda_max > 0 && !P->fused;
 }
 
 int32_t reduction_blocks(int64_t n_kept) {
@@ -1006,6 +1006,7 @@ mm_status build_plan_fixed(const mm_geometry* g, hipStream_t s, Plan** out) {
                      [&](int a, int b) { return key(a) < key(b); });
   }
   std::vector<Chunk> chunks;
+  int64_t n_id_chunks = 0;
   if (algo == MM_TOEPLITZ_FFT) {
     const int64_t L = fft_n - 2 * lambda_max;
     for (int i : seg_order) {
@@ -1018,15 +1019,22 @@ mm_status build_plan_fixed(const mm_geometry* g, hipStream_t s, Plan** out) {
   } else {
     for (int i : seg_order) {
       const int64_t s0 = g->blk_start[i], len = g->blk_len[i];
-      for (int64_t o = 0; o < len; o += 1024)
+      for (int64_t o = 0; o < len; o += direct_tile())
         chunks.push_back(Chunk{s0 + o, s0, static_cast<int32_t>(len),
-                               static_cast<int32_t>(std::min<int64_t>(1024, len - o)),
+                               static_cast<int32_t>(std::min<int64_t>(direct_tile(), len - o)),
                                g->blk_band[i], 0});
     }
+    n_id_chunks = static_cast<int64_t>(chunks.size());
+    for (const Tile& t : id_tiles)
+      for (int32_t o = 0; o < t.len; o += direct_tile())
+        chunks.push_back(Chunk{t.start + o, t.start + o, std::min(direct_tile(), t.len - o),
+                               std::min(direct_tile(), t.len - o), -1, 0});
+    n_id_chunks = static_cast<int64_t>(chunks.size()) - n_id_chunks;
   }
   if (chunks.size() > static_cast<size_t>(INT32_MAX) || idseg.size() / 2 > static_cast<size_t>(INT32_MAX))
     return fail(MM_ERR_UNSUPPORTED, "too many segments");
-  P->n_chunks = static_cast<int32_t>(chunks.size());
+  P->n_chunks = static_cast<int32_t>(static_cast<int64_t>(chunks.size()) - n_id_chunks);
+  P->n_id_chunks = static_cast<int32_t>(n_id_chunks);
   P->n_id_seg = static_cast<int32_t>(idseg.size() / 2);
   P->h_id_seg = idseg;
   MM_TRY(upload(P, &P->chunks, chunks, s));

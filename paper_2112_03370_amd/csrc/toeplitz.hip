@@ -11,9 +11,7 @@
 // coarse[m >> 7] * fine[m & 127]) computed in FP64 on the host.  The symbol is precomputed per
 // band at plan time with the 1/(2N) normalisation folded in.
 //
-// Direct path (short bands and tests): each workgroup owns 1024 outputs, stages the inputs
-// with a lambda halo and the band in LDS, and evaluates y_i = c_0 x_i + sum_k c_k (x_{i-k} +
-// x_{i+k}) in FP32.
+// Short bands take the direct product (direct.hip).
 #include "fft_lds.h"
 #include "mm_internal.h"
 
@@ -55,42 +53,6 @@ __global__ __launch_bounds__(FftCfg<LOG>::T) void k_toeplitz_fft(
   for (int n = lam + tid; n < lam + c.out_len; n += T) u[c.out0 + (n - lam)] = real_out(buf, n);
 }
 
-// ---------------------------------------------------------------------------------------------
-// Direct product
-// ---------------------------------------------------------------------------------------------
-
-constexpr int kDirectTile = 1024;
-constexpr int kDirectThreads = 256;
-constexpr int kDirectMaxLambda = 4096;
-
-__global__ __launch_bounds__(kDirectThreads) void k_toeplitz_direct(
-    const float* __restrict__ t, float* __restrict__ u, const Chunk* __restrict__ tiles,
-    const float* __restrict__ band_coef, const int64_t* __restrict__ band_off,
-    const int32_t* __restrict__ band_ncoef, const int32_t* __restrict__ done) {
-  extern __shared__ float sh[];
-  if (done != nullptr && *done) return;
-  const Chunk c = tiles[blockIdx.x];
-  const int lam = band_ncoef[c.band] - 1;
-  const float* coef = band_coef + band_off[c.band];
-  float* x = sh;                                  // kDirectTile + 2 lam
-  float* cc = sh + kDirectTile + 2 * kDirectMaxLambda;  // lam + 1
-  const int64_t b0 = c.blk_start, b1 = c.blk_start + c.blk_len;
-  const int64_t in0 = c.out0 - lam;
-  const int nin = c.out_len + 2 * lam;
-  for (int i = threadIdx.x; i < nin; i += kDirectThreads) {
-    const int64_t g = in0 + i;
-    x[i] = (g >= b0 && g < b1) ? t[g] : 0.0f;
-  }
-  for (int i = threadIdx.x; i <= lam; i += kDirectThreads) cc[i] = coef[i];
-  __syncthreads();
-  for (int o = threadIdx.x; o < c.out_len; o += kDirectThreads) {
-    const float* xc = x + o + lam;
-    float acc = cc[0] * xc[0];
-    for (int k = 1; k <= lam; ++k) acc = fmaf(cc[k], xc[-k] + xc[k], acc);
-    u[c.out0 + o] = acc;
-  }
-}
-
 // Identity rows (samples outside every block): u = t.
 __global__ __launch_bounds__(256) void k_copy_segments(const float* __restrict__ t,
                                                        float* __restrict__ u,
@@ -111,8 +73,6 @@ mm_status launch_fft(Plan* P, const float* t, float* u, const int32_t* done, hip
 }
 
 }  // namespace
-
-int32_t max_direct_lambda() { return kDirectMaxLambda; }
 
 bool fft_size_supported(int32_t n) {
   return n == (1 << 11) || n == (1 << 12) || n == (1 << 13) || n == (1 << 14) ||
@@ -149,10 +109,7 @@ mm_status launch_noise_weight(Plan* P, const float* t, float* u, float2* scratch
         default: return fail(MM_ERR_UNSUPPORTED, "FFT size not supported");
       }
     } else {
-      const size_t lds = sizeof(float) * (kDirectTile + 2 * kDirectMaxLambda + kDirectMaxLambda + 1);
-      hipLaunchKernelGGL(k_toeplitz_direct, dim3(P->n_chunks), dim3(kDirectThreads), lds, s, t, u,
-                         P->chunks, P->band_coef, P->band_off, P->band_ncoef, done);
-      MM_HIP_TRY(hipGetLastError());
+      MM_TRY(launch_toeplitz_direct(P, t, u, done, s));
     }
   }
   if (P->n_id_seg > 0) {

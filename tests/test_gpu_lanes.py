@@ -93,3 +93,29 @@ def test_lanes_fp64_product(gpu_lib, lam, dwell, flag_frac):
     scale = np.linalg.norm(O.apply_A(absref, np.abs(x)))
     got = plan.apply_A(_dev(x)).cpu().numpy()
     assert np.linalg.norm(got - O.apply_A(ref, x)) <= 1e-12 * scale
+
+
+@pytest.mark.parametrize("unfused", [False, True])
+@pytest.mark.parametrize("lam", [1, 6, 7, 8, 9, 15, 16, 17, 32, 33, 500, 4096])
+def test_lanes_direct_product(gpu_lib, lam, unfused):
+    """Direct products around the rounds of eight lags, with blocks shorter than the band, samples
+    outside every block, ragged tiles and flags; two columns in one launch."""
+    prob = synth.make_random_small(seed=40, n_samples=13007, n_pix=60, n_dets=4, lam_max=4,
+                                   flag_frac=0.1, gap_frac=0.3, dwell=5)
+    k = np.arange(lam + 1)
+    c = -0.3 * np.exp(-k / (1.0 + lam / 4.0)) / (1.0 + lam / 8.0)
+    c[0] = 1.0 + 2.0 * np.abs(c[1:]).sum()
+    bands = [c.astype(np.float32)] + [(c[: max(1, lam // 2)] * 1.5).astype(np.float32)] * (
+        len(prob.bands) - 1)
+    prob = dataclasses.replace(prob, bands=bands)
+    ref = O.plan_from_problem(prob)
+    plan = gpu_lib.Plan.from_problem(prob, toeplitz_algo=gpu_lib.TOEPLITZ_DIRECT,
+                                     flags=gpu_lib.FLAG_UNFUSED if unfused else 0)
+    x = np.random.default_rng(lam).standard_normal((2, ref.n_kept, 3))
+    y = plan.apply_A(_dev(x)).cpu().numpy()
+    for j in range(2):
+        assert _rel(y[j], O.apply_A(ref, x[j])) <= 3e-6
+    assert _rel(plan.rhs(_dev(prob.d[0])).cpu().numpy(), O.rhs(ref, prob.d[0])) <= 3e-6
+    t = np.random.default_rng(1).standard_normal(prob.n_samples).astype(np.float32)
+    u = plan.noise_weight(_dev(t)).cpu().numpy()
+    assert _rel(u, O.noise_weight(t.astype(np.float64), ref)) <= 2e-6
