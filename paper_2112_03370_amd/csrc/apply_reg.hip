@@ -284,13 +284,24 @@ __device__ __forceinline__ void gather_half(float2 (&v)[32], float* lds, int tid
   __syncthreads();
 }
 
-template <bool kFromData>
+// What a segment's transform is fed with and drained into: the pointing products of a map or of
+// data, or FP32 time-domain vectors in HBM (the stand-alone N^-1 t product).
+enum RegIo { kIoApply = 0, kIoRhs = 1, kIoPlain = 2 };
+
+// The plain form has neither gather nor scatter: slot j of thread t is the sample pair
+// 2 (t + 512 j), so a wavefront's loads and stores are runs of 512 bytes straight between registers
+// and memory, with no staging.  64 detectors x 2^20 samples, lambda = 8192: 540 us with the
+// LDS-resident transform (one 1,024-thread workgroup per CU), 244 us here, bound by the
+// transform's VALU issue.  (One kernel for all three, not a shared function: the rounding of the
+// fused products then stays what it is.)
+template <int IO>
 __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(4))) void k_apply_reg(
     const int32_t* __restrict__ lpix, const float* __restrict__ wq, const float* __restrict__ wu,
     const double* __restrict__ x0, const float* __restrict__ d0, double* __restrict__ y0,
-    int ncol, int64_t ldx, int64_t ldy, const Chunk* __restrict__ chunks,
+    float* __restrict__ u0, int ncol, int64_t ldx, int64_t ldy, const Chunk* __restrict__ chunks,
     const float2* __restrict__ tab, const float2* __restrict__ tw0g,
     const float2* __restrict__ tw1g, int lam, const int32_t* __restrict__ done) {
+  constexpr bool kFromData = IO == kIoRhs;
   __shared__ __align__(16) float lds[kLdsF + 64];
   __shared__ float2 tw0[128];
   __shared__ float2 tw1[kN / 128];
@@ -310,7 +321,7 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(4))) void k_
   const int wg = xcd_ordered(blockIdx.x, gridDim.x);
   const int col = wg % ncol;
   const Chunk c = chunks[wg / ncol];
-  const double* __restrict__ x = kFromData ? x0 : x0 + col * ldx;
+  const double* __restrict__ x = IO == kIoApply ? x0 + col * ldx : x0;
   const float* __restrict__ d = kFromData ? d0 + col * ldx : d0;
   double* __restrict__ y = y0 + col * ldy;
   const SegmentStreams win = segment_streams(lpix, wq, wu, d, c.out0 - lam);
@@ -325,21 +336,37 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(4))) void k_
 
   float2 v[32];
 
-  // ---- gather the window in two halves of 16,384 samples through LDS ----------------------
-  // The gather runs at raised wave priority: its waves issue their loads and finish their FP64
-  // sums ahead of the other workgroup's transform, which has VALU work to fill the wait
-  // (measured: -4 % per solve on the ground workload; the same for the scatter gave nothing).
-  __builtin_amdgcn_s_setprio(3);
-  // The right half of a segment's window is the left half of the next segment's (lambda = 2^13;
-  // nearly so otherwise), and neighbouring segments run at the same time on one XCD: even
-  // segments gather their right half first and odd ones their left half first, so that both
-  // readers of a shared half fetch it together and the second finds it in L2.
-  if (((wg / ncol) & 1) == 0) {
-    gather_half<1, kFromData>(v, lds, tid, win, x, lo, hi);
-    gather_half<0, kFromData>(v, lds, tid, win, x, lo, hi);
+  if constexpr (IO == kIoPlain) {
+    if (lo == 0 && hi == kN) {
+#pragma unroll
+      for (int j = 0; j < 32; ++j)
+        v[j] = load2u(win.d + static_cast<uint32_t>(2 * (tid + kT * j)));
+    } else {
+#pragma unroll
+      for (int j = 0; j < 32; ++j) {
+        const int i = 2 * (tid + kT * j);
+        v[j] = make_float2(i >= lo && i < hi ? win.d[i] : 0.0f,
+                           i + 1 >= lo && i + 1 < hi ? win.d[i + 1] : 0.0f);
+      }
+    }
+    __syncthreads();  // the twiddles are in LDS
   } else {
-    gather_half<0, kFromData>(v, lds, tid, win, x, lo, hi);
-    gather_half<1, kFromData>(v, lds, tid, win, x, lo, hi);
+    // ---- gather the window in two halves of 16,384 samples through LDS ----------------------
+    // The gather runs at raised wave priority: its waves issue their loads and finish their FP64
+    // sums ahead of the other workgroup's transform, which has VALU work to fill the wait
+    // (measured: -4 % per solve on the ground workload; the same for the scatter gave nothing).
+    __builtin_amdgcn_s_setprio(3);
+    // The right half of a segment's window is the left half of the next segment's (lambda = 2^13;
+    // nearly so otherwise), and neighbouring segments run at the same time on one XCD: even
+    // segments gather their right half first and odd ones their left half first, so that both
+    // readers of a shared half fetch it together and the second finds it in L2.
+    if (((wg / ncol) & 1) == 0) {
+      gather_half<1, kFromData>(v, lds, tid, win, x, lo, hi);
+      gather_half<0, kFromData>(v, lds, tid, win, x, lo, hi);
+    } else {
+      gather_half<0, kFromData>(v, lds, tid, win, x, lo, hi);
+      gather_half<1, kFromData>(v, lds, tid, win, x, lo, hi);
+    }
   }
 
   // ---- forward transform --------------------------------------------------------------------
@@ -447,6 +474,23 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(4))) void k_
   twiddle_a(v, tid, tw0, tw1);
   dft32_middle(v);
 
+  if constexpr (IO == kIoPlain) {
+    float* __restrict__ out = u0 + c.out0;
+    if (lam == kHalf / 2 && c.out_len == kHalf) {  // every middle point is an output pair
+#pragma unroll
+      for (int j = 8; j < 24; ++j)
+        store2u(out + static_cast<uint32_t>(2 * (tid + kT * (j - 8))), v[j].x, -v[j].y);
+    } else {
+#pragma unroll
+      for (int j = 8; j < 24; ++j) {
+        const int i = 2 * (tid + kT * j) - lam;
+        if (static_cast<unsigned>(i) < static_cast<unsigned>(c.out_len)) out[i] = v[j].x;
+        if (static_cast<unsigned>(i + 1) < static_cast<unsigned>(c.out_len)) out[i + 1] = -v[j].y;
+      }
+    }
+    return;
+  }
+
   // ---- outputs to LDS: sample 2m is Re, 2m+1 is -Im of point m = t + 512 j ------------------
   const int out_len = c.out_len;
   if (lam == kHalf / 2 && out_len == kHalf) {  // every middle point is an output pair
@@ -529,21 +573,33 @@ bool apply_reg_supported(const Plan* P) {
   return P->fft_n == kN && P->fft_n - 2 * static_cast<int64_t>(P->lambda_max) <= kHalf;
 }
 
+mm_status launch_toeplitz_reg(Plan* P, const float* t, float* u, const int32_t* done,
+                              hipStream_t s) {
+  if (!apply_reg_supported(P) || P->spec_reg == nullptr)
+    return fail(MM_ERR_UNSUPPORTED, "register FFT kernel: segment shape");
+  hipLaunchKernelGGL((k_apply_reg<kIoPlain>), dim3(static_cast<unsigned>(P->n_chunks)), dim3(kT), 0,
+                     s, P->lpix, P->wq, P->wu, static_cast<const double*>(nullptr), t,
+                     static_cast<double*>(nullptr), u, 1, int64_t{0}, int64_t{0}, P->chunks,
+                     P->spec_reg, P->tw0, P->tw1, P->lambda_max, done);
+  MM_HIP_TRY(hipGetLastError());
+  return MM_OK;
+}
+
 mm_status launch_apply_reg(Plan* P, const double* x, const float* d, int64_t ldx, double* y,
                            int64_t ldy, int32_t ncol, const int32_t* done, hipStream_t s) {
   if (!apply_reg_supported(P) || P->spec_reg == nullptr)
     return fail(MM_ERR_UNSUPPORTED, "register FFT kernel: segment shape");
   const int64_t grid = static_cast<int64_t>(P->n_chunks) * ncol;
   if (grid > INT32_MAX) return fail(MM_ERR_UNSUPPORTED, "too many segment x column workgroups");
-  if (d != nullptr) {
-    hipLaunchKernelGGL((k_apply_reg<true>), dim3(static_cast<unsigned>(grid)), dim3(kT), 0, s,
-                       P->lpix, P->wq, P->wu, x, d, y, ncol, ldx, ldy, P->chunks, P->spec_reg,
+  const dim3 g(static_cast<unsigned>(grid));
+  if (d != nullptr)
+    hipLaunchKernelGGL((k_apply_reg<kIoRhs>), g, dim3(kT), 0, s, P->lpix, P->wq, P->wu, x, d, y,
+                       static_cast<float*>(nullptr), ncol, ldx, ldy, P->chunks, P->spec_reg,
                        P->tw0, P->tw1, P->lambda_max, done);
-  } else {
-    hipLaunchKernelGGL((k_apply_reg<false>), dim3(static_cast<unsigned>(grid)), dim3(kT), 0, s,
-                       P->lpix, P->wq, P->wu, x, d, y, ncol, ldx, ldy, P->chunks, P->spec_reg,
+  else
+    hipLaunchKernelGGL((k_apply_reg<kIoApply>), g, dim3(kT), 0, s, P->lpix, P->wq, P->wu, x, d, y,
+                       static_cast<float*>(nullptr), ncol, ldx, ldy, P->chunks, P->spec_reg,
                        P->tw0, P->tw1, P->lambda_max, done);
-  }
   MM_HIP_TRY(hipGetLastError());
   return MM_OK;
 }

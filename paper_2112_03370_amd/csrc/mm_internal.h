@@ -314,6 +314,8 @@ mm_status launch_apply_fused(Plan* P, const double* x, const float* d, double* y
 // Register-resident variant for 2^15-sample segments with at most 2^14 outputs (apply_reg.hip).
 bool apply_reg_supported(const Plan* P);
 mm_status build_reg_table(Plan* P, hipStream_t s);  // after the band spectra
+mm_status launch_toeplitz_reg(Plan* P, const float* t, float* u, const int32_t* done,
+                              hipStream_t s);
 mm_status launch_apply_reg(Plan* P, const double* x, const float* d, int64_t ldx, double* y,
                            int64_t ldy, int32_t ncol, const int32_t* done, hipStream_t s);
 mm_status launch_zero(double* y, int64_t n, hipStream_t s);

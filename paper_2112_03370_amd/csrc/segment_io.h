@@ -45,6 +45,14 @@ __device__ __forceinline__ void load4u(const float* p, float* v) {
   v[2] = t.z;
   v[3] = t.w;
 }
+typedef float float2_u __attribute__((ext_vector_type(2), aligned(4)));
+__device__ __forceinline__ float2 load2u(const float* p) {
+  const float2_u t = *reinterpret_cast<const float2_u*>(p);
+  return make_float2(t.x, t.y);
+}
+__device__ __forceinline__ void store2u(float* p, float a, float b) {
+  *reinterpret_cast<float2_u*>(p) = float2_u{a, b};
+}
 __device__ __forceinline__ void store4u(float* p, float a, float b, float c, float d) {
   *reinterpret_cast<float4_u*>(p) = float4_u{a, b, c, d};
 }

@@ -14,6 +14,7 @@
 // Short bands take the direct product (direct.hip).
 #include "fft_lds.h"
 #include "mm_internal.h"
+#include "segment_io.h"
 
 namespace mm {
 
@@ -37,20 +38,29 @@ __global__ __launch_bounds__(FftCfg<LOG>::T) void k_toeplitz_fft(
   for (int i = tid; i < N / 128; i += T) tw1[i] = tw1g[i];
 
   const Chunk c = chunks[xcd_ordered(blockIdx.x, gridDim.x)];
-  const int64_t in0 = c.out0 - lam;
-  const int64_t b0 = c.blk_start, b1 = c.blk_start + c.blk_len;
-  float* fbuf = reinterpret_cast<float*>(buf);
-  for (int n = tid; n < N; n += T) {
-    const int64_t g = in0 + n;
-    const float val = (g >= b0 && g < b1) ? t[g] : 0.0f;
-    fbuf[2 * pad(n >> 1) + (n & 1)] = val;
+  const float* __restrict__ in = t + (c.out0 - lam);
+  int lo, hi;
+  window_range(c, lam, N, lo, hi);
+  for (int p = tid; p < NC; p += T) {  // sample pairs: complex points
+    const int i = 2 * p;
+    if (i >= lo && i + 2 <= hi)
+      buf[pad(p)] = load2u(in + static_cast<uint32_t>(i));
+    else
+      buf[pad(p)] = make_float2(i >= lo && i < hi ? in[i] : 0.0f,
+                                i + 1 >= lo && i + 1 < hi ? in[i + 1] : 0.0f);
   }
   __syncthreads();
   fft_forward<LOG, T>(buf, tw0, tw1);
   symbol_multiply<LOG, T>(buf, spec + static_cast<int64_t>(c.band) * (NC + 1), tw0, tw1);
   fft_forward<LOG, T>(buf, tw0, tw1);
   // outputs are y[lam .. lam + out_len)
-  for (int n = lam + tid; n < lam + c.out_len; n += T) u[c.out0 + (n - lam)] = real_out(buf, n);
+  float* __restrict__ out = u + c.out0;
+  for (int o = 2 * tid; o < c.out_len; o += 2 * T) {
+    if (o + 1 < c.out_len)
+      store2u(out + static_cast<uint32_t>(o), real_out(buf, lam + o), real_out(buf, lam + o + 1));
+    else
+      out[o] = real_out(buf, lam + o);
+  }
 }
 
 // Identity rows (samples outside every block): u = t.
@@ -99,6 +109,8 @@ mm_status launch_noise_weight(Plan* P, const float* t, float* u, float2* scratch
   if (P->n_chunks > 0) {
     if (P->algo == MM_TOEPLITZ_FFT && long_fft_size(P->fft_n)) {
       MM_TRY(launch_toeplitz_long(P, t, u, scratch, done, s));
+    } else if (P->algo == MM_TOEPLITZ_FFT && P->reg_fft) {
+      MM_TRY(launch_toeplitz_reg(P, t, u, done, s));
     } else if (P->algo == MM_TOEPLITZ_FFT) {
       switch (P->fft_n) {
         case 1 << 11: MM_TRY(launch_fft<10>(P, t, u, done, s)); break;

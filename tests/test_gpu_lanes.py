@@ -119,3 +119,21 @@ def test_lanes_direct_product(gpu_lib, lam, unfused):
     t = np.random.default_rng(1).standard_normal(prob.n_samples).astype(np.float32)
     u = plan.noise_weight(_dev(t)).cpu().numpy()
     assert _rel(u, O.noise_weight(t.astype(np.float64), ref)) <= 2e-6
+
+
+@pytest.mark.parametrize("lam", [8192, 8193, 12000, 15000])
+def test_lanes_register_noise_weight(gpu_lib, lam):
+    """u = N^-1 t by the register transform: whole and partial segments (a block shorter than the
+    band, odd block lengths, odd bands), samples outside every block, streams at odd addresses.
+    FP32 transform of 2^15 samples: relative L2 2e-6."""
+    prob, ref = _problem(3, lam, 0.02, n_dets=2, per_det=60013, interval=40011)
+    plan = gpu_lib.Plan.from_problem(prob, toeplitz_algo=gpu_lib.TOEPLITZ_FFT, fft_size=32768)
+    import torch
+    n = prob.n_samples
+    t = np.random.default_rng(lam).standard_normal(n + 1).astype(np.float32)
+    for shift in (0, 1):
+        out = torch.full((n + 4,), 7.0, device="cuda")
+        u = plan.noise_weight(_dev(t)[shift:shift + n], u=out[1 + shift:1 + shift + n]).cpu().numpy()
+        assert _rel(u, O.noise_weight(t[shift:shift + n].astype(np.float64), ref)) <= 2e-6
+        rest = torch.cat([out[:1 + shift], out[1 + shift + n:]]).cpu().numpy()
+        assert np.all(rest == 7.0)
