@@ -137,3 +137,13 @@ def test_lanes_register_noise_weight(gpu_lib, lam):
         assert _rel(u, O.noise_weight(t[shift:shift + n].astype(np.float64), ref)) <= 2e-6
         rest = torch.cat([out[:1 + shift], out[1 + shift + n:]]).cpu().numpy()
         assert np.all(rest == 7.0)
+
+
+@pytest.mark.parametrize("dwell,flag_frac", [(1, 0.02), (3, 0.6), (8, 0.0)])
+def test_lanes_diagonal_product(gpu_lib, dwell, flag_frac):
+    """Diagonal weights: FP64 throughout, 1e-12 relative."""
+    prob, ref = _problem(dwell, 0, flag_frac)
+    plan = gpu_lib.Plan.from_problem(prob)
+    x = np.random.default_rng(dwell).standard_normal((ref.n_kept, 3))
+    assert _rel(plan.apply_A(_dev(x)).cpu().numpy(), O.apply_A(ref, x)) <= 1e-12
+    assert _rel(plan.rhs(_dev(prob.d[0])).cpu().numpy(), O.rhs(ref, prob.d[0])) <= 1e-12
