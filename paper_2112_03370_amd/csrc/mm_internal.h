@@ -201,6 +201,7 @@ struct Plan {
   int32_t precision = MM_PRECISION_MIXED;
   int32_t n_poly = 0;           // template map-making: Legendre orders per baseline
   int64_t n_baselines = 0;
+  int32_t base_max = 0;  // samples of the longest baseline
 
   // pointing (device)
   int32_t* lpix = nullptr;  // local pixel or -1

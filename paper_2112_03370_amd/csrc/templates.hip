@@ -16,12 +16,25 @@
 //   2. c = K_b^+ a
 //   3. u_s = w (t_s - sum_k T_sk c_k)  (template projection subtracted); y += P^T u through the
 //      wavefront run merge
-// Samples of the first kCached steps of a baseline stay in registers between 1 and 3, so
-// baselines of up to kCached x 2048 samples read their pointing once; longer ones re-gather the
-// rest.  Samples outside every baseline get u = w t through the diagonal product.
+// A lane holds 8 consecutive samples and a wavefront steps through the baseline kHeld steps at a
+// time: the pointing of the first kHeld steps is loaded in one go and stays in registers between 1
+// and 3, t waits in LDS, so baselines of up to 1,024 (64 threads), 4,096 (256) or 8,192 (512)
+// samples are read once; longer ones re-gather the rest.  Samples outside every baseline get
+// u = w t through the diagonal product.
+//
+// What bounds it: the chain table entry -> pointing -> pixels -> sums -> coefficients -> pointing
+// sums, whose waits 16 wavefronts per CU have to cover, then the FP64 instructions.  128 detectors
+// x 2^20 samples, baselines of 8,192, 3 templates: 896 us with 4 samples per lane, all of them in
+// registers and the scaled Legendre recurrence twice per sample; 517 us here (3.1 TB/s of pointing).
+// Re-reading the pointing in 3 instead of holding it: 762 us (the reads come late, not from HBM).
+// t in registers instead of LDS: 889 us (spills).  One workgroup size for all baselines
+// left the short ones with idle wavefronts: 64 x 2^19 samples, baselines of 500 (3 templates)
+// 1,147 us with 512 threads, 167 us with 64; of 600 (1 template) 834 and 159 us; of 3,000
+// 323 us and, with 256, 182 us.
 #include <algorithm>
 #include <cmath>
 
+#include "fft_lds.h"
 #include "mm_internal.h"
 #include "segment_io.h"
 #include "wave_runs.h"
@@ -30,9 +43,10 @@ namespace mm {
 
 namespace {
 
-constexpr int kTT = 512;          // threads per workgroup
-constexpr int kStep = 4 * kTT;    // samples per step (4 consecutive per lane)
-constexpr int kCached = 4;        // steps kept in registers
+constexpr int kTT = 512;     // threads per workgroup of the kernel blocks' build
+constexpr int kLane = 8;     // consecutive samples per lane and step
+constexpr int kHeld = 2;     // steps whose pointing stays in registers
+constexpr int kListed = 64;  // runs listed per wavefront
 
 // Scaled Legendre values T_k = scale_k P_k(x), k < NP, by the three-term recurrence
 // k P_k = (2k - 1) x P_(k-1) - (k - 1) P_(k-2), with 1/k as a constant.
@@ -57,174 +71,121 @@ __device__ __forceinline__ void legendre(double x, const double* scale, double (
   }
 }
 
-// Samples j0 .. j0 + 3 of a baseline: pixel, weights and t = (P x)_s (or the data sample) in
-// FP64; key -1 for gap samples and samples past the end.  A lane whose 4 samples lie inside the
-// baseline loads its pointing with 16-byte loads, and since scan runs keep
-// a pixel for several samples, it loads the pixel values of its first and last samples once
-// each and a third pixel only when one occurs.  The sums are those of the one-sample form.
-template <bool kData>
-__device__ __forceinline__ void load4(const int32_t* __restrict__ lpix,
-                                      const float* __restrict__ wq,
-                                      const float* __restrict__ wu,
-                                      const double* __restrict__ x,
-                                      const float* __restrict__ d, int64_t start, int len,
-                                      int j0, int (&key)[4], double (&t)[4], float (&q)[4],
-                                      float (&u)[4]) {
-  const int64_t g0 = start + j0;
-  if (j0 + 4 <= len) {
-    load4u(lpix + g0, key);
-    load4u(wq + g0, q);
-    load4u(wu + g0, u);
-    if constexpr (kData) {
-      float dd[4];
-      load4u(d + g0, dd);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) t[i] = key[i] < 0 ? 0.0 : static_cast<double>(dd[i]);
-    } else {
-      const int ka = key[0], kb = key[3];
-      double a0 = 0.0, a1 = 0.0, a2 = 0.0, b0 = 0.0, b1 = 0.0, b2 = 0.0;
-      if (ka >= 0) {
-        const double* m = x + 3 * static_cast<int64_t>(ka);
-        a0 = m[0];
-        a1 = m[1];
-        a2 = m[2];
-      }
-      if (kb >= 0 && kb != ka) {
-        const double* m = x + 3 * static_cast<int64_t>(kb);
-        b0 = m[0];
-        b1 = m[1];
-        b2 = m[2];
-      }
-      bool other = false;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int k = key[i];
-        other |= k >= 0 && k != ka && k != kb;
-        const double qd = static_cast<double>(q[i]), ud = static_cast<double>(u[i]);
-        const double ta = a0 + qd * a1 + ud * a2;
-        const double tb = b0 + qd * b1 + ud * b2;
-        t[i] = k < 0 ? 0.0 : (k == ka ? ta : tb);
-      }
-      if (other) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int k = key[i];
-          if (k >= 0 && k != ka && k != kb) {
-            const double* m = x + 3 * static_cast<int64_t>(k);
-            t[i] = m[0] + static_cast<double>(q[i]) * m[1] + static_cast<double>(u[i]) * m[2];
-          }
-        }
-      }
-    }
-    return;
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int j = j0 + i;
-    key[i] = -1;
-    t[i] = 0.0;
-    q[i] = u[i] = 0.0f;
-    if (j < len) {
-      const int64_t g = start + j;
-      const int p = lpix[g];
-      if (p >= 0) {
-        key[i] = p;
-        q[i] = wq[g];
-        u[i] = wu[g];
-        if (kData) {
-          t[i] = static_cast<double>(d[g]);
-        } else {
-          const double* m = x + 3 * static_cast<int64_t>(p);
-          t[i] = m[0] + static_cast<double>(q[i]) * m[1] + static_cast<double>(u[i]) * m[2];
-        }
-      }
-    }
-  }
-}
-
-// Projections of 4 samples onto the templates: a_k += T_k(x_j) w t_j.
+// Legendre values P_k(x), k < NP, without the scales, which the projections and the coefficients
+// take once per baseline: P_k = ((2k - 1) / k) x P_(k-1) - ((k - 1) / k) P_(k-2).
 template <int NP>
-__device__ __forceinline__ void project4(const int (&key)[4], const double (&t)[4], int j0,
-                                         double invL, double w, const double* scale,
-                                         double (&a)[NP]) {
+__device__ __forceinline__ void legendre_plain(double x, double (&T)[NP]) {
+  T[0] = 1.0;
+  if constexpr (NP > 1) T[1] = x;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if (key[i] < 0) continue;
-    double T[NP];
-    legendre<NP>(fma(2.0, static_cast<double>(j0 + i), 1.0) * invL - 1.0, scale, T);
-    const double v = w * t[i];
+  for (int k = 2; k < NP; ++k)
+    T[k] = fma((2.0 * k - 1.0) / k * x, T[k - 1], -((k - 1.0) / k) * T[k - 2]);
+}
+
+// t of a lane between the two halves of the kernel, in the lane's own LDS slots.
+__device__ __forceinline__ void park(double2* slot, const double (&t)[kLane], int n) {
 #pragma unroll
-    for (int k = 0; k < NP; ++k) a[k] = fma(T[k], v, a[k]);
+  for (int j = 0; j < kLane; j += 2) slot[j / 2 * n] = make_double2(t[j], t[j + 1]);
+}
+__device__ __forceinline__ void fetch(const double2* slot, double (&t)[kLane], int n) {
+#pragma unroll
+  for (int j = 0; j < kLane; j += 2) {
+    const double2 v = slot[j / 2 * n];
+    t[j] = v.x;
+    t[j + 1] = v.y;
   }
 }
 
-// u_j = w (t_j - sum_k T_k c_k) for 4 samples, then the pointing sums.
+// a_k += sum_j P_k(x_j) t_j, x_j = x0 + j dx (t is zero at flagged samples).
 template <int NP>
-__device__ __forceinline__ void subtract_point4(const int (&key)[4], const double (&t)[4],
-                                                const float (&q)[4], const float (&u)[4],
-                                                int j0, double invL, double w,
-                                                const double* scale, const double (&c)[NP],
-                                                double* y) {
-  double v[4][3];
+__device__ __forceinline__ void project(const double (&t)[kLane], double x0, double dx,
+                                        double (&a)[NP]) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    double r = 0.0;
-    if (key[i] >= 0) {
-      double T[NP];
-      legendre<NP>(fma(2.0, static_cast<double>(j0 + i), 1.0) * invL - 1.0, scale, T);
-      double fit = 0.0;
+  for (int j = 0; j < kLane; ++j) {
+    double P[NP];
+    legendre_plain<NP>(fma(dx, static_cast<double>(j), x0), P);
+    a[0] += t[j];
 #pragma unroll
-      for (int k = 0; k < NP; ++k) fit = fma(T[k], c[k], fit);
-      r = w * (t[i] - fit);
-    }
-    v[i][0] = r;
-    v[i][1] = static_cast<double>(q[i]) * r;
-    v[i][2] = static_cast<double>(u[i]) * r;
+    for (int k = 1; k < NP; ++k) a[k] = fma(P[k], t[j], a[k]);
   }
-  wave_merge_runs<3>(key, v, AtomicFlush{y});
 }
 
-template <bool kData, int NP>
-__global__ __launch_bounds__(kTT) void k_template_apply(
+// t_j = w t_j - sum_k P_k(x_j) c_k.
+template <int NP>
+__device__ __forceinline__ void subtract(double (&t)[kLane], double x0, double dx, double w,
+                                         const double (&c)[NP]) {
+#pragma unroll
+  for (int j = 0; j < kLane; ++j) {
+    double P[NP];
+    legendre_plain<NP>(fma(dx, static_cast<double>(j), x0), P);
+    double r = fma(w, t[j], -c[0]);
+#pragma unroll
+    for (int k = 1; k < NP; ++k) r = fma(-P[k], c[k], r);
+    t[j] = r;
+  }
+}
+
+template <bool kData, int NP, int T>
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_template_apply(
     const int32_t* __restrict__ lpix, const float* __restrict__ wq, const float* __restrict__ wu,
     const double* __restrict__ x, const float* __restrict__ d, const TBase* __restrict__ bases,
     const double* __restrict__ kinv, double* __restrict__ y, const int32_t* __restrict__ done) {
-  constexpr int n_poly = NP;
   if (done != nullptr && *done) return;
-  __shared__ double red[kMaxTemplates][kTT / 64];
-  __shared__ double scale[kMaxTemplates];
-  __shared__ double coef[kMaxTemplates];
-  const TBase B = bases[blockIdx.x];
+  constexpr int kStep = T * kLane;  // samples per step
+  __shared__ double red[NP][T / 64];
+  __shared__ double coef[NP];
+  __shared__ double lists[T / 64][run_list_bytes<3, kListed>() / sizeof(double)];
+  __shared__ double kmat[NP * NP];
+  __shared__ double2 parked[kHeld][kLane / 2][T];
+  const int base = fft::xcd_ordered(blockIdx.x, gridDim.x);
+  const TBase B = bases[base];
   const int tid = threadIdx.x;
-  const double invL = 1.0 / static_cast<double>(B.len);
+  const SegmentStreams str = segment_streams(lpix, wq, wu, d, B.start);
+  const double invL = 1.0 / static_cast<double>(B.len), dx = 2.0 * invL;
   const double w = static_cast<double>(B.w);
-  if (tid < kMaxTemplates) scale[tid] = sqrt((2.0 * tid + 1.0) * invL);
-  __syncthreads();
-  const int nsteps = (B.len + kStep - 1) / kStep;
+  const int first = kLane * tid;              // the lane's first sample in step 0
+  const int wave = first - kLane * (tid & 63);  // its wavefront's: steps past the end are skipped
+  auto midpoint = [&](int j) { return fma(2.0, static_cast<double>(j), 1.0) * invL - 1.0; };
+
+  if (tid < NP * NP) kmat[tid] = kinv[static_cast<int64_t>(base) * NP * NP + tid];
 
   // ---- 1. gather and project ------------------------------------------------------------------
   double a[NP];
 #pragma unroll
   for (int k = 0; k < NP; ++k) a[k] = 0.0;
-  int ck[kCached][4];
-  double ct[kCached][4];
-  float cq[kCached][4], cu[kCached][4];
+  LanePointing<kLane, false> held[kHeld];
 #pragma unroll
-  for (int sidx = 0; sidx < kCached; ++sidx) {
-    if (sidx < nsteps) {
-      const int j0 = sidx * kStep + 4 * tid;
-      load4<kData>(lpix, wq, wu, x, d, B.start, B.len, j0, ck[sidx], ct[sidx], cq[sidx], cu[sidx]);
-      project4<NP>(ck[sidx], ct[sidx], j0, invL, w, scale, a);
+  for (int s = 0; s < kHeld; ++s)
+    if (wave + s * kStep < B.len) held[s].load(str, first + s * kStep, 0, B.len);
+#pragma unroll
+  for (int s = 0; s < kHeld; ++s) {
+    if (wave + s * kStep < B.len) {
+      const int i = first + s * kStep;
+      double t[kLane];
+      if constexpr (kData)
+        gather_lane<kLane, true>(str, x, i, 0, B.len, t);
+      else
+        held[s].resolve(x, t);
+      park(&parked[s][0][tid], t, T);
+      project<NP>(t, midpoint(i), dx, a);
     }
+    __builtin_amdgcn_sched_barrier(0);
   }
-  for (int sidx = kCached; sidx < nsteps; ++sidx) {
-    const int j0 = sidx * kStep + 4 * tid;
-    int k4[4];
-    double t4[4];
-    float q4[4], u4[4];
-    load4<kData>(lpix, wq, wu, x, d, B.start, B.len, j0, k4, t4, q4, u4);
-    project4<NP>(k4, t4, j0, invL, w, scale, a);
+#pragma unroll 1
+  for (int off = kHeld * kStep; wave + off < B.len; off += kStep) {
+    double t[kLane];
+    gather_lane<kLane, kData>(str, x, first + off, 0, B.len, t);
+    project<NP>(t, midpoint(first + off), dx, a);
   }
+  // opaque from here on: the gather's FP64 copies of the weights (64 registers) are not kept for
+  // the scatter
+#pragma unroll
+  for (int s = 0; s < kHeld; ++s)
+#pragma unroll
+    for (int j = 0; j < kLane; ++j) {
+      asm("" : "+v"(held[s].qq[j]));
+      asm("" : "+v"(held[s].uu[j]));
+    }
   // workgroup sums in a fixed order
 #pragma unroll
   for (int k = 0; k < NP; ++k) {
@@ -234,18 +195,17 @@ __global__ __launch_bounds__(kTT) void k_template_apply(
   }
   __syncthreads();
 
-  // ---- 2. c = K^+ a ---------------------------------------------------------------------------
-  if (tid < kMaxTemplates) {
+  // ---- 2. c = K^+ a, with the scales of both sides and the weight -------------------------------
+  if (tid < NP) {
     double acc = 0.0;
-    if (tid < n_poly) {
-      const double* K = kinv + static_cast<int64_t>(blockIdx.x) * n_poly * n_poly + tid * n_poly;
-      for (int k = 0; k < n_poly; ++k) {
-        double ak = 0.0;
-        for (int wv = 0; wv < kTT / 64; ++wv) ak += red[k][wv];
-        acc = fma(K[k], ak, acc);
-      }
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+      double ak = 0.0;
+#pragma unroll
+      for (int wv = 0; wv < T / 64; ++wv) ak += red[k][wv];
+      acc = fma(kmat[tid * NP + k], ak * (w * sqrt((2.0 * k + 1.0) * invL)), acc);
     }
-    coef[tid] = acc;
+    coef[tid] = acc * (w * sqrt((2.0 * tid + 1.0) * invL));
   }
   __syncthreads();
   double c[NP];
@@ -253,19 +213,33 @@ __global__ __launch_bounds__(kTT) void k_template_apply(
   for (int k = 0; k < NP; ++k) c[k] = coef[k];
 
   // ---- 3. subtract the fit, weight, point -----------------------------------------------------
+  void* list = lists[tid >> 6];
+  auto drain = [&](LanePointing<kLane, false>& lane, double (&t)[kLane], int i) {
+    subtract<NP>(t, midpoint(i), dx, w, c);
+    lane.bridge_flags(t);
+    wave_merge_runs_listed_of<kLane, 3, kListed>(
+        lane.kk,
+        [&](int j, int q) {
+          return q == 0 ? t[j] : static_cast<double>(q == 1 ? lane.qq[j] : lane.uu[j]) * t[j];
+        },
+        AtomicFlush{y}, list);
+  };
 #pragma unroll
-  for (int sidx = 0; sidx < kCached; ++sidx) {
-    if (sidx < nsteps)
-      subtract_point4<NP>(ck[sidx], ct[sidx], cq[sidx], cu[sidx], sidx * kStep + 4 * tid, invL,
-                          w, scale, c, y);
+  for (int s = 0; s < kHeld; ++s) {
+    if (wave + s * kStep < B.len) {
+      double t[kLane];
+      fetch(&parked[s][0][tid], t, T);
+      drain(held[s], t, first + s * kStep);
+    }
+    __builtin_amdgcn_sched_barrier(0);
   }
-  for (int sidx = kCached; sidx < nsteps; ++sidx) {
-    const int j0 = sidx * kStep + 4 * tid;
-    int k4[4];
-    double t4[4];
-    float q4[4], u4[4];
-    load4<kData>(lpix, wq, wu, x, d, B.start, B.len, j0, k4, t4, q4, u4);
-    subtract_point4<NP>(k4, t4, q4, u4, j0, invL, w, scale, c, y);
+#pragma unroll 1
+  for (int off = kHeld * kStep; wave + off < B.len; off += kStep) {
+    LanePointing<kLane, false> lane;
+    double t[kLane];
+    lane.load(str, first + off, 0, B.len);
+    gather_lane<kLane, kData>(str, x, first + off, 0, B.len, t);
+    drain(lane, t, first + off);
   }
 }
 
@@ -441,6 +415,7 @@ mm_status build_templates(Plan* P, const mm_geometry* g, const std::vector<Tile>
   }
   std::vector<TBase> bases;
   bases.reserve(static_cast<size_t>(nb));
+  P->base_max = 0;
   int64_t prev_end = 0;
   for (int64_t i : order) {
     const int64_t s0 = g->base_start[i], L = g->base_len[i];
@@ -471,6 +446,7 @@ mm_status build_templates(Plan* P, const mm_geometry* g, const std::vector<Tile>
                                      [](int64_t v, const Tile& t) { return v < t.start; });
     const float w = (ti == tiles.begin()) ? 1.0f : (ti - 1)->c0;
     bases.push_back(TBase{s0, static_cast<int32_t>(L), w});
+    P->base_max = std::max(P->base_max, static_cast<int32_t>(L));
   }
   // samples outside every baseline: the tiles with the baselines cut out
   std::vector<Tile> free_tiles;
@@ -526,18 +502,28 @@ mm_status build_templates(Plan* P, const mm_geometry* g, const std::vector<Tile>
 
 namespace {
 
-template <int NP>
-mm_status launch_np(Plan* P, const double* x, const float* d, double* y, const int32_t* done,
-                    hipStream_t s) {
+template <int NP, int T>
+mm_status launch_npt(Plan* P, const double* x, const float* d, double* y, const int32_t* done,
+                     hipStream_t s) {
   const dim3 grid(static_cast<unsigned>(P->n_baselines));
   if (x != nullptr)
-    hipLaunchKernelGGL((k_template_apply<false, NP>), grid, dim3(kTT), 0, s, P->lpix, P->wq,
+    hipLaunchKernelGGL((k_template_apply<false, NP, T>), grid, dim3(T), 0, s, P->lpix, P->wq,
                        P->wu, x, d, P->tbases, P->tkinv, y, done);
   else
-    hipLaunchKernelGGL((k_template_apply<true, NP>), grid, dim3(kTT), 0, s, P->lpix, P->wq,
+    hipLaunchKernelGGL((k_template_apply<true, NP, T>), grid, dim3(T), 0, s, P->lpix, P->wq,
                        P->wu, x, d, P->tbases, P->tkinv, y, done);
   MM_HIP_TRY(hipGetLastError());
   return MM_OK;
+}
+
+// The fewest threads whose held steps take the longest baseline: every sample is then read once,
+// and no wavefront idles through baselines much shorter than its workgroup's step.
+template <int NP>
+mm_status launch_np(Plan* P, const double* x, const float* d, double* y, const int32_t* done,
+                    hipStream_t s) {
+  if (P->base_max <= 64 * kLane * kHeld) return launch_npt<NP, 64>(P, x, d, y, done, s);
+  if (P->base_max <= 256 * kLane * kHeld) return launch_npt<NP, 256>(P, x, d, y, done, s);
+  return launch_npt<NP, 512>(P, x, d, y, done, s);
 }
 
 }  // namespace

@@ -136,10 +136,10 @@ constexpr int run_list_bytes() {
 // and where the runs fall on different cache lines (pixel ids far apart along the scan), a run
 // costs one memory-side atomic request instead of NV.  More than CAP runs are listed and flushed
 // CAP at a time.
-template <int SPL, int NV, int CAP, class Flush>
-__device__ __forceinline__ void wave_merge_runs_listed(const int (&key)[SPL],
-                                                       const double (&v)[SPL][NV],
-                                                       const Flush& flush, void* list) {
+// The values come from a function v(sample, component), for callers short of registers.
+template <int SPL, int NV, int CAP, class Value, class Flush>
+__device__ __forceinline__ void wave_merge_runs_listed_of(const int (&key)[SPL], const Value& v,
+                                                          const Flush& flush, void* list) {
   static_assert(SPL >= 2 && SPL <= 9, "inner-run counts must fit the 3-bit wavefront prefix");
   const int lane = static_cast<int>(threadIdx.x & 63u);
   int* skey = static_cast<int*>(list);
@@ -174,7 +174,7 @@ __device__ __forceinline__ void wave_merge_runs_listed(const int (&key)[SPL],
   auto walk = [&](int first) {
 #pragma unroll
     for (int c = 0; c < NV; ++c) {
-      acc[c] = v[0][c];
+      acc[c] = v(0, c);
       head[c] = 0.0;
     }
     int cur = key[0];
@@ -195,10 +195,10 @@ __device__ __forceinline__ void wave_merge_runs_listed(const int (&key)[SPL],
         }
         cur = key[j];
 #pragma unroll
-        for (int c = 0; c < NV; ++c) acc[c] = v[j][c];
+        for (int c = 0; c < NV; ++c) acc[c] = v(j, c);
       } else {
 #pragma unroll
-        for (int c = 0; c < NV; ++c) acc[c] += v[j][c];
+        for (int c = 0; c < NV; ++c) acc[c] += v(j, c);
       }
     }
     tk = cur;
@@ -268,6 +268,14 @@ __device__ __forceinline__ void wave_merge_runs_listed(const int (&key)[SPL],
     wave_lds_sync();  // the listed runs have been read before their slots are reused
     if (first < r_in) walk(first);
   }
+}
+
+template <int SPL, int NV, int CAP, class Flush>
+__device__ __forceinline__ void wave_merge_runs_listed(const int (&key)[SPL],
+                                                       const double (&v)[SPL][NV],
+                                                       const Flush& flush, void* list) {
+  wave_merge_runs_listed_of<SPL, NV, CAP>(
+      key, [&](int j, int c) { return v[j][c]; }, flush, list);
 }
 
 template <int NV, class Flush>

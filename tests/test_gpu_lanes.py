@@ -139,6 +139,40 @@ def test_lanes_register_noise_weight(gpu_lib, lam):
         assert np.all(rest == 7.0)
 
 
+@pytest.mark.parametrize("flag_frac", [0.0, 0.02])
+@pytest.mark.parametrize("baseline,n_poly", [(60, 1), (500, 3), (1024, 3), (1025, 2), (4096, 4),
+                                             (4097, 3), (8192, 3), (8193, 8), (20011, 3)])
+def test_lanes_template_product(gpu_lib, baseline, n_poly, flag_frac):
+    """Template products around the rules of workgroup size and held steps, with samples outside
+    every baseline (diagonal tiles) and runs of two samples (more runs than a list holds).  FP64
+    throughout: 1e-11 of the product with every factor replaced by its magnitude, which bounds
+    the sums that form each element."""
+    prob = synth.make_templates(cfg_id=800 + n_poly, n_dets=3, samples_per_det=60033,
+                                interval=20011, side=20, dwell=2, baseline=baseline,
+                                n_poly=n_poly, cover=0.9, flag_frac=flag_frac)
+    m = prob.meta
+    tp = O.template_plan_from_problem(prob)
+    plan = gpu_lib.Plan.from_problem(prob, n_poly=n_poly, base_start=m["base_start"],
+                                     base_len=m["base_len"])
+    x = np.random.default_rng(n_poly).standard_normal((tp.plan.n_kept, 3))
+
+    def magnitude(t):
+        fit = np.zeros_like(t)
+        for i, (s, L) in enumerate(zip(tp.base_start, tp.base_len)):
+            T = O.legendre_templates(int(L), n_poly)
+            fit[s:s + L] = np.abs(T) @ (np.abs(tp.Kinv[i]) @ (np.abs(T).T @ np.abs(
+                tp.w[s:s + L] * t[s:s + L])))
+        a = tp.w * (np.abs(t) + fit)
+        p = dataclasses.replace(tp.plan, wq=np.abs(tp.plan.wq), wu=np.abs(tp.plan.wu))
+        return O.point(p, a)
+
+    err = np.abs(plan.apply_A(_dev(x)).cpu().numpy() - O.template_apply_A(tp, x))
+    assert np.all(err <= 1e-11 * magnitude(O.unpoint(tp.plan, x)) + 1e-300)
+    err = np.abs(plan.rhs(_dev(prob.d[0])).cpu().numpy() - O.template_rhs(tp, prob.d[0]))
+    d = np.where(tp.plan.lpix >= 0, prob.d[0], 0.0)
+    assert np.all(err <= 1e-11 * magnitude(d) + 1e-300)
+
+
 @pytest.mark.parametrize("dwell,flag_frac", [(1, 0.02), (3, 0.6), (8, 0.0)])
 def test_lanes_diagonal_product(gpu_lib, dwell, flag_frac):
     """Diagonal weights: FP64 throughout, 1e-12 relative."""
