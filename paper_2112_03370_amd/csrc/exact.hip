@@ -8,9 +8,11 @@
 // sets its design; it runs on the plan's own segment table:
 //
 //   FFT plans      the overlap-save segments of the plan (N real samples each, N - 2 lambda
-//                  outputs).  A batch of segments is staged in two device tiles of N/2 complex
-//                  FP64 points per segment and transformed by radix-16 Stockham passes (a last
-//                  pass of radix 2, 4 or 8), one kernel launch per pass for the whole batch:
+//                  outputs).  Segments of 2^11 .. 2^15 samples run one workgroup each, the
+//                  transform in registers and LDS (k_x_fused below).  Longer ones: a batch of
+//                  segments is staged in two device tiles of N/2 complex FP64 points per segment
+//                  and transformed by radix-16 Stockham passes (a last pass of radix 2, 4 or 8),
+//                  one kernel launch per pass for the whole batch:
 //                    load      window samples t_s = x[p,0] + c_s x[p,1] + s_s x[p,2] (or the
 //                              data sample), zero outside the block, packed as complex points
 //                              z[n] = t[2n] + i t[2n+1]
@@ -28,6 +30,7 @@
 // Samples outside every block (identity rows) use the FP64 diagonal product with weight 1.
 #include <cmath>
 
+#include "fft_lds.h"
 #include "mm_internal.h"
 #include "segment_io.h"
 #include "wave_runs.h"
@@ -360,23 +363,32 @@ __global__ __launch_bounds__(kXThreads) void k_x_direct(
 }
 
 // ---- one segment per workgroup: FP64 transform with the data in registers ----------------
-// NC = 2^M complex points (M = 11..14), T = NC / 16 threads of 16 points each.  Stockham passes
+// NC = 2^M complex points (M = 10..14), T = NC / 16 threads of 16 points each.  Stockham passes
 // of radix 16, then (8 or) 4, then a last radix-4 pass; between passes the points move through
 // LDS one component at a time (NC doubles, padded one per 16 against bank conflicts).  Pass
 // butterflies b = t + i T (i < 16 / R); the last pass of the forward transform instead gives
 // thread t the butterflies {t, 4T - t, t + T, 3T - t} (thread 0: {0, 2T, T, 3T}), so that every
 // output k = b + m NC / 4 finds its mirror NC - k in the same thread and the real-spectrum step
-// runs in registers.
+// runs in registers.  The second transform runs the same passes transposed and in reverse order.
+//
+// What bounds it, at M = 14 (1,024 threads, one workgroup per CU, so that nothing overlaps a
+// segment's phases; 62 us per segment): the gather's waits 12 us, the two transforms 14 and 20 us
+// (FP64 issue 5 us each, LDS moves 5 us each, the rest barriers between them), spectrum 5, staging
+// 3, scatter 7.  64 detectors x 2^20 samples, lambda = 8192: 1,073 us with an exchange back to the
+// first pass's slots between the transforms (8.5 us per segment) and outputs staged in sample
+// order (6 us), 957 us here.  Short bands, whose segments kept more than NC outputs and therefore
+// ran the batched passes: lambda = 100 (N = 2048) 2,456 -> 495 us, 800 3,289 -> 668, 2000
+// 3,725 -> 815, 12001 3,628 -> 1,750.
 template <int M>
 struct XFused {
   static constexpr int NC = 1 << M;
   static constexpr int T = NC / 16;
-  static constexpr int R2 = M == 11 ? 8 : 16;            // second pass
-  static constexpr int R3 = M == 11 ? 4 : (M == 12 ? 4 : (M == 13 ? 8 : 16));
+  static constexpr int R2 = M == 10 ? 4 : (M == 11 ? 8 : 16);  // second pass
+  static constexpr int R3 = M <= 12 ? 4 : (M == 13 ? 8 : 16);
   static constexpr int LDS = NC + NC / 16;  // exchange area (32 more doubles: thread 0's slot)
 };
 
-__device__ __forceinline__ int xpad(int i) { return i + (i >> 4); }
+__device__ __forceinline__ constexpr int xpad(int i) { return i + (i >> 4); }
 
 // Butterfly i of thread t in a radix-R pass (16 / R per thread).
 template <int R, int T>
@@ -414,71 +426,100 @@ __device__ __forceinline__ V xopaque(V v) {
   return v;
 }
 
-// One radix-R pass on the registers (inputs already in place).
-template <int R, int T>
+// W_(pR)^(j k) of butterfly k for j < R, applied to the points: from the table for j = 1, 2, 4, 8
+// and by products for the others.
+template <int R, int NC>
+__device__ __forceinline__ void xtwiddle(double2 (&u)[R], int k, int p,
+                                         const double2* __restrict__ tw) {
+  const int step = 2 * k * (NC / (p * R));
+  const double2 w1 = tw_n(tw, step, NC);
+  double2 w2 = make_double2(1.0, 0.0), w4 = w2, w8 = w2;
+  if (R > 2) w2 = tw_n(tw, 2 * step, NC);
+  if (R > 4) w4 = tw_n(tw, 4 * step, NC);
+  if (R > 8) w8 = tw_n(tw, 8 * step, NC);
+#pragma unroll
+  for (int j = 1; j < R; ++j) {
+    double2 w = (j & 1) ? w1 : make_double2(1.0, 0.0);
+    if (j & 2) w = (j & 1) ? cmul(w, w2) : w2;
+    if (j & 4) w = (j & 3) ? cmul(w, w4) : w4;
+    if (j & 8) w = (j & 7) ? cmul(w, w8) : w8;
+    u[j] = cmul(u[j], w);
+  }
+}
+
+// One radix-R pass on the registers: from its input slots to its output slots, or, transposed
+// (the DFT matrix is symmetric), from its output slots to its input slots.
+template <int R, int T, bool kTransposed>
 __device__ __forceinline__ void xpass(double2 (&v)[16], int t, int p, bool paired,
                                       const double2* __restrict__ tw) {
-  constexpr int NC = 16 * T;
 #pragma unroll
   for (int i = 0; i < 16 / R; ++i) {
-    const int b = xbutterfly<R, T>(t, i, paired);
-    const int k = b & (p - 1);
+    const int k = xbutterfly<R, T>(t, i, paired) & (p - 1);
     double2(&u)[R] = *reinterpret_cast<double2(*)[R]>(v + i * R);
-    if (p > 1) {
-      // W_(pR)^(j k) from the table for j = 1, 2, 4, 8 and by products for the others
-      const int step = 2 * k * (NC / (p * R));
-      const double2 w1 = tw_n(tw, step, NC);
-      double2 w2 = make_double2(1.0, 0.0), w4 = w2, w8 = w2;
-      if (R > 2) w2 = tw_n(tw, 2 * step, NC);
-      if (R > 4) w4 = tw_n(tw, 4 * step, NC);
-      if (R > 8) w8 = tw_n(tw, 8 * step, NC);
-#pragma unroll
-      for (int j = 1; j < R; ++j) {
-        double2 w = (j & 1) ? w1 : make_double2(1.0, 0.0);
-        if (j & 2) w = (j & 1) ? cmul(w, w2) : w2;
-        if (j & 4) w = (j & 3) ? cmul(w, w4) : w4;
-        if (j & 8) w = (j & 7) ? cmul(w, w8) : w8;
-        u[j] = cmul(u[j], w);
-      }
-    }
+    if (!kTransposed && p > 1) xtwiddle<R, 16 * T>(u, k, p, tw);
     dft<R>(u);
+    if (kTransposed && p > 1) xtwiddle<R, 16 * T>(u, k, p, tw);
     __builtin_amdgcn_sched_barrier(0);  // one butterfly's twiddles in flight at a time
   }
 }
 
-// Move the points from the output slots of pass A to the input slots of pass B through LDS.
-template <int RA, int RB, int T>
+// Move the points from the output slots of pass A to the input slots of pass B through LDS, or,
+// transposed, back.
+template <int RA, int RB, int T, bool kTransposed>
 __device__ __forceinline__ void xexchange(double2 (&v)[16], double* sh, int t, int pa,
-                                          bool paired_a, bool paired_b) {
+                                          bool paired_b) {
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
     const int tw_ = xopaque(t);  // addresses recomputed per component, not held across
 #pragma unroll
-    for (int s = 0; s < 16; ++s) sh[xpad(xout_pos<RA, T>(tw_, s, pa, paired_a))] = c ? v[s].y : v[s].x;
+    for (int s = 0; s < 16; ++s) {
+      const int pos = kTransposed ? xin_pos<RB, T>(tw_, s, paired_b)
+                                  : xout_pos<RA, T>(tw_, s, pa, false);
+      sh[xpad(pos)] = c ? v[s].y : v[s].x;
+    }
     __syncthreads();
     const int tr_ = xopaque(t);
 #pragma unroll
     for (int s = 0; s < 16; ++s) {
-      const double val = sh[xpad(xin_pos<RB, T>(tr_, s, paired_b))];
+      const int pos = kTransposed ? xout_pos<RA, T>(tr_, s, pa, false)
+                                  : xin_pos<RB, T>(tr_, s, paired_b);
+      const double val = sh[xpad(pos)];
       if (c) v[s].y = val; else v[s].x = val;
     }
     __syncthreads();
   }
 }
 
-// Forward transform: inputs at the first pass's slots, outputs at the last pass's slots.
+// Forward transform: inputs at the first pass's slots, outputs at the last pass's (paired) slots.
 template <int M>
-__device__ __forceinline__ void xfft(double2 (&v)[16], double* sh, int t, bool paired_last,
+__device__ __forceinline__ void xfft(double2 (&v)[16], double* sh, int t,
                                      const double2* __restrict__ tw) {
   using C = XFused<M>;
   constexpr int T = C::T, R2 = C::R2, R3 = C::R3;
-  xpass<16, T>(v, t, 1, false, tw);
-  xexchange<16, R2, T>(v, sh, t, 1, false, false);
-  xpass<R2, T>(v, t, 16, false, tw);
-  xexchange<R2, R3, T>(v, sh, t, 16, false, false);
-  xpass<R3, T>(v, t, 16 * R2, false, tw);
-  xexchange<R3, 4, T>(v, sh, t, 16 * R2, false, paired_last);
-  xpass<4, T>(v, t, 16 * R2 * R3, paired_last, tw);
+  xpass<16, T, false>(v, t, 1, false, tw);
+  xexchange<16, R2, T, false>(v, sh, t, 1, false);
+  xpass<R2, T, false>(v, t, 16, false, tw);
+  xexchange<R2, R3, T, false>(v, sh, t, 16, false);
+  xpass<R3, T, false>(v, t, 16 * R2, false, tw);
+  xexchange<R3, 4, T, false>(v, sh, t, 16 * R2, true);
+  xpass<4, T, false>(v, t, 16 * R2 * R3, true, tw);
+}
+
+// The same transform by its transposed passes in reverse order: inputs at the last pass's (paired)
+// slots, where the spectrum step leaves them, outputs at the first pass's, point t + j T in slot
+// j, so that no exchange stands between the two transforms.
+template <int M>
+__device__ __forceinline__ void xfft_transposed(double2 (&v)[16], double* sh, int t,
+                                                const double2* __restrict__ tw) {
+  using C = XFused<M>;
+  constexpr int T = C::T, R2 = C::R2, R3 = C::R3;
+  xpass<4, T, true>(v, t, 16 * R2 * R3, true, tw);
+  xexchange<R3, 4, T, true>(v, sh, t, 16 * R2, true);
+  xpass<R3, T, true>(v, t, 16 * R2, false, tw);
+  xexchange<R2, R3, T, true>(v, sh, t, 16, false);
+  xpass<R2, T, true>(v, t, 16, false, tw);
+  xexchange<16, R2, T, true>(v, sh, t, 1, false);
+  xpass<16, T, true>(v, t, 1, false, tw);
 }
 
 // FP64 samples of one lane of 8 consecutive window samples, zero outside [lo, hi): P x, the data
@@ -497,7 +538,7 @@ __device__ __forceinline__ void xgather8(const SegmentStreams& win, const double
   }
 }
 
-template <int M, int kIn>
+template <int M, int kIn, bool kWide>
 __global__ __launch_bounds__(XFused<M>::T) void k_x_fused(
     const int32_t* __restrict__ lpix, const float* __restrict__ wq, const float* __restrict__ wu,
     const double* __restrict__ x, const float* __restrict__ d,
@@ -506,8 +547,14 @@ __global__ __launch_bounds__(XFused<M>::T) void k_x_fused(
   using C = XFused<M>;
   constexpr int NC = C::NC, T = C::T, PL = NC / 4;
   static_assert(C::R2 * C::R3 * 16 * 4 == NC, "pass radices");
-  __shared__ __align__(16) double sh[C::LDS + 32];
-  const Chunk c = chunks[blockIdx.x];
+  // The odd plane of the staged outputs lies past the even one's NC / 2 + 1 points; the last
+  // wavefront may start at the last of them and reads (and lists) 256 further on.
+  constexpr int kOdd = xpad(NC / 2) + 1, kEnd = kOdd + xpad(NC / 2 + 256) + 1;
+  constexpr int kXListed = 64;
+  static_assert(run_list_bytes<3, kXListed>() <= 256 * sizeof(double),
+                "run list must fit a wavefront's slice");
+  __shared__ __align__(16) double sh[C::LDS + 32 > kEnd ? C::LDS + 32 : kEnd];
+  const Chunk c = chunks[fft::xcd_ordered(blockIdx.x, gridDim.x)];
   const int t = threadIdx.x;
   const SegmentStreams win = segment_streams(lpix, wq, wu, d, c.out0 - lam);
   int lo, hi;
@@ -535,7 +582,7 @@ __global__ __launch_bounds__(XFused<M>::T) void k_x_fused(
   }
 
   // ---- forward transform; real spectrum x symbol with mirrors in the same thread -----------
-  xfft<M>(v, sh, t, true, tw0);
+  xfft<M>(v, sh, t, tw0);
   {
     const int t = xopaque(threadIdx.x);
     const double2* __restrict__ tw = reinterpret_cast<const double2*>(
@@ -602,69 +649,93 @@ __global__ __launch_bounds__(XFused<M>::T) void k_x_fused(
       for (int s2 = 0; s2 < 8; ++s2) v[s2] = own[8 + s2];
     }
   }
-  // back to the first pass's slots, then the forward transform of conj Q
+  // the forward transform of conj Q
   __syncthreads();  // every thread has reloaded its parked points
   {
     const int t2 = xopaque(threadIdx.x);
     const double2* __restrict__ tw2 = reinterpret_cast<const double2*>(
         xopaque(reinterpret_cast<uintptr_t>(tw0)));
-    xexchange<4, 16, T>(v, sh, t2, PL, true, false);
-    xfft<M>(v, sh, t2, false, tw2);
+    xfft_transposed<M>(v, sh, t2, tw2);
   }
 
-  // ---- outputs y[n] = Re G[n/2] / N (n even), -Im G[n/2] / N (n odd), staged in LDS -------
-#pragma unroll
-  for (int s = 0; s < 16; ++s) {
-    const int k = xbutterfly<4, T>(t, s >> 2, false) + (s & 3) * PL;
-    const int o0 = 2 * k - lam;
-    if (o0 >= 0 && o0 < c.out_len) sh[xpad(o0)] = v[s].x * inv_n;
-    if (o0 + 1 >= 0 && o0 + 1 < c.out_len) sh[xpad(o0 + 1)] = -v[s].y * inv_n;
-  }
-  __syncthreads();
-  // Each wavefront reads its own 512 staged outputs per round (out_len <= NC, so every round's
-  // slices lie inside sh); once read, that slice holds the wavefront's list of completed runs,
-  // flushed one FP64 value per lane.
-  constexpr int kXListed = 64;
-  static_assert(run_list_bytes<3, kXListed>() <= 512 * sizeof(double),
-                "run list must fit a wavefront's slice");
+  // ---- outputs y[2k] = Re G[k] / N, y[2k + 1] = -Im G[k] / N -------------------------------
+  // Staged from point `first` on in two planes (even and odd samples), so that a wavefront writes
+  // consecutive values.  At most NC outputs are staged at once; more (kWide) in the window's two
+  // halves, slots 0 .. 7 and then 8 .. 15, the second of which then stays live through the first
+  // half's scatter: at M = 14, whose 1,024 threads leave 128 registers each, 53 of them would
+  // spill, and a product of 64 x 2^20 samples with lambda = 8192 takes 1,143 us instead of 954.
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  for (int base = 0; base < c.out_len; base += 8 * T) {  // same trip count for every lane
-    const int i0 = base + 8 * t;
-    LanePointing<8, false> lane;
-    lane.load(win, lam + i0, lam, lam + c.out_len);
-    double u[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) u[i] = sh[xpad(i0 + i)];
-    lane.bridge_flags(u);
-    double vv[8][3];
+  for (int h = 0; h < (kWide ? 2 : 1); ++h) {
+    const int first = kWide ? h * (NC / 2) : lam >> 1;
+    const int w0 = kWide && h == 1 ? NC : lam;
+    const int w1 = kWide && h == 0 ? min(lam + c.out_len, NC) : lam + c.out_len;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      vv[i][0] = u[i];
-      vv[i][1] = static_cast<double>(lane.qq[i]) * u[i];
-      vv[i][2] = static_cast<double>(lane.uu[i]) * u[i];
+    for (int j = 0; j < (kWide ? 8 : 16); ++j) {
+      const int s = kWide ? 8 * h + j : j;
+      const int k = t + s * T - first;
+      if (kWide || static_cast<unsigned>(k) < static_cast<unsigned>((c.out_len + 2) >> 1)) {
+        sh[xpad(k)] = v[s].x * inv_n;
+        sh[kOdd + xpad(k)] = -v[s].y * inv_n;
+      }
     }
-    wave_merge_runs_listed<8, 3, kXListed>(lane.kk, vv, AtomicFlush{y},
-                                           sh + xpad(base + 512 * wave));
+    __syncthreads();
+    // Each wavefront reads its own 512 outputs per round; its slice of the odd plane, which no
+    // other wavefront reads, then holds its list of completed runs, flushed one FP64 value per
+    // lane.
+    for (int g = w0 + 512 * wave; g < w1; g += 8 * T) {  // wavefront-uniform
+      const int i = g + 8 * (t & 63);
+      LanePointing<8, false> lane;
+      lane.load(win, i, w0, w1);
+      double u[8];
+      const int b = i - 2 * first;
+      const bool odd_first = (w0 & 1) != 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const double odd = sh[kOdd + xpad((b >> 1) + q)];
+        const double even = sh[xpad(((b + 1) >> 1) + q)];
+        u[2 * q] = odd_first ? odd : even;
+        u[2 * q + 1] = odd_first ? even : odd;
+      }
+      lane.bridge_flags(u);
+      double vv[8][3];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        vv[j][0] = u[j];
+        vv[j][1] = static_cast<double>(lane.qq[j]) * u[j];
+        vv[j][2] = static_cast<double>(lane.uu[j]) * u[j];
+      }
+      wave_merge_runs_listed<8, 3, kXListed>(lane.kk, vv, AtomicFlush{y},
+                                             sh + kOdd + xpad((g - 2 * first) >> 1));
+    }
+    if (kWide && h == 0) __syncthreads();
   }
+}
+
+// Segments with more outputs than a workgroup stages at once (N / 2).
+bool wide_segments(const Plan* P) { return P->fft_n - 2 * P->lambda_max > P->fft_n / 2; }
+
+template <int M, bool kWide>
+mm_status launch_fused_mw(Plan* P, const double* x, const float* d, double* y, hipStream_t s) {
+  const double inv_n = 1.0 / static_cast<double>(P->fft_n);
+  const dim3 grid(static_cast<unsigned>(P->n_chunks)), block(XFused<M>::T);
+  if (x == nullptr)
+    hipLaunchKernelGGL((k_x_fused<M, kInData, kWide>), grid, block, 0, s, P->lpix, P->wq, P->wu, x,
+                       d, P->chunks, P->lambda_max, P->x_spec, P->x_tw, inv_n, y);
+  else if (d == nullptr)
+    hipLaunchKernelGGL((k_x_fused<M, kInMap, kWide>), grid, block, 0, s, P->lpix, P->wq, P->wu, x,
+                       d, P->chunks, P->lambda_max, P->x_spec, P->x_tw, inv_n, y);
+  else
+    hipLaunchKernelGGL((k_x_fused<M, kInResid, kWide>), grid, block, 0, s, P->lpix, P->wq, P->wu,
+                       x, d, P->chunks, P->lambda_max, P->x_spec, P->x_tw, inv_n, y);
+  MM_HIP_TRY(hipGetLastError());
+  return MM_OK;
 }
 
 template <int M>
 mm_status launch_fused_m(Plan* P, const double* x, const float* d, double* y, hipStream_t s) {
-  const double inv_n = 1.0 / static_cast<double>(P->fft_n);
-  if (x == nullptr)
-    hipLaunchKernelGGL((k_x_fused<M, kInData>), dim3(P->n_chunks), dim3(XFused<M>::T), 0, s,
-                       P->lpix, P->wq, P->wu, x, d, P->chunks, P->lambda_max, P->x_spec,
-                       P->x_tw, inv_n, y);
-  else if (d == nullptr)
-    hipLaunchKernelGGL((k_x_fused<M, kInMap>), dim3(P->n_chunks), dim3(XFused<M>::T), 0, s,
-                       P->lpix, P->wq, P->wu, x, d, P->chunks, P->lambda_max, P->x_spec,
-                       P->x_tw, inv_n, y);
-  else
-    hipLaunchKernelGGL((k_x_fused<M, kInResid>), dim3(P->n_chunks), dim3(XFused<M>::T), 0, s,
-                       P->lpix, P->wq, P->wu, x, d, P->chunks, P->lambda_max, P->x_spec,
-                       P->x_tw, inv_n, y);
-  MM_HIP_TRY(hipGetLastError());
-  return MM_OK;
+  if (wide_segments(P)) return launch_fused_mw<M, true>(P, x, d, y, s);
+  return launch_fused_mw<M, false>(P, x, d, y, s);
 }
 
 // Device buffer released at scope exit (after the caller's stream has been synchronised).
@@ -761,17 +832,19 @@ mm_status exact_product(Plan* P, const double* x, const float* d, double* y, hip
   const bool data = x == nullptr;
   if (P->n_poly > 0) return launch_template_apply(P, x, d, y, nullptr, s);  // FP64 already
   if (P->lambda_max == 0) return launch_diag_apply(P, x, d, y, nullptr, s);
-  if (P->algo == MM_TOEPLITZ_FFT && P->n_chunks > 0 && P->fft_n >= (1 << 12) &&
-      P->fft_n <= (1 << 15) && P->fft_n - 2 * P->lambda_max <= P->fft_n / 2) {
+  if (P->algo == MM_TOEPLITZ_FFT && P->n_chunks > 0 && P->fft_n >= (1 << 11) &&
+      P->fft_n <= (1 << 15)) {
     // one workgroup per segment with the transform in registers and LDS
     MM_TRY(prepare(P, s));
     switch (P->fft_n) {
+      case 1 << 11: MM_TRY(launch_fused_m<10>(P, x, d, y, s)); break;
       case 1 << 12: MM_TRY(launch_fused_m<11>(P, x, d, y, s)); break;
       case 1 << 13: MM_TRY(launch_fused_m<12>(P, x, d, y, s)); break;
       case 1 << 14: MM_TRY(launch_fused_m<13>(P, x, d, y, s)); break;
       default: MM_TRY(launch_fused_m<14>(P, x, d, y, s)); break;
     }
     if (P->n_id_tiles > 0) MM_TRY(launch_diag_tiles(P, P->id_tiles, P->n_id_tiles, x, d, y, nullptr, s));
+    if (wide_segments(P)) MM_HIP_TRY(hipStreamSynchronize(s));  // documented as synchronous
     return MM_OK;
   }
   if (P->algo == MM_TOEPLITZ_FFT) {

@@ -95,6 +95,25 @@ def test_lanes_fp64_product(gpu_lib, lam, dwell, flag_frac):
     assert np.linalg.norm(got - O.apply_A(ref, x)) <= 1e-12 * scale
 
 
+@pytest.mark.parametrize("n,lam", [(2048, 1), (2048, 301), (2048, 600), (4096, 1023), (4096, 1025),
+                                   (8192, 999), (8192, 2500), (16384, 4095), (16384, 4096),
+                                   (32768, 1), (32768, 8191), (32768, 8193)])
+def test_lanes_fp64_segments(gpu_lib, n, lam):
+    """FP64 segments of every size with more and with at most N / 2 outputs, even and odd bands."""
+    prob, ref = _problem(3, lam, 0.02, n_dets=2, per_det=60013, interval=40011)
+    plan = gpu_lib.Plan.from_problem(prob, precision=gpu_lib.PRECISION_FP64,
+                                     toeplitz_algo=gpu_lib.TOEPLITZ_FFT, fft_size=n)
+    x = np.random.default_rng(lam).standard_normal((ref.n_kept, 3))
+    absref = dataclasses.replace(ref, bands=[np.abs(b) for b in ref.bands],
+                                 wq=np.abs(ref.wq), wu=np.abs(ref.wu))
+    got = plan.apply_A(_dev(x)).cpu().numpy()
+    scale = np.linalg.norm(O.apply_A(absref, np.abs(x)))
+    assert np.linalg.norm(got - O.apply_A(ref, x)) <= 1e-12 * scale
+    b = plan.rhs(_dev(prob.d[0])).cpu().numpy()
+    d = np.abs(np.where(prob.pix >= 0, prob.d[0], 0.0))
+    assert np.linalg.norm(b - O.rhs(ref, prob.d[0])) <= 1e-12 * np.linalg.norm(O.rhs(absref, d))
+
+
 @pytest.mark.parametrize("unfused", [False, True])
 @pytest.mark.parametrize("lam", [1, 6, 7, 8, 9, 15, 16, 17, 32, 33, 500, 4096])
 def test_lanes_direct_product(gpu_lib, lam, unfused):
