@@ -12,6 +12,10 @@
 // by one slot per 8 samples: lanes 8 samples apart then hit different banks.  Samples outside
 // every block are tiles with band -1 (identity rows, c_0 = 1).
 //
+// FP64 plans take the fused form with window, sums and map products in FP64: 64 detectors x 2^20
+// samples, lambda = 32, 2,097 us with 4 outputs per thread, two window samples read per
+// multiply-add, and one load at a time in the gather; 396 us here (lambda = 8: 740 and 284).
+//
 // Bound by the pointing's bytes at short bands (lambda = 16: 12 B against 50 multiply-adds a
 // sample).  64 detectors x 2^18 samples, lambda = 16: 188 us for the three kernels (un-pointing
 // 44, direct product 95, pointing 47) before, 73 us fused.
@@ -56,15 +60,20 @@ __device__ __forceinline__ int slot(int i) { return i + (i >> 3); }
 
 // LDS bytes: the window of a tile with 8 samples before and after it (the last round of sums reads
 // up to 7 past either end), or the run lists that replace it.
+template <class T>
 inline size_t lds_bytes(int lambda) {
   const int window = (kTile + 2 * lambda + kLane - 1) / kLane + 2;
-  return std::max<size_t>(sizeof(float) * static_cast<size_t>(window * (kLane + 1)),
+  return std::max<size_t>(sizeof(T) * static_cast<size_t>(window * (kLane + 1)),
                           kWaves * run_list_bytes<3, kListed>());
 }
 
-template <int IO>
+__device__ __forceinline__ float mul_add(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double mul_add(double a, double b, double c) { return fma(a, b, c); }
+
+template <int IO, class T>
 __global__ __launch_bounds__(kThreads) void k_direct(const DirectArgs a) {
-  extern __shared__ __align__(16) float xs[];
+  extern __shared__ __align__(16) char lds[];
+  T* xs = reinterpret_cast<T*>(lds);
   if (a.done != nullptr && *a.done) return;
   const int tid = threadIdx.x;
   const int col = static_cast<int>(blockIdx.x) % a.ncol;
@@ -81,7 +90,7 @@ __global__ __launch_bounds__(kThreads) void k_direct(const DirectArgs a) {
 
   // ---- window: sample out0 - lam + i at slot(i + 8), zero outside the block -----------------
   for (int i = tid * kLane; i < nin; i += kTile) {
-    float v[kLane];
+    T v[kLane];
     if constexpr (IO == kIoPlain) {
       if (i >= lo && i + kLane <= hi) {
         load4u(win.d + static_cast<uint32_t>(i), v);
@@ -103,14 +112,14 @@ __global__ __launch_bounds__(kThreads) void k_direct(const DirectArgs a) {
   // window's first or past its last are read (slots of the padding, or whatever a shorter tile
   // left there) only into sums that no output uses.
   const int o = tid * kLane;
-  const float* mine = xs + (kLane + 1) * tid;
+  const T* mine = xs + (kLane + 1) * tid;
   auto at = [&](int i) { return mine[slot(i + kLane)]; };
-  const float c0 = coef != nullptr ? coef[0] : 1.0f;
-  float acc[kLane];
+  const T c0 = coef != nullptr ? coef[0] : 1.0f;
+  T acc[kLane];
 #pragma unroll
   for (int j = 0; j < kLane; ++j) acc[j] = c0 * at(lam + j);
   // a round's k0 .. k0 + 7: left[i] = at(lam - k0 - 7 + i), right[i] = at(lam + k0 + i), i < 15
-  float left[2 * kLane - 1], right[2 * kLane - 1];
+  T left[2 * kLane - 1], right[2 * kLane - 1];
 #pragma unroll
   for (int j = 0; j < kLane - 1; ++j) {
     left[kLane + j] = at(lam + j);
@@ -125,10 +134,10 @@ __global__ __launch_bounds__(kThreads) void k_direct(const DirectArgs a) {
 #pragma unroll
     for (int m = 0; m < kLane; ++m) {
       if (k0 + m <= lam) {
-        const float ck = coef[k0 + m];
+        const T ck = coef[k0 + m];
 #pragma unroll
         for (int j = 0; j < kLane; ++j)
-          acc[j] = fmaf(ck, left[kLane - 1 + j - m] + right[j + m], acc[j]);
+          acc[j] = mul_add(ck, left[kLane - 1 + j - m] + right[j + m], acc[j]);
       }
     }
 #pragma unroll
@@ -163,16 +172,21 @@ __global__ __launch_bounds__(kThreads) void k_direct(const DirectArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     wave_merge_runs_listed<kLane, 3, kListed>(
         lane.kk, val, AtomicFlush{a.y0 + col * a.ldy},
-        reinterpret_cast<char*>(xs) + wave * run_list_bytes<3, kListed>());
+        lds + wave * run_list_bytes<3, kListed>());
   }
 }
 
-template <int IO>
+template <int IO, class T>
 mm_status launch(Plan* P, const DirectArgs& a, int64_t n_tiles, hipStream_t s) {
   const int64_t grid = n_tiles * a.ncol;
   if (grid > INT32_MAX) return fail(MM_ERR_UNSUPPORTED, "too many tile x column workgroups");
-  hipLaunchKernelGGL(k_direct<IO>, dim3(static_cast<unsigned>(grid)), dim3(kThreads),
-                     lds_bytes(P->lambda_max), s, a);
+  const size_t lds = lds_bytes<T>(P->lambda_max);
+  if (lds > 64 * 1024)  // FP64 windows of lambda > 3,000
+    MM_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_direct<IO, T>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   static_cast<int>(lds)));
+  hipLaunchKernelGGL((k_direct<IO, T>), dim3(static_cast<unsigned>(grid)), dim3(kThreads), lds, s,
+                     a);
   MM_HIP_TRY(hipGetLastError());
   return MM_OK;
 }
@@ -202,12 +216,12 @@ mm_status launch_toeplitz_direct(Plan* P, const float* t, float* u, const int32_
   DirectArgs a = base_args(P, done);
   a.t = t;
   a.u = u;
-  return launch<kIoPlain>(P, a, P->n_chunks, s);
+  return launch<kIoPlain, float>(P, a, P->n_chunks, s);
 }
 
 mm_status launch_apply_direct(Plan* P, const double* x, const float* d, double* y,
                               const int32_t* done, hipStream_t s, int32_t ncol, int64_t ldx,
-                              int64_t ldy) {
+                              int64_t ldy, bool fp64) {
   const int64_t n_tiles = static_cast<int64_t>(P->n_chunks) + P->n_id_chunks;
   if (P->n_kept == 0 || ncol <= 0 || n_tiles == 0) return MM_OK;
   TimedLaunch tl(P, K_TOEPLITZ, s);
@@ -218,7 +232,11 @@ mm_status launch_apply_direct(Plan* P, const double* x, const float* d, double* 
   a.ldx = ldx != 0 ? ldx : (d != nullptr ? P->n_samples : 3 * P->n_kept);
   a.ldy = ldy != 0 ? ldy : 3 * P->n_kept;
   a.ncol = ncol;
-  return d != nullptr ? launch<kIoRhs>(P, a, n_tiles, s) : launch<kIoApply>(P, a, n_tiles, s);
+  if (fp64)
+    return d != nullptr ? launch<kIoRhs, double>(P, a, n_tiles, s)
+                        : launch<kIoApply, double>(P, a, n_tiles, s);
+  return d != nullptr ? launch<kIoRhs, float>(P, a, n_tiles, s)
+                      : launch<kIoApply, float>(P, a, n_tiles, s);
 }
 
 }  // namespace mm

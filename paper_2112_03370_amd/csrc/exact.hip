@@ -24,8 +24,7 @@
 //                    forward   G = DFT_{N/2}(conj Q); y[2n] = Re G[n] / N, y[2n+1] = -Im G[n] / N
 //                    scatter   outputs lambda .. lambda + out_len of each segment, P^T in FP64
 //                              through the wavefront run merge
-//   direct plans   each tile of <= 1024 outputs stages its window of FP64 samples in LDS and
-//                  sums c_|j| t_(i+j) over |j| <= lambda in FP64
+//   direct plans   the fused direct product with FP64 windows and sums (direct.hip)
 //   lambda = 0     the diagonal product, which is FP64 already
 // Samples outside every block (identity rows) use the FP64 diagonal product with weight 1.
 #include <cmath>
@@ -302,64 +301,6 @@ __global__ __launch_bounds__(kXThreads) void k_x_scatter(
     }
   }
   wave_merge_runs_listed<4, 3, kScatterListed>(key, v, AtomicFlush{y}, list[wave]);
-}
-
-// ---- direct product for short bands (direct plans) ---------------------------------------
-template <bool kData>
-__global__ __launch_bounds__(kXThreads) void k_x_direct(
-    const int32_t* __restrict__ lpix, const float* __restrict__ wq, const float* __restrict__ wu,
-    const double* __restrict__ x, const float* __restrict__ d, const Chunk* __restrict__ tiles,
-    const float* __restrict__ band_coef, const int64_t* __restrict__ band_off,
-    const int32_t* __restrict__ band_ncoef, double* __restrict__ y) {
-  extern __shared__ double xs[];  // window: out_len + 2 lambda samples, then lambda + 1 coefs
-  const Chunk c = tiles[blockIdx.x];
-  const int lam = band_ncoef[c.band] - 1;
-  const float* coef = band_coef + band_off[c.band];
-  const int nin = c.out_len + 2 * lam;
-  double* cs = xs + nin;
-  const int64_t b0 = c.blk_start, b1 = c.blk_start + c.blk_len;
-  for (int i = threadIdx.x; i < nin; i += kXThreads) {
-    const int64_t g = c.out0 - lam + i;
-    double t = 0.0;
-    if (g >= b0 && g < b1) {
-      const int p = lpix[g];
-      if (p >= 0) {
-        if (kData) {
-          t = static_cast<double>(d[g]);
-        } else {
-          const double* m = x + 3 * static_cast<int64_t>(p);
-          t = m[0] + static_cast<double>(wq[g]) * m[1] + static_cast<double>(wu[g]) * m[2];
-        }
-      }
-    }
-    xs[i] = t;
-  }
-  for (int i = threadIdx.x; i <= lam; i += kXThreads) cs[i] = static_cast<double>(coef[i]);
-  __syncthreads();
-  for (int o0 = 0; o0 < c.out_len; o0 += 4 * kXThreads) {
-    int key[4];
-    double v[4][3];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int o = o0 + 4 * threadIdx.x + q;
-      key[q] = -1;
-      v[q][0] = v[q][1] = v[q][2] = 0.0;
-      if (o < c.out_len) {
-        const int64_t g = c.out0 + o;
-        const int p = lpix[g];
-        if (p >= 0) {
-          const double* xc = xs + o + lam;
-          double acc = cs[0] * xc[0];
-          for (int j = 1; j <= lam; ++j) acc += cs[j] * (xc[-j] + xc[j]);
-          key[q] = p;
-          v[q][0] = acc;
-          v[q][1] = static_cast<double>(wq[g]) * acc;
-          v[q][2] = static_cast<double>(wu[g]) * acc;
-        }
-      }
-    }
-    wave_merge_runs<3>(key, v, AtomicFlush{y});
-  }
 }
 
 // ---- one segment per workgroup: FP64 transform with the data in registers ----------------
@@ -888,29 +829,7 @@ mm_status exact_product(Plan* P, const double* x, const float* d, double* y, hip
     MM_HIP_TRY(hipStreamSynchronize(s));  // the tiles are released on return
     return MM_OK;
   }
-  // direct plans: tiles of <= 1024 outputs with their lambda halo in LDS
-  if (P->n_chunks > 0) {
-    const size_t lds = sizeof(double) * (1024 + 2 * static_cast<size_t>(P->lambda_max) +
-                                         static_cast<size_t>(P->lambda_max) + 1);
-    if (lds > 160 * 1024) return fail(MM_ERR_UNSUPPORTED, "FP64 direct product: band too long");
-    if (lds > 64 * 1024) {
-      MM_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_x_direct<true>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
-      MM_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(k_x_direct<false>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
-    }
-    if (data)
-      hipLaunchKernelGGL(k_x_direct<true>, dim3(P->n_chunks), dim3(kXThreads), lds, s, P->lpix,
-                         P->wq, P->wu, x, d, P->chunks, P->band_coef, P->band_off,
-                         P->band_ncoef, y);
-    else
-      hipLaunchKernelGGL(k_x_direct<false>, dim3(P->n_chunks), dim3(kXThreads), lds, s, P->lpix,
-                         P->wq, P->wu, x, d, P->chunks, P->band_coef, P->band_off,
-                         P->band_ncoef, y);
-    MM_HIP_TRY(hipGetLastError());
-  }
-  if (P->n_id_tiles > 0) MM_TRY(launch_diag_tiles(P, P->id_tiles, P->n_id_tiles, x, d, y, nullptr, s));
-  return MM_OK;
+  return launch_apply_direct(P, x, d, y, nullptr, s, 1, 0, 0, true);
 }
 
 }  // namespace mm

@@ -408,7 +408,7 @@ mm_status launch_toeplitz_direct(Plan* P, const float* t, float* u, const int32_
                                  hipStream_t s);
 mm_status launch_apply_direct(Plan* P, const double* x, const float* d, double* y,
                               const int32_t* done, hipStream_t s, int32_t ncol = 1,
-                              int64_t ldx = 0, int64_t ldy = 0);
+                              int64_t ldx = 0, int64_t ldy = 0, bool fp64 = false);
 // Long segments (toeplitz_long.hip): N = 2^16, 2^17 through a global tile per segment.
 bool long_fft_size(int32_t n);
 int32_t long_fine_size();

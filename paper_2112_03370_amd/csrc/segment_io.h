@@ -11,12 +11,6 @@ namespace mm {
 
 struct AtomicFlush {
   double* y;
-  __device__ void operator()(int key, const double (&v)[3]) const {
-    double* dst = y + 3 * static_cast<int64_t>(key);
-    unsafeAtomicAdd(dst + 0, v[0]);
-    unsafeAtomicAdd(dst + 1, v[1]);
-    unsafeAtomicAdd(dst + 2, v[2]);
-  }
   __device__ void one(int key, int c, double v) const {
     unsafeAtomicAdd(y + 3 * static_cast<int64_t>(key) + c, v);
   }

@@ -200,3 +200,29 @@ def test_lanes_diagonal_product(gpu_lib, dwell, flag_frac):
     x = np.random.default_rng(dwell).standard_normal((ref.n_kept, 3))
     assert _rel(plan.apply_A(_dev(x)).cpu().numpy(), O.apply_A(ref, x)) <= 1e-12
     assert _rel(plan.rhs(_dev(prob.d[0])).cpu().numpy(), O.rhs(ref, prob.d[0])) <= 1e-12
+
+
+@pytest.mark.parametrize("lam", [1, 7, 8, 9, 32, 33, 500, 4096])
+def test_lanes_fp64_direct_product(gpu_lib, lam):
+    """FP64 direct products around the rounds of eight lags (and a window beyond 64 KiB of LDS),
+    with blocks shorter than the band, samples outside every block, ragged tiles and flags."""
+    prob = synth.make_random_small(seed=41, n_samples=13007, n_pix=60, n_dets=4, lam_max=4,
+                                   flag_frac=0.1, gap_frac=0.3, dwell=5)
+    k = np.arange(lam + 1)
+    c = -0.3 * np.exp(-k / (1.0 + lam / 4.0)) / (1.0 + lam / 8.0)
+    c[0] = 1.0 + 2.0 * np.abs(c[1:]).sum()
+    bands = [c.astype(np.float32)] + [(c[: max(1, lam // 2)] * 1.5).astype(np.float32)] * (
+        len(prob.bands) - 1)
+    prob = dataclasses.replace(prob, bands=bands)
+    ref = O.plan_from_problem(prob)
+    plan = gpu_lib.Plan.from_problem(prob, toeplitz_algo=gpu_lib.TOEPLITZ_DIRECT,
+                                     precision=gpu_lib.PRECISION_FP64)
+    absref = dataclasses.replace(ref, bands=[np.abs(b) for b in ref.bands],
+                                 wq=np.abs(ref.wq), wu=np.abs(ref.wu))
+    x = np.random.default_rng(lam).standard_normal((ref.n_kept, 3))
+    got = plan.apply_A(_dev(x)).cpu().numpy()
+    scale = np.linalg.norm(O.apply_A(absref, np.abs(x)))
+    assert np.linalg.norm(got - O.apply_A(ref, x)) <= 1e-12 * scale
+    b = plan.rhs(_dev(prob.d[0])).cpu().numpy()
+    d = np.abs(np.where(prob.pix >= 0, prob.d[0], 0.0))
+    assert np.linalg.norm(b - O.rhs(ref, prob.d[0])) <= 1e-12 * np.linalg.norm(O.rhs(absref, d))
