@@ -11,13 +11,15 @@
 //
 // The gather is bound by the number of vector memory instructions, not by bytes: a lane takes
 // 8 consecutive samples (two 16-byte loads per pointing array) and loads a pixel's three values
-// only when the pixel changes, which scan runs make rare.
+// only when the pixel changes, which scan runs make rare.  On small problems, with one or two
+// wavefronts to a segment and a segment to a CU, its waits count: two rounds are in flight.
+// Rates: 64 detectors x 2^19 samples on 16-sample runs, lambda = 1000 (N = 4096) 222 us; 61
+// detectors x 200,003 samples on 7-sample runs with 2 % flags, lambda = 2047, 101 us (254 us with
+// scalar loads where windows start unaligned and runs flushed where they end).
 #include "fft_lds.h"
 #include "mm_internal.h"
 #include "segment_io.h"
 #include "wave_runs.h"
-
-
 
 namespace mm {
 
@@ -37,6 +39,8 @@ constexpr int kScatterLane = 8;
 // samples of the window's end may reach past it: at most kListSlack points.
 constexpr int kListed = 64;
 constexpr int kListSlack = 96;
+constexpr int kReadSlack = 8;  // points that the last output's lane reads past the window
+constexpr int kListPoints = run_list_bytes<3, kListed>() / static_cast<int>(sizeof(float2));
 static_assert(run_list_bytes<3, kListed>() <= 254 * sizeof(float2),
               "run list must fit between the shared points of a slice");
 
@@ -50,7 +54,8 @@ __global__ __launch_bounds__(FftCfg<LOG>::T) void k_apply_fused(
     const int32_t* __restrict__ done) {
   using C = FftCfg<LOG>;
   constexpr int NC = C::NC, N = C::N, T = C::T;
-  __shared__ float2 buf[C::LDS + kListSlack];
+  constexpr int kBuf = C::LDS + (T > 64 ? kListSlack : kReadSlack);
+  __shared__ float2 buf[kBuf];
   __shared__ float2 tw0[128];
   __shared__ float2 tw1[N / 128];
   if (done != nullptr && *done) return;
@@ -77,16 +82,32 @@ __global__ __launch_bounds__(FftCfg<LOG>::T) void k_apply_fused(
   // half first, so both readers of a shared half fetch it together and the second finds it in
   // L2.
   constexpr int SG = kGatherLane;
+  // Two rounds' loads in flight where registers allow (LOG = 14 has 128 and uses them all): at
+  // lambda = 512, 18 detectors x 2^17 samples, a solve takes 1,236 us against 1,264 with one; all
+  // four at once take 208 registers and 1,477 us.
+  constexpr int kDeep = LOG <= 13 ? 2 : 1;
   static_assert(N == 4 * T * SG, "four gather rounds");
   const int rot = ((wg / ncol) & 1) == 0 ? 2 : 0;
-  for (int rr = 0; rr < 4; ++rr) {
-    const int n = ((rr + rot) & 3) * (T * SG) + tid * SG;
-    float v[SG];
-    gather_lane<SG, kFromData>(win, x, n, lo, hi, v);
-    // samples n..n+SG-1 are complex points n/2.. (n/2 even: contiguous pairs after padding)
-    float2* dst = buf + pad(n >> 1);
+  for (int rr = 0; rr < 4; rr += kDeep) {
+    LanePointing<SG, kFromData> lane[kDeep];
+    typename LanePointing<SG, kFromData>::Pixels px[kDeep];
+    int n[kDeep];
 #pragma unroll
-    for (int j = 0; j < SG / 2; ++j) dst[j] = make_float2(v[2 * j], v[2 * j + 1]);
+    for (int e = 0; e < kDeep; ++e) {
+      n[e] = ((rr + e + rot) & 3) * (T * SG) + tid * SG;
+      lane[e].load(win, n[e], lo, hi);
+    }
+#pragma unroll
+    for (int e = 0; e < kDeep; ++e) lane[e].fetch(x, px[e]);
+#pragma unroll
+    for (int e = 0; e < kDeep; ++e) {
+      float v[SG];
+      lane[e].finish(x, px[e], v);
+      // samples n..n+SG-1 are complex points n/2.. (n/2 even: contiguous pairs after padding)
+      float2* dst = buf + pad(n[e] >> 1);
+#pragma unroll
+      for (int j = 0; j < SG / 2; ++j) dst[j] = make_float2(v[2 * j], v[2 * j + 1]);
+    }
   }
   __syncthreads();
 
@@ -99,14 +120,34 @@ __global__ __launch_bounds__(FftCfg<LOG>::T) void k_apply_fused(
   constexpr int SS = kScatterLane;
   const AtomicFlush flush{y};
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  for (int base = 0; base < c.out_len; base += T * SS) {  // same trip count for every lane
+  // (wavefronts past the last output have nothing to do in the last round)
+  for (int base = 0; base + 64 * SS * wave < c.out_len; base += T * SS) {
     const int i0 = base + tid * SS;
-    float u[SS];
     LanePointing<SS, false> lane;
     lane.load(win, lam + i0, lam, lam + c.out_len);
+    // the lane's outputs: window samples lam + i0 on, two to a point (samples past the last output
+    // have no pixel, and bridge_flags clears their values)
+    float2 z[SS / 2 + 1];
 #pragma unroll
-    for (int j = 0; j < SS; ++j)
-      u[j] = i0 + j < c.out_len ? real_out(buf, lam + i0 + j) : 0.0f;
+    for (int q = 0; q <= SS / 2; ++q) z[q] = make_float2(0.0f, 0.0f);
+    if (i0 < c.out_len) {
+#pragma unroll
+      for (int q = 0; q <= SS / 2; ++q) z[q] = buf[pad(((lam + i0) >> 1) + q)];
+    }
+    float u[SS];
+    if (lam & 1) {  // uniform
+#pragma unroll
+      for (int q = 0; q < SS / 2; ++q) {
+        u[2 * q] = -z[q].y;
+        u[2 * q + 1] = z[q + 1].x;
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < SS / 2; ++q) {
+        u[2 * q] = z[q].x;
+        u[2 * q + 1] = -z[q].y;
+      }
+    }
     lane.bridge_flags(u);
     double v[SS][3];
 #pragma unroll
@@ -116,8 +157,9 @@ __global__ __launch_bounds__(FftCfg<LOG>::T) void k_apply_fused(
       v[j][1] = static_cast<double>(lane.qq[j]) * tv;
       v[j][2] = static_cast<double>(lane.uu[j]) * tv;
     }
-    wave_merge_runs_listed<SS, 3, kListed>(
-        lane.kk, v, flush, buf + pad(((lam + base + 64 * SS * wave) >> 1) + 1));
+    int at = pad(((lam + base + 64 * SS * wave) >> 1) + 1);
+    if constexpr (T == 64) at = min(at, kBuf - kListPoints);
+    wave_merge_runs_listed<SS, 3, kListed>(lane.kk, v, flush, buf + at);
   }
 }
 

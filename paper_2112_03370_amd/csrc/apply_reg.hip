@@ -516,7 +516,7 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(4))) void k_
                 "run list must fit the wavefront's slice of the staged outputs");
   static_assert((kHalf + kT * kLane - 1) / (kT * kLane) * (kT * kLane) <= kLdsF,
                 "every round's slices lie inside the staging buffer");
-  for (int base = 0; base < out_len; base += kT * kLane) {  // same trip count for every lane
+  for (int base = 0; base + 64 * kLane * wave < out_len; base += kT * kLane) {
     const int i0 = base + tid * kLane;
     float u[kLane];
     LanePointing<kLane, false> lane;

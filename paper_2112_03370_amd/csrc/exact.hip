@@ -318,8 +318,8 @@ __global__ __launch_bounds__(kXThreads) void k_x_scatter(
 // 3, scatter 7.  64 detectors x 2^20 samples, lambda = 8192: 1,073 us with an exchange back to the
 // first pass's slots between the transforms (8.5 us per segment) and outputs staged in sample
 // order (6 us), 957 us here.  Short bands, whose segments kept more than NC outputs and therefore
-// ran the batched passes: lambda = 100 (N = 2048) 2,456 -> 495 us, 800 3,289 -> 668, 2000
-// 3,725 -> 815, 12001 3,628 -> 1,750.
+// ran the batched passes: lambda = 100 (N = 2048) 2,456 -> 516 us, 800 3,289 -> 681, 2000
+// 3,725 -> 828, 12001 3,628 -> 1,750.
 template <int M>
 struct XFused {
   static constexpr int NC = 1 << M;

@@ -133,99 +133,109 @@ struct LanePointing {
   // Scan runs keep a pixel for several consecutive samples, so a lane usually sees one or two
   // pixels: the lane's first and last pixels are loaded together, with the first other pixel
   // between them where some lane of the wavefront has one (short runs), all behind a single wait;
-  // further pixels, one at a time, only when they occur.
+  // further pixels, one at a time, only when they occur.  fetch() issues those loads and
+  // finish() forms the samples, so that a caller can have several lanes' loads in flight.
+  struct Pixels {
+    int ka, kb, kc;  // first, last and first other pixel; -1: none
+    bool flagged, more;  // wavefront-uniform: some lane has flagged samples, an other pixel
+    double a[3], b[3], c[3];
+  };
+
+  __device__ __forceinline__ static void load_pixel(const double* __restrict__ x, int k,
+                                                    double (&m)[3]) {
+    const double* p = x + 3 * static_cast<int64_t>(k);
+    m[0] = p[0];
+    m[1] = p[1];
+    m[2] = p[2];
+  }
+
+  __device__ __forceinline__ void fetch(const double* __restrict__ x, Pixels& f) const {
+    if constexpr (!kFromData) {
+      // The tests for flagged samples sit behind a wavefront-uniform branch (per sample, the
+      // compiler turns them into a branch around that sample's sums).
+      f.ka = kk[0];
+      f.kb = kk[S - 1];
+      bool other = false;
+      f.flagged = __any(least_key() < 0);
+      if (f.flagged) {
+        f.ka = f.kb = -1;  // the first and last pixels observed
+#pragma unroll
+        for (int j = 0; j < S; ++j) {
+          f.kb = kk[j] >= 0 ? kk[j] : f.kb;
+          f.ka = kk[S - 1 - j] >= 0 ? kk[S - 1 - j] : f.ka;
+        }
+#pragma unroll
+        for (int j = 1; j < S - 1; ++j) other |= kk[j] >= 0 && kk[j] != f.ka && kk[j] != f.kb;
+      } else {
+#pragma unroll
+        for (int j = 1; j < S - 1; ++j) other |= kk[j] != f.ka && kk[j] != f.kb;
+      }
+#pragma unroll
+      for (int q = 0; q < 3; ++q) f.a[q] = f.b[q] = f.c[q] = 0.0;
+      if (f.ka >= 0) load_pixel(x, f.ka, f.a);
+      if (f.kb >= 0 && f.kb != f.ka) load_pixel(x, f.kb, f.b);
+      f.more = __any(other);
+      f.kc = -1;
+      if (f.more) {
+#pragma unroll
+        for (int j = S - 2; j > 0; --j)
+          f.kc = kk[j] >= 0 && kk[j] != f.ka && kk[j] != f.kb ? kk[j] : f.kc;
+        if (f.kc >= 0) load_pixel(x, f.kc, f.c);
+      }
+    }
+  }
+
   template <class T>
-  __device__ __forceinline__ void resolve(const double* __restrict__ x, T (&v)[S]) const {
+  __device__ __forceinline__ void finish(const double* __restrict__ x, Pixels& f,
+                                         T (&v)[S]) const {
     if constexpr (kFromData) {
 #pragma unroll
       for (int j = 0; j < S; ++j) v[j] = kk[j] < 0 ? T(0) : static_cast<T>(qq[j]);
     } else {
-      // The tests for flagged samples sit behind a wavefront-uniform branch (per sample, the
-      // compiler turns them into a branch around that sample's sums).
-      int ka = kk[0], kb = kk[S - 1];
-      bool other = false;
-      const bool flagged = __any(least_key() < 0);
-      if (flagged) {
-        ka = kb = -1;  // the first and last pixels observed
-#pragma unroll
-        for (int j = 0; j < S; ++j) {
-          kb = kk[j] >= 0 ? kk[j] : kb;
-          ka = kk[S - 1 - j] >= 0 ? kk[S - 1 - j] : ka;
-        }
-#pragma unroll
-        for (int j = 1; j < S - 1; ++j) other |= kk[j] >= 0 && kk[j] != ka && kk[j] != kb;
-      } else {
-#pragma unroll
-        for (int j = 1; j < S - 1; ++j) other |= kk[j] != ka && kk[j] != kb;
-      }
-      double a0 = 0.0, a1 = 0.0, a2 = 0.0, b0 = 0.0, b1 = 0.0, b2 = 0.0;
-      if (ka >= 0) {
-        const double* m = x + 3 * static_cast<int64_t>(ka);
-        a0 = m[0];
-        a1 = m[1];
-        a2 = m[2];
-      }
-      if (kb >= 0 && kb != ka) {
-        const double* m = x + 3 * static_cast<int64_t>(kb);
-        b0 = m[0];
-        b1 = m[1];
-        b2 = m[2];
-      }
-      const bool more = __any(other);
-      int kc = -1;
-      double c0 = 0.0, c1 = 0.0, c2 = 0.0;
-      if (more) {
-#pragma unroll
-        for (int j = S - 2; j > 0; --j)
-          kc = kk[j] >= 0 && kk[j] != ka && kk[j] != kb ? kk[j] : kc;
-        if (kc >= 0) {
-          const double* m = x + 3 * static_cast<int64_t>(kc);
-          c0 = m[0];
-          c1 = m[1];
-          c2 = m[2];
-        }
-      }
 #pragma unroll
       for (int j = 0; j < S; ++j) {
         // both candidate pixels' sums, then one select (cheaper than selecting three FP64
         // pixel values)
         const double q = static_cast<double>(qq[j]), u = static_cast<double>(uu[j]);
-        const double ta = a0 + q * a1 + u * a2;
-        const double tb = b0 + q * b1 + u * b2;
-        v[j] = static_cast<T>(kk[j] == ka ? ta : tb);
+        const double ta = f.a[0] + q * f.a[1] + u * f.a[2];
+        const double tb = f.b[0] + q * f.b[1] + u * f.b[2];
+        v[j] = static_cast<T>(kk[j] == f.ka ? ta : tb);
       }
-      if (flagged) {
+      if (f.flagged) {
 #pragma unroll
         for (int j = 0; j < S; ++j) v[j] = kk[j] < 0 ? T(0) : v[j];
       }
-      if (more) {
+      if (f.more) {
         int done = 0;  // samples before this one are resolved as far as kc goes
         while (true) {
 #pragma unroll
           for (int j = 1; j < S - 1; ++j) {
-            const double t = c0 + static_cast<double>(qq[j]) * c1 + static_cast<double>(uu[j]) * c2;
-            if (kc >= 0 && kk[j] == kc) v[j] = static_cast<T>(t);
+            const double t = f.c[0] + static_cast<double>(qq[j]) * f.c[1] +
+                             static_cast<double>(uu[j]) * f.c[2];
+            if (f.kc >= 0 && kk[j] == f.kc) v[j] = static_cast<T>(t);
           }
           // the next pixel after kc's first sample that none of the loaded ones was
           int next = -1, at = S;
 #pragma unroll
           for (int j = S - 2; j > 0; --j)
-            if (j > done && kk[j] >= 0 && kk[j] != ka && kk[j] != kb && kk[j] != kc) {
+            if (j > done && kk[j] >= 0 && kk[j] != f.ka && kk[j] != f.kb && kk[j] != f.kc) {
               next = kk[j];
               at = j;
             }
           if (!__any(next >= 0)) break;
           done = at;
-          kc = next;
-          if (kc >= 0) {
-            const double* m = x + 3 * static_cast<int64_t>(kc);
-            c0 = m[0];
-            c1 = m[1];
-            c2 = m[2];
-          }
+          f.kc = next;
+          if (f.kc >= 0) load_pixel(x, f.kc, f.c);
         }
       }
     }
+  }
+
+  template <class T>
+  __device__ __forceinline__ void resolve(const double* __restrict__ x, T (&v)[S]) const {
+    Pixels f;
+    fetch(x, f);
+    finish(x, f, v);
   }
 };
 

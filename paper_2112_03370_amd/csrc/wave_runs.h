@@ -25,16 +25,21 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Lanes below this one that are set in a wavefront mask.
+__device__ __forceinline__ int lanes_below(unsigned long long m) {
+  return static_cast<int>(__builtin_amdgcn_mbcnt_hi(
+      static_cast<unsigned>(m >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(m), 0u)));
+}
+
 // Exclusive prefix sum over the wavefront of a small per-lane count c < 2^BITS.
 template <int BITS>
-__device__ __forceinline__ int wave_exclusive_count(int c, int lane, int& total) {
-  const unsigned long long below = (1ull << lane) - 1ull;
+__device__ __forceinline__ int wave_exclusive_count(int c, int& total) {
   int before = 0;
   total = 0;
 #pragma unroll
   for (int b = 0; b < BITS; ++b) {
     const unsigned long long m = __ballot((c >> b) & 1);
-    before += __popcll(m & below) << b;
+    before += lanes_below(m) << b;
     total += __popcll(m) << b;
   }
   return before;
@@ -75,8 +80,8 @@ __device__ __forceinline__ void wave_merge_runs_listed_of(const int (&key)[SPL],
       last_keyed = key[j] >= 0 ? 1 : 0;
     }
   }
-  int r_in = 0;
-  const int in_base = wave_exclusive_count<3>(n_in, lane, r_in);
+  int r_in = 0, in_base = 0;
+  if (__any(n_in > 0)) in_base = wave_exclusive_count<3>(n_in, r_in);  // wavefront-uniform
   wave_lds_sync();  // the previous call's listed runs have been read before slots are reused
 
   auto put = [&](int slot, int k, const double (&w)[NV]) {
@@ -161,12 +166,12 @@ __device__ __forceinline__ void wave_merge_runs_listed_of(const int (&key)[SPL],
   const bool ends = (lane == 63) || next_start;
   const bool has_tail =
       ends && tk >= 0 && !((lane < 63) && !next_single && next_hk == tk);
-  const int n_ht = (has_head ? 1 : 0) + (has_tail ? 1 : 0);
   const int head_key = hk, tail_key = tk;
-  int r_ht = 0;
-  const int s_head = r_in + wave_exclusive_count<2>(n_ht, lane, r_ht);
+  // slots in lane order, a lane's first run before its last: neighbouring pixels stay together
+  const unsigned long long m_head = __ballot(has_head), m_tail = __ballot(has_tail);
+  const int s_head = r_in + lanes_below(m_head) + lanes_below(m_tail);
   const int s_tail = s_head + (has_head ? 1 : 0);
-  const int total = r_in + r_ht;
+  const int total = r_in + __popcll(m_head) + __popcll(m_tail);
 
   // ---- list heads and tails, flush one value of one listed run per lane --------------------
   for (int first = 0;;) {
