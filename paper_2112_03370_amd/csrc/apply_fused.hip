@@ -149,17 +149,9 @@ __global__ __launch_bounds__(FftCfg<LOG>::T) void k_apply_fused(
       }
     }
     lane.bridge_flags(u);
-    double v[SS][3];
-#pragma unroll
-    for (int j = 0; j < SS; ++j) {
-      const double tv = u[j];
-      v[j][0] = tv;
-      v[j][1] = static_cast<double>(lane.qq[j]) * tv;
-      v[j][2] = static_cast<double>(lane.uu[j]) * tv;
-    }
     int at = pad(((lam + base + 64 * SS * wave) >> 1) + 1);
     if constexpr (T == 64) at = min(at, kBuf - kListPoints);
-    wave_merge_runs_listed<SS, 3, kListed>(lane.kk, v, flush, buf + at);
+    wave_point_runs<SS, kListed>(lane.kk, lane.qq, lane.uu, u, flush, buf + at);
   }
 }
 

@@ -524,16 +524,8 @@ __global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(4))) void k_
 #pragma unroll
     for (int j = 0; j < kLane; ++j) u[j] = lds[i0 + j];
     lane.bridge_flags(u);
-    double val[kLane][3];
-#pragma unroll
-    for (int j = 0; j < kLane; ++j) {
-      const double tv = u[j];
-      val[j][0] = tv;
-      val[j][1] = static_cast<double>(lane.qq[j]) * tv;
-      val[j][2] = static_cast<double>(lane.uu[j]) * tv;
-    }
-    wave_merge_runs_listed<kLane, 3, kListed>(lane.kk, val, flush,
-                                              lds + base + 64 * kLane * wave);
+    wave_point_runs<kLane, kListed>(lane.kk, lane.qq, lane.uu, u, flush,
+                                    lds + base + 64 * kLane * wave);
   }
 }
 

@@ -639,15 +639,8 @@ __global__ __launch_bounds__(XFused<M>::T) void k_x_fused(
         u[2 * q + 1] = odd_first ? even : odd;
       }
       lane.bridge_flags(u);
-      double vv[8][3];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        vv[j][0] = u[j];
-        vv[j][1] = static_cast<double>(lane.qq[j]) * u[j];
-        vv[j][2] = static_cast<double>(lane.uu[j]) * u[j];
-      }
-      wave_merge_runs_listed<8, 3, kXListed>(lane.kk, vv, AtomicFlush{y},
-                                             sh + kOdd + xpad((g - 2 * first) >> 1));
+      wave_point_runs<8, kXListed>(lane.kk, lane.qq, lane.uu, u, AtomicFlush{y},
+                                   sh + kOdd + xpad((g - 2 * first) >> 1));
     }
     if (kWide && h == 0) __syncthreads();
   }

@@ -217,7 +217,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_t
   auto drain = [&](LanePointing<kLane, false>& lane, double (&t)[kLane], int i) {
     subtract<NP>(t, midpoint(i), dx, w, c);
     lane.bridge_flags(t);
-    wave_merge_runs_listed_of<kLane, 3, kListed>(
+    wave_merge_runs_of<kLane, 3, kListed>(
         lane.kk,
         [&](int j, int q) {
           return q == 0 ? t[j] : static_cast<double>(q == 1 ? lane.qq[j] : lane.uu[j]) * t[j];

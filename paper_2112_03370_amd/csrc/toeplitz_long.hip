@@ -249,15 +249,7 @@ __device__ __forceinline__ void drain_lane(const LongArgs& a, const SegmentStrea
     LanePointing<kLane, false> lane;
     lane.load(win, a.lam + o, a.lam, a.lam + c.out_len);
     lane.bridge_flags(v);
-    double val[kLane][3];
-#pragma unroll
-    for (int j = 0; j < kLane; ++j) {
-      const double tv = v[j];
-      val[j][0] = tv;
-      val[j][1] = static_cast<double>(lane.qq[j]) * tv;
-      val[j][2] = static_cast<double>(lane.uu[j]) * tv;
-    }
-    wave_merge_runs_listed<kLane, 3, kListed>(lane.kk, val, AtomicFlush{y}, list);
+    wave_point_runs<kLane, kListed>(lane.kk, lane.qq, lane.uu, v, AtomicFlush{y}, list);
   }
 }
 

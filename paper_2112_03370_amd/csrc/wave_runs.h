@@ -60,17 +60,36 @@ constexpr int run_list_bytes() {
 // several rounds of nearly idle atomic instructions per wavefront; and where the runs fall on
 // different cache lines (pixel ids far apart along the scan), a run costs one memory-side atomic
 // request instead of NV.  More than CAP runs are listed and flushed CAP at a time.
-// The values come from a function v(sample, component), for callers short of registers.
-template <int SPL, int NV, int CAP, class Value, class Flush>
-__device__ __forceinline__ void wave_merge_runs_listed_of(const int (&key)[SPL], const Value& v,
-                                                          const Flush& flush, void* list) {
-  static_assert(SPL >= 2 && SPL <= 9, "inner-run counts must fit the 3-bit wavefront prefix");
-  const int lane = static_cast<int>(threadIdx.x & 63u);
-  int* skey = static_cast<int*>(list);
-  double* sval = reinterpret_cast<double*>(skey + CAP);
+template <int NV, int CAP>
+struct RunList {
   static_assert(CAP % 2 == 0, "8-byte aligned values");
+  int* key;
+  double* val;
+  __device__ __forceinline__ explicit RunList(void* list)
+      : key(static_cast<int*>(list)), val(reinterpret_cast<double*>(key + CAP)) {}
+  // Lists a run whose number lies in [0, CAP) of the current pass.
+  __device__ __forceinline__ void put(int slot, int k, const double (&w)[NV]) const {
+    if (static_cast<unsigned>(slot) < static_cast<unsigned>(CAP)) {
+      key[slot] = k;
+#pragma unroll
+      for (int c = 0; c < NV; ++c) val[slot * NV + c] = w[c];
+    }
+  }
+};
 
-  // ---- runs inside the lane: count, then list ---------------------------------------------
+// A lane's runs: the first (when it holds more than one; hk = -1 otherwise or when it is skipped)
+// and the last; those between are listed.
+template <int NV>
+struct LaneRuns {
+  double head[NV], acc[NV];
+  int hk, tk;
+  bool single;
+};
+
+// Runs that begin and end inside a lane, whose first sample is not the lane's first.
+template <int SPL>
+__device__ __forceinline__ int inner_runs(const int (&key)[SPL]) {
+  static_assert(SPL >= 2 && SPL <= 9, "inner-run counts must fit the 3-bit wavefront prefix");
   // A run starting at a key change j > 0 lies inside the lane when another change follows.
   int n_in = 0, last_keyed = 0;
 #pragma unroll
@@ -80,61 +99,61 @@ __device__ __forceinline__ void wave_merge_runs_listed_of(const int (&key)[SPL],
       last_keyed = key[j] >= 0 ? 1 : 0;
     }
   }
-  int r_in = 0, in_base = 0;
-  if (__any(n_in > 0)) in_base = wave_exclusive_count<3>(n_in, r_in);  // wavefront-uniform
-  wave_lds_sync();  // the previous call's listed runs have been read before slots are reused
+  return n_in;
+}
 
-  auto put = [&](int slot, int k, const double (&w)[NV]) {
-    skey[slot] = k;
+// The lane's walk over values v(sample, component): its first and last runs, and its inner runs,
+// of which the wavefront's numbers start at `slot`, into the list.
+template <int SPL, int NV, int CAP, class Value>
+__device__ __forceinline__ void walk_runs(const int (&key)[SPL], const Value& v, int slot,
+                                          const RunList<NV, CAP>& list, LaneRuns<NV>& r) {
 #pragma unroll
-    for (int c = 0; c < NV; ++c) sval[slot * NV + c] = w[c];
-  };
-  // The lane's walk: lists its inner runs whose slots lie in [first, first + CAP) and leaves its
-  // first run (when it holds more than one) in head and its last in acc.
-  double acc[NV];
-  double head[NV];
-  int hk = -1, tk = -1;
-  bool single = true;
-  auto walk = [&](int first) {
+  for (int c = 0; c < NV; ++c) {
+    r.acc[c] = v(0, c);
+    r.head[c] = 0.0;
+  }
+  int cur = key[0];
+  r.hk = -1;
+  r.single = true;
 #pragma unroll
-    for (int c = 0; c < NV; ++c) {
-      acc[c] = v(0, c);
-      head[c] = 0.0;
-    }
-    int cur = key[0];
-    hk = -1;
-    single = true;
-    int slot = in_base - first;
+  for (int j = 1; j < SPL; ++j) {
+    if (key[j] != cur) {
+      if (r.single) {
+        r.hk = cur;
 #pragma unroll
-    for (int j = 1; j < SPL; ++j) {
-      if (key[j] != cur) {
-        if (single) {
-          hk = cur;
-#pragma unroll
-          for (int c = 0; c < NV; ++c) head[c] = acc[c];
-          single = false;
-        } else if (cur >= 0) {
-          if (static_cast<unsigned>(slot) < static_cast<unsigned>(CAP)) put(slot, cur, acc);
-          ++slot;
-        }
-        cur = key[j];
-#pragma unroll
-        for (int c = 0; c < NV; ++c) acc[c] = v(j, c);
-      } else {
-#pragma unroll
-        for (int c = 0; c < NV; ++c) acc[c] += v(j, c);
+        for (int c = 0; c < NV; ++c) r.head[c] = r.acc[c];
+        r.single = false;
+      } else if (cur >= 0) {
+        list.put(slot, cur, r.acc);
+        ++slot;
       }
+      cur = key[j];
+#pragma unroll
+      for (int c = 0; c < NV; ++c) r.acc[c] = v(j, c);
+    } else {
+#pragma unroll
+      for (int c = 0; c < NV; ++c) r.acc[c] += v(j, c);
     }
-    tk = cur;
-  };
-  walk(0);
+  }
+  r.tk = cur;
+}
+
+// Joins the lanes' runs and flushes every run of the wavefront; the first r_in of its list are
+// inner runs, listed already as far as they fit, and again(first) lists those from `first` on.
+template <int NV, int CAP, class Again, class Flush>
+__device__ __forceinline__ void join_and_flush(const LaneRuns<NV>& r, int r_in,
+                                               const RunList<NV, CAP>& list, const Again& again,
+                                               const Flush& flush) {
+  const int lane = static_cast<int>(threadIdx.x & 63u);
+  const int hk = r.hk, tk = r.tk;
+  const bool single = r.single;
 
   // ---- segmented inclusive scan of the lane tails ------------------------------------------
   const int prev_tk = __shfl_up(tk, 1);
   const bool start = (lane == 0) || !single || (prev_tk != tk);
   double S[NV];
 #pragma unroll
-  for (int c = 0; c < NV; ++c) S[c] = acc[c];
+  for (int c = 0; c < NV; ++c) S[c] = r.acc[c];
   int f = start ? 1 : 0;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
@@ -162,11 +181,10 @@ __device__ __forceinline__ void wave_merge_runs_listed_of(const int (&key)[SPL],
   double H[NV];
 #pragma unroll
   for (int c = 0; c < NV; ++c)
-    H[c] = has_head && lane > 0 && prev_tk == hk ? head[c] + prevS[c] : head[c];
+    H[c] = has_head && lane > 0 && prev_tk == hk ? r.head[c] + prevS[c] : r.head[c];
   const bool ends = (lane == 63) || next_start;
   const bool has_tail =
       ends && tk >= 0 && !((lane < 63) && !next_single && next_hk == tk);
-  const int head_key = hk, tail_key = tk;
   // slots in lane order, a lane's first run before its last: neighbouring pixels stay together
   const unsigned long long m_head = __ballot(has_head), m_tail = __ballot(has_tail);
   const int s_head = r_in + lanes_below(m_head) + lanes_below(m_tail);
@@ -175,31 +193,106 @@ __device__ __forceinline__ void wave_merge_runs_listed_of(const int (&key)[SPL],
 
   // ---- list heads and tails, flush one value of one listed run per lane --------------------
   for (int first = 0;;) {
-    if (has_head && static_cast<unsigned>(s_head - first) < static_cast<unsigned>(CAP))
-      put(s_head - first, head_key, H);
-    if (has_tail && static_cast<unsigned>(s_tail - first) < static_cast<unsigned>(CAP))
-      put(s_tail - first, tail_key, S);
+    if (has_head) list.put(s_head - first, hk, H);
+    if (has_tail) list.put(s_tail - first, tk, S);
     wave_lds_sync();  // runs listed by other lanes of the wavefront are visible
     const int n = min(total - first, CAP) * NV;
     for (int e = lane; e - lane < n; e += 64) {
       if (e < n) {
-        const int r = e / NV;
-        flush.one(skey[r], e - r * NV, sval[e]);
+        const int k = e / NV;
+        flush.one(list.key[k], e - k * NV, list.val[e]);
       }
     }
     first += CAP;
     if (first >= total) break;  // wavefront-uniform
     wave_lds_sync();  // the listed runs have been read before their slots are reused
-    if (first < r_in) walk(first);
+    if (first < r_in) again(first);
   }
+}
+
+// Runs of NV values given by v(sample, component).
+template <int SPL, int NV, int CAP, class Value, class Flush>
+__device__ __forceinline__ void wave_merge_runs_of(const int (&key)[SPL], const Value& v,
+                                                   const Flush& flush, void* at) {
+  const RunList<NV, CAP> list(at);
+  const int n_in = inner_runs(key);
+  int r_in = 0, in_base = 0;
+  if (__any(n_in > 0)) in_base = wave_exclusive_count<3>(n_in, r_in);  // wavefront-uniform
+  wave_lds_sync();  // the previous call's listed runs have been read before slots are reused
+  LaneRuns<NV> r;
+  walk_runs(key, v, in_base, list, r);
+  join_and_flush(
+      r, r_in, list,
+      [&](int first) {
+        LaneRuns<NV> unused;
+        walk_runs(key, v, in_base - first, list, unused);
+      },
+      flush);
 }
 
 template <int SPL, int NV, int CAP, class Flush>
 __device__ __forceinline__ void wave_merge_runs_listed(const int (&key)[SPL],
                                                        const double (&v)[SPL][NV],
-                                                       const Flush& flush, void* list) {
-  wave_merge_runs_listed_of<SPL, NV, CAP>(
-      key, [&](int j, int c) { return v[j][c]; }, flush, list);
+                                                       const Flush& flush, void* at) {
+  wave_merge_runs_of<SPL, NV, CAP>(
+      key, [&](int j, int c) { return v[j][c]; }, flush, at);
+}
+
+// The pointing sums P^T: runs of u, q u and w u.
+//
+// Where no lane of the wavefront sees more than two pixels (pixels visited for at least SPL
+// samples), a lane's two sums are formed without branches: each sample counts in one of them and
+// as a zero in the other.  The walk executes both sides of its branch at nearly every sample, since
+// some lane of 64 changes pixel there, with the products formed beforehand: about twice the
+// instructions, in kernels that are bound by the issue of vector instructions.
+template <int SPL, int CAP, class T, class Flush>
+__device__ __forceinline__ void wave_point_runs(const int (&key)[SPL], const float (&q)[SPL],
+                                                const float (&w)[SPL], const T (&u)[SPL],
+                                                const Flush& flush, void* at) {
+  const RunList<3, CAP> list(at);
+  int changes = 0;
+#pragma unroll
+  for (int j = 1; j < SPL; ++j) changes += key[j] != key[j - 1] ? 1 : 0;
+  wave_lds_sync();  // the previous call's listed runs have been read before slots are reused
+  const auto value = [&](int j, int c) {
+    const double t = static_cast<double>(u[j]);
+    return c == 0 ? t : static_cast<double>(c == 1 ? q[j] : w[j]) * t;
+  };
+  int r_in = 0, in_base = 0;
+  LaneRuns<3> r;
+  if (!__any(changes > 1)) {  // wavefront-uniform
+    r.single = changes == 0;
+    r.hk = r.single ? -1 : key[0];
+    r.tk = key[SPL - 1];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) r.head[c] = r.acc[c] = 0.0;
+#pragma unroll
+    for (int j = 0; j < SPL; ++j) {
+      const double qd = static_cast<double>(q[j]), wd = static_cast<double>(w[j]);
+      const bool last = j == SPL - 1 || key[j] == r.tk;
+      const double tail = static_cast<double>(last ? u[j] : T(0));
+      r.acc[0] += tail;
+      r.acc[1] = fma(qd, tail, r.acc[1]);
+      r.acc[2] = fma(wd, tail, r.acc[2]);
+      if (j < SPL - 1) {
+        const double head = static_cast<double>(last ? T(0) : u[j]);
+        r.head[0] += head;
+        r.head[1] = fma(qd, head, r.head[1]);
+        r.head[2] = fma(wd, head, r.head[2]);
+      }
+    }
+  } else {
+    const int n_in = inner_runs(key);
+    in_base = wave_exclusive_count<3>(n_in, r_in);
+    walk_runs(key, value, in_base, list, r);
+  }
+  join_and_flush(
+      r, r_in, list,
+      [&](int first) {
+        LaneRuns<3> unused;
+        walk_runs(key, value, in_base - first, list, unused);
+      },
+      flush);
 }
 
 }  // namespace mm
