@@ -60,11 +60,11 @@ KERNEL_SOURCES = {
     "apply_fused": ("apply_fused.hip", "fft_lds.h", "segment_io.h", "wave_runs.h"),
     "apply_reg": ("apply_reg.hip", "fft_lds.h", "segment_io.h", "wave_runs.h"),
     "apply_long": ("toeplitz_long.hip", "fft_lds.h", "segment_io.h", "wave_runs.h"),
-    "toeplitz": ("toeplitz.hip", "fft_lds.h"),
-    "toeplitz_long": ("toeplitz_long.hip", "fft_lds.h"),
-    "unpoint": ("pointing.hip",),
-    "point": ("pointing.hip", "wave_runs.h"),
-    "template_apply": ("templates.hip", "wave_runs.h"),
+    "toeplitz": ("toeplitz.hip", "apply_reg.hip", "fft_lds.h", "segment_io.h"),
+    "toeplitz_long": ("toeplitz_long.hip", "fft_lds.h", "segment_io.h"),
+    "unpoint": ("pointing.hip", "segment_io.h"),
+    "point": ("pointing.hip", "segment_io.h", "wave_runs.h"),
+    "template_apply": ("templates.hip", "segment_io.h", "wave_runs.h"),
 }
 
 

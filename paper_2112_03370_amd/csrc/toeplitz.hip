@@ -11,7 +11,9 @@
 // coarse[m >> 7] * fine[m & 127]) computed in FP64 on the host.  The symbol is precomputed per
 // band at plan time with the 1/(2N) normalisation folded in.
 //
-// Short bands take the direct product (direct.hip).
+// Segments of 2^15 samples with at most 2^14 outputs take the register-resident transform
+// (apply_reg.hip), short bands the direct product (direct.hip), segments of 2^16 and 2^17 the
+// four-step one (toeplitz_long.hip).
 #include "fft_lds.h"
 #include "mm_internal.h"
 #include "segment_io.h"

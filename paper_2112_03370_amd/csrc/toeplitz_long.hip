@@ -35,10 +35,12 @@
 //     lambda halos of neighbouring windows are fetched together.
 //   * Global accesses are wavefront-contiguous: 256 bytes per tile row piece, 8 samples per
 //     lane in the fills and drains (64-sample row pieces).
-// Measured on the satellite-sized workload (2^28 samples, N = 2^17): one fused product takes
-// 5.4 ms, against 7.1 ms for the three kernels (gather, four-step product, scatter) with FP32
-// time-domain vectors in HBM; of it about 1.9 ms is the FP64 atomic scatter, 1.1 ms the
-// gather and 0.9 ms the tile passes.
+// Measured on a satellite scan of 2^27 samples, N = 2^17: one fused product takes 2.14 ms, against
+// 2.31 ms for the three kernels (gather 0.43, four-step product 1.36, scatter 0.53) with FP32
+// time-domain vectors in HBM.  The tile's four passes move 4.2 GB, at 4.3 TB/s with the samples:
+// they bound the plain product, and with the gather's pixel loads and the atomics the fused one.
+// (Second-pass twiddles from a table of their own: 2 % less, other rounding.  Two fill rounds in
+// flight: 38 spilled registers, 2.81 ms.)
 #include "fft_lds.h"
 #include "mm_internal.h"
 #include "segment_io.h"
