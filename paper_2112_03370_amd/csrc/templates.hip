@@ -30,7 +30,7 @@
 // t in registers instead of LDS: 889 us (spills).  One workgroup size for all baselines
 // left the short ones with idle wavefronts: 64 x 2^19 samples, baselines of 500 (3 templates)
 // 1,147 us with 512 threads, 167 us with 64; of 600 (1 template) 834 and 159 us; of 3,000
-// 323 us and, with 256, 182 us.
+// 323 us and, with 256, 153 us.
 #include <algorithm>
 #include <cmath>
 
@@ -125,8 +125,18 @@ __device__ __forceinline__ void subtract(double (&t)[kLane], double x0, double d
   }
 }
 
+// Wavefronts per SIMD: 512 threads need four for two workgroups per CU and spill some of their
+// registers for it (25 at three templates); smaller workgroups fill a CU with three and no spills,
+// which is faster where four would spill much: 64 x 2^19 samples, 3 templates, baselines of 3,000
+// 180 -> 153 us, but 1 template, baselines of 600 154 -> 173 us.
+template <int NP, int T>
+constexpr int template_waves() {
+  return T == 512 || NP < 3 ? 4 : 3;
+}
+
 template <bool kData, int NP, int T>
-__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_template_apply(
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(template_waves<NP, T>())))
+void k_template_apply(
     const int32_t* __restrict__ lpix, const float* __restrict__ wq, const float* __restrict__ wu,
     const double* __restrict__ x, const float* __restrict__ d, const TBase* __restrict__ bases,
     const double* __restrict__ kinv, double* __restrict__ y, const int32_t* __restrict__ done) {
