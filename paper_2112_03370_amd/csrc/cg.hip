@@ -183,12 +183,10 @@ __global__ __launch_bounds__(kThreads) void k_dot_pq(const double* __restrict__ 
                                                      int nrb) {
   __shared__ double sh[kThreads / 64];
   constexpr int kBatch = 3;  // a pixel's worth of elements per thread and round
-  const int done = st->done;
   const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
-  double v = 0.0;
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; i < n;
-       i += kBatch * stride) {
-    double a[kBatch], b[kBatch];
+  int64_t i = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
+  double a[kBatch], b[kBatch];
+  auto load = [&]() {
 #pragma unroll
     for (int k = 0; k < kBatch; ++k) {
       const bool in = i + k * stride < n;
@@ -200,12 +198,21 @@ __global__ __launch_bounds__(kThreads) void k_dot_pq(const double* __restrict__ 
       pin(a[k]);
       pin(b[k]);
     }
-    if (done) return;
+  };
+  const int done = st->done;
+  load();
+  // Tested by the whole workgroup at once, also by threads without an element: the sum below has
+  // a barrier.
+  if (done) return;
+  double v = 0.0;
+  while (i < n) {
 #pragma unroll
     for (int k = 0; k < kBatch; ++k) v += a[k] * b[k];
+    i += kBatch * stride;
+    if (i < n) load();
   }
   const double s = block_sum(v, sh);
-  if (threadIdx.x == 0 && !done) partial[2 * nrb + blockIdx.x] = s;
+  if (threadIdx.x == 0) partial[2 * nrb + blockIdx.x] = s;
 }
 
 // One pixel's part of the update.

@@ -545,3 +545,18 @@ def test_satellite_long_band_pcg(gpu_lib):
     err = float(_rel(x.cpu().numpy(), res.x))
     assert info["converged"] == 1 and err <= 1e-6, (err, info, res.iterations)
     assert abs(info["iterations"] - res.iterations) <= 2
+
+
+@pytest.mark.parametrize("side", [3, 18, 40])
+def test_iterations_queued_past_convergence_change_nothing(gpu_lib, side):
+    """Iterations queued behind the converging one leave at once, on maps whose last workgroup is
+    filled in part: the same iterations and map as with a check after each (1e-9, the order of the
+    FP64 atomic additions)."""
+    prob = synth.make_raster(cfg_id=97, n_dets=2, side=side, dwell=8, lam=40)
+    plan = _plan(gpu_lib, prob)
+    d = _dev(prob.d[0])
+    want, one = plan.pcg_solve(d, tol=1e-8, check_every=1)
+    for graph in (False, True, True):
+        x, info = plan.pcg_solve(d, tol=1e-8, check_every=64, use_graph=graph)
+        assert abs(info["iterations"] - one["iterations"]) <= 1 and info["converged"] == 1
+        assert _rel(x.cpu().numpy(), want.cpu().numpy()) <= 1e-9
