@@ -11,7 +11,8 @@
 // block (their X is final).  The t x t algebra runs on the host in FP64; the tall-skinny Gram
 // products, updates and the block-Jacobi apply run in the kernels below, in FP64.  An iteration
 // meets the host once: G and H1 come back (with the outcome of the previous iteration's stop
-// tests, which the device has already applied to Z), a1 and G^+ go out.
+// tests, which the device has already applied to Z), a1 and G^+ go out; on FP64 plans the outcome
+// comes back on its own, ahead of the product.
 //
 // Block size: opts->block >= 2 fixes t; opts->block < 0 tunes it: the first column groups are
 // solved with t = 1 (8 columns, each alone by Alg. 1), 8, 16, 32 in turn (real work, not a
@@ -23,6 +24,7 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <initializer_list>
 #include <map>
 #include <mutex>
 #include <numeric>
@@ -542,6 +544,32 @@ mm_status solve_group(Plan* P, Work& Wk, const float* d, int64_t ld_d, double* x
         conv[j] = 1;
     }
   };
+  // Drops the columns that have left from the block's vectors and slot tables.
+  auto compact = [&](std::initializer_list<double*> vecs) -> mm_status {
+    const int tn = static_cast<int>(keep.size());
+    for (int i = 0; i < tn; ++i) {
+      if (keep[i] != i)
+        for (double* v : vecs)
+          MM_HIP_TRY(hipMemcpyAsync(v + i * nu, v + keep[i] * nu, sizeof(double) * nu,
+                                    hipMemcpyDeviceToDevice, s));
+      act[i] = act[keep[i]];
+      slot_of[i] = slot_of[keep[i]];
+    }
+    ta = tn;
+    act.resize(ta);
+    slot_of.resize(ta);
+    return ta > 0 ? upload_slots() : MM_OK;
+  };
+  // The stop flag gates every product but the FP64 one: there the host reads an update's outcome
+  // ahead of the next product, not with its Gram matrices, so that no column takes a product after
+  // its last update (a second read-back per iteration, against a product per column).
+  const bool gated = P->precision != MM_PRECISION_FP64 || P->lambda_max == 0;
+  auto read_outcome = [&](int k) -> mm_status {
+    MM_HIP_TRY(hipMemcpyAsync(host, ws.small, sizeof(double) * kG, hipMemcpyDeviceToHost, s));
+    MM_HIP_TRY(hipStreamSynchronize(s));
+    settle(k);
+    return MM_OK;
+  };
   std::vector<double> G, H, Gi, A;
   if (ta > 0) {
     MM_TRY(upload_slots());
@@ -549,8 +577,9 @@ mm_status solve_group(Plan* P, Work& Wk, const float* d, int64_t ld_d, double* x
   }
   int k = 0;
   while (ta > 0 && k < max_iter) {
-    // W = A Z; G = Z^T W, H1 = Z^T R.  Columns that left in the last update have Z = 0 (and rows
-    // and columns of zeros in G); with none left the product exits at once.
+    // W = A Z; G = Z^T W, H1 = Z^T R.  With the outcome of the last update still on the device,
+    // columns that left in it have Z = 0 (and rows and columns of zeros in G); with none left the
+    // product exits at once.
     MM_TRY(apply_A_multi(P, Wk, ws.Z, nu, ws.W, nu, ta, s, done));
     const int ng = launch_gram(ws.Z, ta, ws.W, ta, ws.R, ta, nu, ws.partial, s);
     launch_reduce(ws.partial, ng, 2 * ta * ta, ws.small + kG, nullptr, 0, 0, nullptr, s);
@@ -559,29 +588,15 @@ mm_status solve_group(Plan* P, Work& Wk, const float* d, int64_t ld_d, double* x
                               hipMemcpyDeviceToHost, s));
     MM_HIP_TRY(hipStreamSynchronize(s));
     const int told = ta;
-    if (k > 0) settle(k);
-    if (k > 0 && keep.empty()) {
-      ta = 0;
-      break;
-    }
-    if (k > 0 && static_cast<int>(keep.size()) < told) {
-      // compact Z, W and R to the remaining columns
-      const int tn = static_cast<int>(keep.size());
-      for (int i = 0; i < tn; ++i) {
-        if (keep[i] != i)
-          for (double* v : {ws.Z, ws.W, ws.R})
-            MM_HIP_TRY(hipMemcpyAsync(v + i * nu, v + keep[i] * nu, sizeof(double) * nu,
-                                      hipMemcpyDeviceToDevice, s));
-        act[i] = act[keep[i]];
-        slot_of[i] = slot_of[keep[i]];
+    keep.resize(ta);
+    std::iota(keep.begin(), keep.end(), 0);
+    if (k > 0 && gated) {
+      settle(k);
+      if (keep.empty()) {
+        ta = 0;
+        break;
       }
-      ta = tn;
-      act.resize(ta);
-      slot_of.resize(ta);
-      MM_TRY(upload_slots());
-    } else if (k == 0) {
-      keep.resize(ta);
-      std::iota(keep.begin(), keep.end(), 0);
+      if (static_cast<int>(keep.size()) < told) MM_TRY(compact({ws.Z, ws.W, ws.R}));
     }
     G.resize(static_cast<size_t>(ta) * ta);
     H.resize(static_cast<size_t>(ta) * ta);
@@ -611,12 +626,12 @@ mm_status solve_group(Plan* P, Work& Wk, const float* d, int64_t ld_d, double* x
                    ws.small + kAct);
     MM_HIP_TRY(hipGetLastError());
     ++k;
+    if (!gated) {
+      MM_TRY(read_outcome(k));
+      if (static_cast<int>(keep.size()) < ta) MM_TRY(compact({ws.Z, ws.R}));
+    }
   }
-  if (ta > 0) {  // stopped by max_iter: the last update's outcome
-    MM_HIP_TRY(hipMemcpyAsync(host, ws.small, sizeof(double) * kG, hipMemcpyDeviceToHost, s));
-    MM_HIP_TRY(hipStreamSynchronize(s));
-    if (k > 0) settle(k);
-  }
+  if (ta > 0 && gated) MM_TRY(read_outcome(k));  // stopped by max_iter
 
   // true residuals ||b - A x|| (W = A X, R = b)
   std::vector<double> tr(t, 0.0);

@@ -191,3 +191,36 @@ def test_block_sizes_around_the_gram_tiles(gpu_lib, t):
     _, short = plan.pcg_solve(_dev(d), tol=1e-8, block=t, max_iter=3, raise_on_error=False)
     assert [i["iterations"] for i in short] == [3] * t
     assert all(i["converged"] == 0 and 1e-8 < i["relres"] < 1.0 for i in short)
+
+
+@pytest.mark.parametrize("fft", [False, True])
+def test_fp64_columns_take_no_product_after_their_last(gpu_lib, fft):
+    """A stacked solve of an FP64 plan runs one product per column still in the block and
+    iteration: none for columns that have left, and none after the last update.  Counted by the
+    launches of the direct product (kind 1) and, on the FFT plan, of the diagonal product of the
+    samples outside every block (kind 2): one for each right-hand side (taken twice) and each
+    product."""
+    prob = synth.make_random_small(seed=9, n_samples=6007, n_pix=70, n_dets=4,
+                                   lam_max=48 if fft else 24, flag_frac=0.1, gap_frac=0.2,
+                                   dwell=5, n_rhs=5)
+    ref = O.plan_from_problem(prob)
+    plan = gpu_lib.Plan.from_problem(
+        prob, precision=gpu_lib.PRECISION_FP64,
+        toeplitz_algo=gpu_lib.TOEPLITZ_FFT if fft else gpu_lib.TOEPLITZ_DIRECT)
+    d = prob.d.copy()
+    d[2] = 100.0  # leaves the block early
+    d[3] = 0.0    # never enters it
+    plan.set_timing(True)
+    x, infos = plan.pcg_solve(_dev(d), tol=1e-8, block=5)
+    count = plan.kernel_time(2 if fft else 1)[1]
+    its = [i["iterations"] for i in infos]
+    assert fft or len(set(its)) > 2, its
+    assert count == 3 * len(d) + sum(its), (count, its)
+    plan.set_timing(True)
+    _, short = plan.pcg_solve(_dev(d), tol=1e-8, block=5, max_iter=2, raise_on_error=False)
+    assert [i["iterations"] for i in short] == [2 if j != 3 else 0 for j in range(5)]
+    assert plan.kernel_time(2 if fft else 1)[1] == 3 * len(d) + 8
+    m = x.cpu().numpy()
+    for j in (0, 1, 2, 4):
+        assert infos[j]["converged"] == 1 and infos[j]["relres"] < 1e-8
+        assert _rel(m[j], O.pcg(ref, O.rhs(ref, d[j]), tol=1e-8).x) <= 1e-6
