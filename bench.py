@@ -60,6 +60,7 @@ KERNEL_SOURCES = {
     "apply_fused": ("apply_fused.hip", "fft_lds.h", "segment_io.h", "wave_runs.h"),
     "apply_reg": ("apply_reg.hip", "fft_lds.h", "segment_io.h", "wave_runs.h"),
     "apply_long": ("toeplitz_long.hip", "fft_lds.h", "segment_io.h", "wave_runs.h"),
+    "apply_direct": ("direct.hip", "segment_io.h", "wave_runs.h"),
     "toeplitz": ("toeplitz.hip", "apply_reg.hip", "fft_lds.h", "segment_io.h"),
     "toeplitz_long": ("toeplitz_long.hip", "fft_lds.h", "segment_io.h"),
     "unpoint": ("pointing.hip", "segment_io.h"),
@@ -71,8 +72,8 @@ KERNEL_SOURCES = {
 def fused_kernel(pinfo):
     """Name of the fused product kernel a plan runs: register-resident FFT (2^15-sample
     segments with at most 2^14 outputs), persistent four-step FFT (2^16 and 2^17-sample
-    segments) or LDS-resident FFT."""
-    return {2: "apply_reg", 3: "apply_long"}.get(pinfo["fused"], "apply_fused")
+    segments), direct product (short bands) or LDS-resident FFT."""
+    return {2: "apply_reg", 3: "apply_long", 4: "apply_direct"}.get(pinfo["fused"], "apply_fused")
 
 
 def plan_flags(args):

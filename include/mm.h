@@ -127,8 +127,9 @@ typedef struct {
   const int64_t* base_len;
 } mm_geometry;
 
-/* mm_geometry.flags: MM_FLAG_UNFUSED keeps the FFT path's gather, Toeplitz product and scatter
- * as three kernels with FP32 time-domain vectors in HBM (the fused kernel is the default).
+/* mm_geometry.flags: MM_FLAG_UNFUSED keeps the gather, Toeplitz product (FFT or direct) and
+ * scatter as three kernels with FP32 time-domain vectors in HBM (the fused kernel is the default;
+ * FP64 products take it always).
  * MM_FLAG_LDS_FFT keeps fused 2^15-sample segments in the LDS-resident kernel (one workgroup
  * per CU); by default segments of that length with at most 2^14 outputs (lambda >= 2^13) use
  * the register-resident kernel, which runs two workgroups per CU. */
@@ -149,7 +150,9 @@ typedef struct {
   int32_t n_chunks;       /* overlap-save segments (FFT) or tiles (direct) per product */
   int32_t fused;          /* 1: gather, Toeplitz and scatter run as one kernel per segment
                              (LDS-resident FFT), 2: the same with the register-resident FFT,
-                             3: the same with the four-step FFT of long segments */
+                             3: the same with the four-step FFT of long segments, 4: one
+                             kernel per tile with the direct product; 0: three kernels, or
+                             diagonal weights */
   int32_t precision;      /* MM_PRECISION_* of the plan */
   int32_t n_poly;         /* template orders per baseline (0: maximum-likelihood system) */
   int64_t n_baselines;
@@ -282,8 +285,8 @@ mm_status mm_pcg_solve(const mm_plan_t* plan, const float* d, int32_t k, int64_t
  * 40 * n_kept bytes (five FP64 vectors of 3 n_kept) plus a few KB must fit: MM_ERR_INVALID
  * beyond that.  Same arguments and results as mm_pcg_solve, restricted to PCG per column
  * with block-Jacobi (opts->block 0/1, precond 0, refine 0, check_fp64 0; use_graph is
- * ignored: launches are eager) on plans whose product keeps the time domain on chip (fused
- * FFT product or diagonal weights, MM_PRECISION_MIXED, no templates); otherwise
+ * ignored: launches are eager) on plans with the fused FFT product of at most 2^15-sample
+ * segments or with diagonal weights, MM_PRECISION_MIXED and no templates; otherwise
  * MM_ERR_UNSUPPORTED.  Per-kernel timing must be off.  All calls on one GPU share its array:
  * calls are serialised per device inside the process; concurrent calls are therefore safe
  * but never overlap.  Synchronous. */

@@ -72,8 +72,8 @@ mm_status mm_pcg_solve_noalloc(const mm_plan_t* plan, const float* d, int32_t k,
       P->precision != MM_PRECISION_MIXED || P->n_poly > 0 ||
       (P->algo == MM_TOEPLITZ_FFT && long_fft_size(P->fft_n)))
     return fail(MM_ERR_UNSUPPORTED,
-                "the allocation-free solve needs a plan whose product keeps the time domain on "
-                "chip (fused FFT or diagonal weights)");
+                "the allocation-free solve needs a plan with the fused FFT product of at most "
+                "2^15-sample segments or diagonal weights, mixed precision and no templates");
   if (P->timing.enabled)
     return fail(MM_ERR_UNSUPPORTED, "per-kernel timing records events: disable it first");
   const size_t need = scratch_need(P);

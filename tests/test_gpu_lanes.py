@@ -226,3 +226,20 @@ def test_lanes_fp64_direct_product(gpu_lib, lam):
     b = plan.rhs(_dev(prob.d[0])).cpu().numpy()
     d = np.abs(np.where(prob.pix >= 0, prob.d[0], 0.0))
     assert np.linalg.norm(b - O.rhs(ref, prob.d[0])) <= 1e-12 * np.linalg.norm(O.rhs(absref, d))
+
+
+@pytest.mark.parametrize("lam", [1, 32])
+def test_direct_plans_report_their_product(gpu_lib, lam):
+    """mm_plan_info.fused of direct plans: 4 for the fused product, 0 for the three kernels, and 0
+    for diagonal weights, which take neither."""
+    prob, _ = _problem(3, lam, 0.02, n_dets=2, per_det=5003, interval=2001)
+    for flags, fused in ((0, 4), (gpu_lib.FLAG_UNFUSED, 0)):
+        plan = gpu_lib.Plan.from_problem(prob, flags=flags)
+        assert plan.info["toeplitz_algo"] == gpu_lib.TOEPLITZ_DIRECT
+        assert plan.info["fused"] == fused, plan.info
+        plan.set_timing(True)
+        plan.apply_A(_dev(np.ones((plan.n_kept, 3))))
+        # un-pointing, Toeplitz product, pointing: the launches that the flag selects
+        assert [plan.kernel_time(k)[1] for k in range(3)] == ([0, 1, 0] if fused else [1, 1, 1])
+    diag, _ = _problem(3, 0, 0.02, n_dets=2, per_det=5003, interval=2001)
+    assert gpu_lib.Plan.from_problem(diag).info["fused"] == 0
