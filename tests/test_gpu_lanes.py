@@ -243,3 +243,34 @@ def test_direct_plans_report_their_product(gpu_lib, lam):
         assert [plan.kernel_time(k)[1] for k in range(3)] == ([0, 1, 0] if fused else [1, 1, 1])
     diag, _ = _problem(3, 0, 0.02, n_dets=2, per_det=5003, interval=2001)
     assert gpu_lib.Plan.from_problem(diag).info["fused"] == 0
+
+
+@pytest.mark.parametrize("lam", [8192, 8193, 12000])
+def test_lanes_register_noise_weight_short_blocks_and_gaps(gpu_lib, lam):
+    """The register transform on blocks shorter than the band, next to samples outside every block
+    (copied by the same call) and to blocks of one and several segments at odd starts.  FP32
+    transform of 2^15 samples: relative L2 2e-6; samples outside every block exactly."""
+    import torch
+    n = 90_007
+    start = np.array([3, 5_100, 46_007, 46_010, 89_000], np.int64)
+    length = np.array([5_001, 40_011, 1, 30_000, 1_006], np.int64)
+    prob, _ = _problem(3, lam, 0.0, n_dets=1, per_det=n, interval=n)
+    prob = dataclasses.replace(prob, blk_start=start, blk_len=length,
+                               blk_band=np.zeros(len(start), np.int32))
+    ref = O.plan_from_problem(prob)
+    plan = gpu_lib.Plan.from_problem(prob, toeplitz_algo=gpu_lib.TOEPLITZ_FFT, fft_size=32768)
+    assert plan.info["fused"] == 2, plan.info
+    outside = np.ones(n, bool)
+    for s, m in zip(start, length):
+        outside[s:s + m] = False
+    t = np.random.default_rng(lam).standard_normal(n + 1).astype(np.float32)
+    for shift in (0, 1):
+        out = torch.full((n + 4,), 7.0, device="cuda")
+        ts = t[shift:shift + n]
+        u = plan.noise_weight(_dev(t)[shift:shift + n], u=out[1 + shift:1 + shift + n]).cpu().numpy()
+        want = O.noise_weight(ts.astype(np.float64), ref)
+        assert np.array_equal(u[outside], ts[outside])
+        for s, m in zip(start, length):
+            assert _rel(u[s:s + m], want[s:s + m]) <= 2e-6
+        rest = torch.cat([out[:1 + shift], out[1 + shift + n:]]).cpu().numpy()
+        assert np.all(rest == 7.0)
