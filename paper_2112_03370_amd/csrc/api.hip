@@ -91,17 +91,6 @@ mm_status guarded(F&& f) {
   }
 }
 
-// The wait that makes the products of FP64 plans synchronous: here and once per call, not in the
-// product, so that it holds for every segment length and costs the solves nothing.  Nothing waits
-// while the stream is being captured.
-mm_status finish_fp64(const Plan* P, hipStream_t s) {
-  if (P->precision != MM_PRECISION_FP64) return MM_OK;
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  MM_HIP_TRY(hipStreamIsCapturing(s, &capture));
-  if (capture == hipStreamCaptureStatusNone) MM_HIP_TRY(hipStreamSynchronize(s));
-  return MM_OK;
-}
-
 mm_status drain_timing(Plan* P) {
   for (int k = 0; k < K_NKINDS; ++k) {
     auto& v = P->timing.pending[k];
@@ -212,12 +201,10 @@ mm_status mm_rhs(const mm_plan_t* plan, const float* d, int32_t k, int64_t ld_d,
   if (k > 1 && ld_d < P->n_samples) return fail(MM_ERR_INVALID, "ld_d < n_samples");
   if (k > 0 && ((P->n_samples > 0 && !d) || (P->n_kept > 0 && !b))) return fail(MM_ERR_INVALID, "NULL vector");
   hipStream_t s = as_stream(stream);
+  std::lock_guard<std::mutex> lock(P->mu);
   return guarded([&]() -> mm_status {
-    {
-      std::lock_guard<std::mutex> lock(P->mu);
-      for (int32_t j = 0; j < k; ++j) MM_TRY(compute_rhs(P, P->work, d + j * ld_d, b + j * 3 * P->n_kept, s));
-    }
-    return finish_fp64(P, s);
+    for (int32_t j = 0; j < k; ++j) MM_TRY(compute_rhs(P, P->work, d + j * ld_d, b + j * 3 * P->n_kept, s));
+    return MM_OK;
   });
 }
 
@@ -229,12 +216,9 @@ mm_status mm_apply_A(const mm_plan_t* plan, const double* x, double* y, int32_t 
   if (k > 0 && P->n_kept > 0 && (!x || !y)) return fail(MM_ERR_INVALID, "NULL vector");
   if (k > 0 && P->n_kept > 0 && x == y) return fail(MM_ERR_INVALID, "x and y must not alias");
   hipStream_t s = as_stream(stream);
+  std::lock_guard<std::mutex> lock(P->mu);
   return guarded([&]() -> mm_status {
-    {
-      std::lock_guard<std::mutex> lock(P->mu);
-      MM_TRY(apply_A_multi(P, P->work, x, 3 * P->n_kept, y, 3 * P->n_kept, k, s));
-    }
-    return finish_fp64(P, s);
+    return apply_A_multi(P, P->work, x, 3 * P->n_kept, y, 3 * P->n_kept, k, s);
   });
 }
 

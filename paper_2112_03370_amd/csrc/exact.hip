@@ -778,6 +778,7 @@ mm_status exact_product(Plan* P, const double* x, const float* d, double* y, hip
       default: MM_TRY(launch_fused_m<14>(P, x, d, y, s)); break;
     }
     if (P->n_id_tiles > 0) MM_TRY(launch_diag_tiles(P, P->id_tiles, P->n_id_tiles, x, d, y, nullptr, s));
+    if (wide_segments(P)) MM_HIP_TRY(hipStreamSynchronize(s));  // documented as synchronous
     return MM_OK;
   }
   if (P->algo == MM_TOEPLITZ_FFT) {

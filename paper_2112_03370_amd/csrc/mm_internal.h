@@ -356,8 +356,7 @@ mm_status deflation_apply(Plan* P, const double* r, double* z, double* p, double
 mm_status launch_band_symbol64(Plan* P, double* spec64, hipStream_t s);
 // FP64 product (exact.hip): y = P^T N^-1 P x (d == nullptr), y = P^T N^-1 d (x == nullptr) or,
 // with both, y = P^T N^-1 (d - P x) = b - A x (plans with exact_residual_supported only), every
-// step in FP64, y overwritten.  Asynchronous, except for the call that builds the plan's FP64
-// tables and for segments beyond 2^15 samples, whose staging tiles are allocated per call.
+// step in FP64, y overwritten.  Synchronous (staging tiles are allocated per call).
 mm_status exact_product(Plan* P, const double* x, const float* d, double* y, hipStream_t s);
 bool exact_residual_supported(const Plan* P);
 

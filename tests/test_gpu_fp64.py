@@ -151,49 +151,3 @@ def test_refinement_reaches_fp64_tolerance(gpu_lib, name):
     print(f"{name}: {info['iterations']} + {info['inner_iterations']} inner iterations, "
           f"{info['refine_steps']} step(s), FP64 true {info['true_relres64']:.2e} "
           f"(oracle {r:.2e})", flush=True)
-
-
-SYNC_CASES = ["direct_lam24", "diag", "fft_2e11", "fft_2e13", "fft_2e15", "fft_2e17"]
-
-
-@pytest.mark.parametrize("name", SYNC_CASES)
-def test_fp64_calls_return_with_their_result(gpu_lib, name):
-    """b = P^T N^-1 d and A x are synchronous on FP64 plans, whatever the band's length and the
-    product it selects: the stream, busy when the call is made, is idle when it returns."""
-    import torch
-    prob, ref, kw = case(name)
-    plan = gpu_lib.Plan.from_problem(prob, precision=gpu_lib.PRECISION_FP64, **kw)
-    x = _dev(np.random.default_rng(3).standard_normal((2, ref.n_kept, 3)))
-    d = _dev(prob.d[0])
-    s = torch.cuda.Stream()
-    s.wait_stream(torch.cuda.current_stream())
-    with torch.cuda.stream(s):
-        plan.apply_A(x)  # the tables of the first product are built
-        for call in (lambda: plan.apply_A(x), lambda: plan.rhs(d)):
-            torch.cuda._sleep(20_000_000)
-            assert not s.query()
-            call()
-            assert s.query()
-
-
-@pytest.mark.parametrize("name", ["direct_lam24", "fft_2e13", "fft_2e15"])
-def test_fp64_product_in_a_captured_graph(gpu_lib, name):
-    """A captured FP64 product does not wait for the stream; its replays follow the contents of
-    its input."""
-    import torch
-    prob, ref, kw = case(name)
-    plan = gpu_lib.Plan.from_problem(prob, precision=gpu_lib.PRECISION_FP64, **kw)
-    rng = np.random.default_rng(4)
-    xs = [_dev(rng.standard_normal((ref.n_kept, 3))) for _ in range(3)]
-    x, y = xs[0].clone(), torch.empty_like(xs[0])
-    want = [plan.apply_A(v) for v in xs]
-    torch.cuda.synchronize()
-    g = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(g):
-        plan.apply_A(x, y=y)
-    for v, w in zip(xs + xs, want + want):
-        x.copy_(v)
-        g.replay()
-        torch.cuda.synchronize()
-        assert float((y - w).norm() / w.norm()) <= 1e-12
-        assert torch.equal(x, v)
