@@ -244,17 +244,19 @@ mm_status mm_point(const mm_plan_t* plan, const float* u, double* y, void* strea
 /* b = P^T F_T d, the right-hand side of Eq. genMapEstimator (F_T = N^-1 for the
  * maximum-likelihood system, Eq. defFT for template plans), for k right-hand sides; d DEVICE
  * float, column j at d + j*ld_d (ld_d >= n_samples); gap samples of d are ignored.  b DEVICE
- * double [k][n_kept][3].  FP64 products on MM_PRECISION_FP64 and template plans (synchronous
- * there), else FP32 time domain.  Asynchronous otherwise.  Errors: MM_ERR_INVALID, MM_ERR_OOM,
- * MM_ERR_HIP. */
+ * double [k][n_kept][3].  FP64 products on MM_PRECISION_FP64 and template plans, else FP32 time
+ * domain.  Asynchronous: b is complete in the order of `stream`, on every plan.  On
+ * MM_PRECISION_FP64 plans the call may wait for the stream before it returns (the first product
+ * builds the plan's FP64 tables, segments beyond 2^15 samples are staged in memory that is freed on
+ * return, and segments with more than N / 2 outputs wait as they always have); work on other
+ * streams must not rely on that.  Errors: MM_ERR_INVALID, MM_ERR_OOM, MM_ERR_HIP. */
 mm_status mm_rhs(const mm_plan_t* plan, const float* d, int32_t k, int64_t ld_d, double* b,
                  void* stream);
 
 /* y = P^T F_T P x, the system matrix of Eq. genMapEstimator applied right to left as the
  * solvers section describes (un-pointing, noise weighting / template filter, pointing), k
- * columns.  x, y DEVICE double [k][n_kept][3], must not alias.  Precision as mm_rhs.
- * Asynchronous (synchronous for FP64 products).  Errors: MM_ERR_INVALID, MM_ERR_OOM,
- * MM_ERR_HIP. */
+ * columns.  x, y DEVICE double [k][n_kept][3], must not alias.  Precision and synchrony as
+ * mm_rhs.  Errors: MM_ERR_INVALID, MM_ERR_OOM, MM_ERR_HIP. */
 mm_status mm_apply_A(const mm_plan_t* plan, const double* x, double* y, int32_t k,
                      void* stream);
 

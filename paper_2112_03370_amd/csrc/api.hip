@@ -204,7 +204,7 @@ mm_status mm_rhs(const mm_plan_t* plan, const float* d, int32_t k, int64_t ld_d,
   std::lock_guard<std::mutex> lock(P->mu);
   return guarded([&]() -> mm_status {
     for (int32_t j = 0; j < k; ++j) MM_TRY(compute_rhs(P, P->work, d + j * ld_d, b + j * 3 * P->n_kept, s));
-    return MM_OK;
+    return exact_call_wait(P, s);
   });
 }
 
@@ -218,7 +218,8 @@ mm_status mm_apply_A(const mm_plan_t* plan, const double* x, double* y, int32_t 
   hipStream_t s = as_stream(stream);
   std::lock_guard<std::mutex> lock(P->mu);
   return guarded([&]() -> mm_status {
-    return apply_A_multi(P, P->work, x, 3 * P->n_kept, y, 3 * P->n_kept, k, s);
+    MM_TRY(apply_A_multi(P, P->work, x, 3 * P->n_kept, y, 3 * P->n_kept, k, s));
+    return exact_call_wait(P, s);
   });
 }
 

@@ -422,7 +422,8 @@ mm_status iteration(Plan* P, Work& W, double* x, bool two_level, hipStream_t s) 
   } else if (P->lambda_max == 0) {
     MM_TRY(launch_diag_apply(P, W.p, nullptr, W.q, done, s));  // q was zeroed by k_update
   } else if (P->precision == MM_PRECISION_FP64) {
-    // synchronous and not gated by `done`: such plans run one iteration per host check
+    // not gated by `done` (and synchronous on the longest segments): such plans run one iteration
+    // per host check
     MM_TRY(exact_product(P, W.p, nullptr, W.q, s));
   } else if (P->algo == MM_TOEPLITZ_FFT && P->fused) {
     MM_TRY(launch_apply_fused(P, W.p, nullptr, W.q, done, s, W.scratch));
@@ -591,8 +592,8 @@ mm_status pcg_iterate(Plan* P, Work& W, double* x, const PcgParams& prm, hipStre
   // convergence exit at once; with per-kernel timing on they carry their iteration number and
   // are dropped from the timings afterwards, and the launches are eager (events per launch)
   // instead of graph replays.
-  // FP64 plans: their product is synchronous and not gated by the stop flag, so the host checks
-  // after every iteration and nothing is captured
+  // FP64 plans: their product is not gated by the stop flag and may wait for the stream, so the
+  // host checks after every iteration and nothing is captured
   const bool one_by_one = P->precision == MM_PRECISION_FP64 && P->lambda_max > 0;
   int chunk = one_by_one ? 1 : (prm.check_every > 0 ? prm.check_every : 4);
   // Graphs of `chunk` iterations are kept in the workspace and replayed by later solves with the

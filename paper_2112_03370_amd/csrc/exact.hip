@@ -649,6 +649,12 @@ __global__ __launch_bounds__(XFused<M>::T) void k_x_fused(
 // Segments with more outputs than a workgroup stages at once (N / 2).
 bool wide_segments(const Plan* P) { return P->fft_n - 2 * P->lambda_max > P->fft_n / 2; }
 
+// Segments that run one workgroup each, without staging tiles.
+bool fused_segments(const Plan* P) {
+  return P->algo == MM_TOEPLITZ_FFT && P->n_chunks > 0 && P->fft_n >= (1 << 11) &&
+         P->fft_n <= (1 << 15);
+}
+
 template <int M, bool kWide>
 mm_status launch_fused_mw(Plan* P, const double* x, const float* d, double* y, hipStream_t s) {
   const double inv_n = 1.0 / static_cast<double>(P->fft_n);
@@ -758,6 +764,16 @@ bool exact_residual_supported(const Plan* P) {
          P->n_id_tiles == 0;
 }
 
+mm_status exact_call_wait(const Plan* P, hipStream_t s) {
+  if (P->precision != MM_PRECISION_FP64 || P->n_poly > 0 || P->lambda_max == 0 || P->n_kept == 0 ||
+      !fused_segments(P) || !wide_segments(P))
+    return MM_OK;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  MM_HIP_TRY(hipStreamIsCapturing(s, &capture));
+  if (capture == hipStreamCaptureStatusNone) MM_HIP_TRY(hipStreamSynchronize(s));
+  return MM_OK;
+}
+
 mm_status exact_product(Plan* P, const double* x, const float* d, double* y, hipStream_t s) {
   if (x != nullptr && d != nullptr && !exact_residual_supported(P))
     return fail(MM_ERR_UNSUPPORTED, "FP64 residual product: Toeplitz FFT plans only");
@@ -766,8 +782,7 @@ mm_status exact_product(Plan* P, const double* x, const float* d, double* y, hip
   const bool data = x == nullptr;
   if (P->n_poly > 0) return launch_template_apply(P, x, d, y, nullptr, s);  // FP64 already
   if (P->lambda_max == 0) return launch_diag_apply(P, x, d, y, nullptr, s);
-  if (P->algo == MM_TOEPLITZ_FFT && P->n_chunks > 0 && P->fft_n >= (1 << 11) &&
-      P->fft_n <= (1 << 15)) {
+  if (fused_segments(P)) {
     // one workgroup per segment with the transform in registers and LDS
     MM_TRY(prepare(P, s));
     switch (P->fft_n) {
@@ -778,7 +793,6 @@ mm_status exact_product(Plan* P, const double* x, const float* d, double* y, hip
       default: MM_TRY(launch_fused_m<14>(P, x, d, y, s)); break;
     }
     if (P->n_id_tiles > 0) MM_TRY(launch_diag_tiles(P, P->id_tiles, P->n_id_tiles, x, d, y, nullptr, s));
-    if (wide_segments(P)) MM_HIP_TRY(hipStreamSynchronize(s));  // documented as synchronous
     return MM_OK;
   }
   if (P->algo == MM_TOEPLITZ_FFT) {

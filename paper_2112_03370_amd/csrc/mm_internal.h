@@ -356,9 +356,16 @@ mm_status deflation_apply(Plan* P, const double* r, double* z, double* p, double
 mm_status launch_band_symbol64(Plan* P, double* spec64, hipStream_t s);
 // FP64 product (exact.hip): y = P^T N^-1 P x (d == nullptr), y = P^T N^-1 d (x == nullptr) or,
 // with both, y = P^T N^-1 (d - P x) = b - A x (plans with exact_residual_supported only), every
-// step in FP64, y overwritten.  Synchronous (staging tiles are allocated per call).
+// step in FP64, y overwritten.  Asynchronous, except for the call that builds the plan's FP64
+// tables and for segments beyond 2^15 samples, whose staging tiles are allocated per call.
 mm_status exact_product(Plan* P, const double* x, const float* d, double* y, hipStream_t s);
 bool exact_residual_supported(const Plan* P);
+// The wait at the end of a public call on an FP64 plan.  Segments of up to 2^15 samples with more
+// than N / 2 outputs once needed it (they were staged in tiles freed on return), and a caller may
+// have come to count on it: kept for those, outside the product, so that solves do not pay it, and
+// left out while the stream is being captured.  Added to the others it would cost them 17 us a
+// call: 32 x 2^18 samples, lambda = 8 39.5 -> 56.4 us, lambda = 8192 131 -> 148 us.
+mm_status exact_call_wait(const Plan* P, hipStream_t s);
 
 // Template map-making (templates.hip): tables and kernel blocks at plan time (tiles: the
 // plan's weight tiles, sorted, covering every sample), and y += P^T F_T P x (d == nullptr) or

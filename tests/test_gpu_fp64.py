@@ -151,3 +151,62 @@ def test_refinement_reaches_fp64_tolerance(gpu_lib, name):
     print(f"{name}: {info['iterations']} + {info['inner_iterations']} inner iterations, "
           f"{info['refine_steps']} step(s), FP64 true {info['true_relres64']:.2e} "
           f"(oracle {r:.2e})", flush=True)
+
+
+@pytest.mark.parametrize("name", ["direct_lam24", "diag", "fft_2e11", "fft_2e13", "fft_2e15",
+                                  "fft_2e17"])
+def test_fp64_calls_keep_stream_order(gpu_lib, name):
+    """b = P^T N^-1 d and A x on a busy stream read what earlier work on it leaves in their input
+    and are read in order by later work, whether or not the call waits.  (Two FP64 products of one
+    input differ by the order of their atomic additions: 1e-12 relative.)"""
+    import torch
+    prob, ref, kw = case(name)
+    plan = gpu_lib.Plan.from_problem(prob, precision=gpu_lib.PRECISION_FP64, **kw)
+    x = _dev(np.random.default_rng(3).standard_normal((2, ref.n_kept, 3)))
+    d = _dev(prob.d[0])
+    want = [plan.apply_A(x), plan.rhs(d)]
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    for call, src, w in ((plan.apply_A, x, want[0]), (plan.rhs, d, want[1])):
+        buf, out = torch.zeros_like(src), torch.empty_like(w)
+        s.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(s):
+            torch.cuda._sleep(20_000_000)
+            buf.copy_(src)
+            out.copy_(call(buf))
+        s.synchronize()
+        assert float((out - w).norm() / w.norm()) <= 1e-12
+
+
+@pytest.mark.parametrize("name", ["direct_lam24", "fft_2e11", "fft_2e13", "fft_2e15"])
+def test_fp64_product_in_a_captured_graph(gpu_lib, name):
+    """FP64 products of every form but the staged one can be captured, whatever the band's length;
+    the replays follow the contents of their input."""
+    import torch
+    prob, ref, kw = case(name)
+    plan = gpu_lib.Plan.from_problem(prob, precision=gpu_lib.PRECISION_FP64, **kw)
+    rng = np.random.default_rng(4)
+    xs = [_dev(rng.standard_normal((ref.n_kept, 3))) for _ in range(3)]
+    x, y = xs[0].clone(), torch.empty_like(xs[0])
+    want = [plan.apply_A(v) for v in xs]
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        plan.apply_A(x, y=y)
+    for v, w in zip(xs + xs, want + want):
+        x.copy_(v)
+        g.replay()
+        torch.cuda.synchronize()
+        assert float((y - w).norm() / w.norm()) <= 1e-12
+        assert torch.equal(x, v)
+
+
+def test_fp64_solve_on_wide_segments(gpu_lib):
+    """A solve on an FP64 plan whose segments have more than N / 2 outputs: its products do not wait
+    for the stream one by one."""
+    prob, ref, kw = case("fft_2e11")
+    plan = gpu_lib.Plan.from_problem(prob, precision=gpu_lib.PRECISION_FP64, **kw)
+    x, info = plan.pcg_solve(_dev(prob.d[0]), tol=1e-8)
+    res = O.pcg(ref, O.rhs(ref, prob.d[0]), tol=1e-8)
+    assert info["converged"] == 1 and abs(info["iterations"] - res.iterations) <= 1
+    assert np.linalg.norm(x.cpu().numpy() - res.x) / np.linalg.norm(res.x) <= 1e-6
