@@ -268,39 +268,36 @@ __global__ __launch_bounds__(kXThreads) void k_x_spectrum(
 }
 
 // ---- outputs of each segment, pointed back into the pixel domain -------------------------
+// A lane takes 4 consecutive outputs with all of its loads ahead of the first use: the kernel is
+// bound by their latency.  4 x 2^20 samples, lambda = 2^15: with each sample's loads behind a
+// branch on its pixel 29 or 40 us a launch, as the compiler came to schedule them, 17 us here.
 __global__ __launch_bounds__(kXThreads) void k_x_scatter(
     const double2* __restrict__ G, const int32_t* __restrict__ lpix,
     const float* __restrict__ wq, const float* __restrict__ wu, const Chunk* __restrict__ chunks,
     int seg0, int lam, int NC, double inv_n, double* __restrict__ y) {
   // per wavefront: the runs it completes, listed before the atomics (one value per lane)
-  constexpr int kScatterListed = 64;
+  constexpr int kScatterListed = 64, kLane = 4;
   __shared__ double list[kXThreads / 64][run_list_bytes<3, kScatterListed>() / sizeof(double)];
   const int wave = static_cast<int>(threadIdx.x >> 6);
   const Chunk c = chunks[seg0 + blockIdx.y];
-  const int64_t base = static_cast<int64_t>(blockIdx.y) * NC;
-  const int j0 = 4 * (blockIdx.x * kXThreads + threadIdx.x);
-  int key[4];
-  double v[4][3];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int j = j0 + q;
-    key[q] = -1;
-    v[q][0] = v[q][1] = v[q][2] = 0.0;
-    if (j < c.out_len) {
-      const int64_t g = c.out0 + j;
-      const int p = lpix[g];
-      if (p >= 0) {
-        const int n = lam + j;
-        const double2 gv = G[base + (n >> 1)];
-        const double u = ((n & 1) ? -gv.y : gv.x) * inv_n;
-        key[q] = p;
-        v[q][0] = u;
-        v[q][1] = static_cast<double>(wq[g]) * u;
-        v[q][2] = static_cast<double>(wu[g]) * u;
-      }
-    }
+  const double2* __restrict__ g0 = G + static_cast<int64_t>(blockIdx.y) * NC;
+  const int j = kLane * static_cast<int>(blockIdx.x * kXThreads + threadIdx.x);
+  LanePointing<kLane, false> lane;
+  lane.load(segment_streams(lpix, wq, wu, nullptr, c.out0 - lam), lam + j, lam, lam + c.out_len);
+  double u[kLane] = {0.0, 0.0, 0.0, 0.0};
+  if (j < c.out_len) {
+    // outputs j .. j + 3 are window samples lam + j on, two to a point (of the last lane's points
+    // the ones past its outputs may lie past the segment: any value does)
+    const int k = (lam + j) >> 1;
+    const double2 a = g0[k], b = g0[min(k + 1, NC - 1)], e = g0[min(k + 2, NC - 1)];
+    const bool odd = (lam & 1) != 0;
+    u[0] = (odd ? -a.y : a.x) * inv_n;
+    u[1] = (odd ? b.x : -a.y) * inv_n;
+    u[2] = (odd ? -b.y : b.x) * inv_n;
+    u[3] = (odd ? e.x : -b.y) * inv_n;
   }
-  wave_merge_runs_listed<4, 3, kScatterListed>(key, v, AtomicFlush{y}, list[wave]);
+  lane.bridge_flags(u);
+  wave_point_runs<kLane, kScatterListed>(lane.kk, lane.qq, lane.uu, u, AtomicFlush{y}, list[wave]);
 }
 
 // ---- one segment per workgroup: FP64 transform with the data in registers ----------------

@@ -274,3 +274,19 @@ def test_lanes_register_noise_weight_short_blocks_and_gaps(gpu_lib, lam):
             assert _rel(u[s:s + m], want[s:s + m]) <= 2e-6
         rest = torch.cat([out[:1 + shift], out[1 + shift + n:]]).cpu().numpy()
         assert np.all(rest == 7.0)
+
+
+@pytest.mark.parametrize("n,lam", [(65536, 1), (65536, 3), (65536, 12000), (131072, 2),
+                                   (131072, 16385)])
+def test_lanes_fp64_long_segments(gpu_lib, n, lam):
+    """The scatter of long FP64 segments: even and odd bands, and bands so short that the last
+    lane's outputs end at the segment's last point."""
+    prob, ref = _problem(3, lam, 0.02, n_dets=2, per_det=150013, interval=140011)
+    plan = gpu_lib.Plan.from_problem(prob, precision=gpu_lib.PRECISION_FP64,
+                                     toeplitz_algo=gpu_lib.TOEPLITZ_FFT, fft_size=n)
+    x = np.random.default_rng(lam).standard_normal((ref.n_kept, 3))
+    absref = dataclasses.replace(ref, bands=[np.abs(b) for b in ref.bands],
+                                 wq=np.abs(ref.wq), wu=np.abs(ref.wu))
+    got = plan.apply_A(_dev(x)).cpu().numpy()
+    scale = np.linalg.norm(O.apply_A(absref, np.abs(x)))
+    assert np.linalg.norm(got - O.apply_A(ref, x)) <= 1e-12 * scale
