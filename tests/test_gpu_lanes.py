@@ -290,3 +290,19 @@ def test_lanes_fp64_long_segments(gpu_lib, n, lam):
     got = plan.apply_A(_dev(x)).cpu().numpy()
     scale = np.linalg.norm(O.apply_A(absref, np.abs(x)))
     assert np.linalg.norm(got - O.apply_A(ref, x)) <= 1e-12 * scale
+
+
+@pytest.mark.parametrize("lam", [8192, 9001])
+def test_register_noise_weight_is_as_accurate_as_the_lds_one(gpu_lib, lam):
+    """u = N^-1 t of 2^15-sample segments by the register transform is no further from FP64 than by
+    the LDS transform.  Both errors are sums over 2^21 samples, whose ratio scatters by about 0.1 %
+    from one draw of rounding errors to another: 0.3 % is allowed for."""
+    prob, ref = _problem(8, lam, 0.0, n_dets=8, per_det=1 << 18, interval=1 << 16, side=32)
+    t = np.random.default_rng(lam).standard_normal(prob.n_samples).astype(np.float32)
+    want = O.noise_weight(t.astype(np.float64), ref, "fft")
+    err = []
+    for flags, fused in ((0, 2), (gpu_lib.FLAG_LDS_FFT, 1)):
+        plan = gpu_lib.Plan.from_problem(prob, flags=flags)
+        assert plan.info["fused"] == fused
+        err.append(_rel(plan.noise_weight(_dev(t)).cpu().numpy(), want))
+    assert err[0] <= 1.003 * err[1], err
