@@ -1018,18 +1018,20 @@ mm_status build_plan_fixed(const mm_geometry* g, hipStream_t s, Plan** out) {
                                g->blk_band[i], 0});
     }
   } else {
+    const int32_t tile = direct_tile();  // (a call into another source: not once per tile)
     for (int i : seg_order) {
       const int64_t s0 = g->blk_start[i], len = g->blk_len[i];
-      for (int64_t o = 0; o < len; o += direct_tile())
+      for (int64_t o = 0; o < len; o += tile)
         chunks.push_back(Chunk{s0 + o, s0, static_cast<int32_t>(len),
-                               static_cast<int32_t>(std::min<int64_t>(direct_tile(), len - o)),
+                               static_cast<int32_t>(std::min<int64_t>(tile, len - o)),
                                g->blk_band[i], 0});
     }
     n_id_chunks = static_cast<int64_t>(chunks.size());
     for (const Tile& t : id_tiles)
-      for (int32_t o = 0; o < t.len; o += direct_tile())
-        chunks.push_back(Chunk{t.start + o, t.start + o, std::min(direct_tile(), t.len - o),
-                               std::min(direct_tile(), t.len - o), -1, 0});
+      for (int32_t o = 0; o < t.len; o += tile) {
+        const int32_t m = std::min(tile, t.len - o);
+        chunks.push_back(Chunk{t.start + o, t.start + o, m, m, -1, 0});
+      }
     n_id_chunks = static_cast<int64_t>(chunks.size()) - n_id_chunks;
   }
   if (chunks.size() > static_cast<size_t>(INT32_MAX) || idseg.size() / 2 > static_cast<size_t>(INT32_MAX))
