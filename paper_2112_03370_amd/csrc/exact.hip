@@ -9,10 +9,10 @@
 //
 //   FFT plans      the overlap-save segments of the plan (N real samples each, N - 2 lambda
 //                  outputs).  Segments of 2^11 .. 2^15 samples run one workgroup each, the
-//                  transform in registers and LDS (k_x_fused below).  Longer ones: a batch of
-//                  segments is staged in two device tiles of N/2 complex FP64 points per segment
-//                  and transformed by radix-16 Stockham passes (a last pass of radix 2, 4 or 8),
-//                  one kernel launch per pass for the whole batch:
+//                  transform in registers and LDS (k_x_fused below).  Longer ones (2^16, 2^17):
+//                  a batch of segments is staged in two device tiles of N/2 complex FP64 points
+//                  per segment and transformed by Stockham passes of radix 256, 16 and 8, one
+//                  kernel launch per pass for the whole batch:
 //                    load      window samples t_s = x[p,0] + c_s x[p,1] + s_s x[p,2] (or the
 //                              data sample), zero outside the block, packed as complex points
 //                              z[n] = t[2n] + i t[2n+1]
@@ -700,8 +700,9 @@ mm_status run_pass(const double2* in, double2* out, const double2* tw, int NC, i
   return MM_OK;
 }
 
-// Forward DFT of every segment of the batch: radix-256 passes (two radix-16 levels each
-// through LDS), then radix-16 passes, then the remaining factor.
+// Forward DFT of every segment of the batch: radix-256 passes (two radix-16 levels each through
+// LDS), then radix-16 passes, then the remaining factor of 8 (N = 2^16: 256 x 16 x 8 points, N =
+// 2^17: 256 x 256).
 // Returns the tile holding the result (a or b).
 mm_status batch_fft(double2* a, double2* b, const double2* tw, int NC, int nseg, hipStream_t s,
                     double2** result) {
@@ -722,9 +723,8 @@ mm_status batch_fft(double2* a, double2* b, const double2* tw, int NC, int nseg,
   }
   const int rest = NC / p;
   if (rest > 1) {
-    if (rest == 2) MM_TRY(run_pass<2>(in, out, tw, NC, p, nseg, s));
-    if (rest == 4) MM_TRY(run_pass<4>(in, out, tw, NC, p, nseg, s));
-    if (rest == 8) MM_TRY(run_pass<8>(in, out, tw, NC, p, nseg, s));
+    if (rest != 8) return fail(MM_ERR_UNSUPPORTED, "FP64 transform: segment length");
+    MM_TRY(run_pass<8>(in, out, tw, NC, p, nseg, s));
     std::swap(in, out);
   }
   *result = in;
