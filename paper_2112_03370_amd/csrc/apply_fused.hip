@@ -14,7 +14,7 @@
 // only when the pixel changes, which scan runs make rare.  On small problems, with one or two
 // wavefronts to a segment and a segment to a CU, its waits count: two rounds are in flight.
 // Rates: 64 detectors x 2^19 samples on 16-sample runs, lambda = 1000 (N = 4096) 222 us; 61
-// detectors x 200,003 samples on 7-sample runs with 2 % flags, lambda = 2047, 101 us (254 us with
+// detectors x 200,003 samples on 7-sample runs with 2 % flags, lambda = 2047, 94 us (254 us with
 // scalar loads where windows start unaligned and runs flushed where they end).
 #include "fft_lds.h"
 #include "mm_internal.h"

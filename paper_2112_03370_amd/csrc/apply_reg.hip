@@ -294,7 +294,7 @@ enum RegIo { kIoApply = 0, kIoRhs = 1, kIoPlain = 2 };
 // The plain form has neither gather nor scatter: slot j of thread t is the sample pair
 // 2 (t + 512 j), so a wavefront's loads and stores are runs of 512 bytes straight between registers
 // and memory, with no staging.  64 detectors x 2^20 samples, lambda = 8192: 540 us with the
-// LDS-resident transform (one 1,024-thread workgroup per CU), 244 us here, bound by the
+// LDS-resident transform (one 1,024-thread workgroup per CU), 238 us here, bound by the
 // transform's VALU issue.  (One kernel for all three, not a shared function: the rounding of the
 // fused products then stays what it is.)
 template <int IO>

@@ -75,9 +75,10 @@ __device__ __forceinline__ double group_total(const double* p, int n, double* sh
 // one wait, instead of sinking below the tests they do not depend on.
 __device__ __forceinline__ void pin(double& v) { asm volatile("" : "+v"(v)); }
 
-// Scalars of the recurrence: every wavefront of the kernel that needs alpha or beta sums the
+// Scalars of the recurrence: every workgroup of the kernel that needs alpha or beta sums the
 // previous kernel's per-workgroup partials itself, in the same fixed order, so all of them hold
-// the same value (the kernel boundary makes the partials visible; no fence, counter or barrier).
+// the same value (the kernel boundary makes the partials visible; no fence or counter): up to 128
+// partials by each of its wavefronts, without a barrier, more by its wavefronts together, with one.
 // Workgroup 0 alone records the scalars in the state; the state fields that the other
 // workgroups read in that kernel were written one kernel earlier.
 //

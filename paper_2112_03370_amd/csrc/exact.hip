@@ -314,7 +314,7 @@ __global__ __launch_bounds__(kXThreads) void k_x_scatter(
 // (FP64 issue 5 us each, LDS moves 5 us each, the rest barriers between them), spectrum 5, staging
 // 3, scatter 7.  64 detectors x 2^20 samples, lambda = 8192: 1,073 us with an exchange back to the
 // first pass's slots between the transforms (8.5 us per segment) and outputs staged in sample
-// order (6 us), 957 us here.  Short bands, whose segments kept more than NC outputs and therefore
+// order (6 us), 966 us here.  Short bands, whose segments kept more than NC outputs and therefore
 // ran the batched passes: lambda = 100 (N = 2048) 2,456 -> 516 us, 800 3,289 -> 681, 2000
 // 3,725 -> 828, 12001 3,628 -> 1,750.
 template <int M>
@@ -600,8 +600,10 @@ __global__ __launch_bounds__(XFused<M>::T) void k_x_fused(
   // Staged from point `first` on in two planes (even and odd samples), so that a wavefront writes
   // consecutive values.  At most NC outputs are staged at once; more (kWide) in the window's two
   // halves, slots 0 .. 7 and then 8 .. 15, the second of which then stays live through the first
-  // half's scatter: at M = 14, whose 1,024 threads leave 128 registers each, 53 of them would
+  // half's scatter: at M = 14, whose 1,024 threads leave 128 registers each, some 50 of them
   // spill, and a product of 64 x 2^20 samples with lambda = 8192 takes 1,143 us instead of 954.
+  // Segments with more outputs have no narrow form; wide, with the spills, they take a third of the
+  // batched passes' time (32 x 2^18 samples, lambda = 5000 410 -> 161 us, 8000 510 -> 170 us).
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
 #pragma unroll
   for (int h = 0; h < (kWide ? 2 : 1); ++h) {

@@ -242,7 +242,9 @@ __device__ __forceinline__ void symbol_multiply(float2* buf, const float* __rest
       const float sig = a + b, del = a - b;
       // The fused multiply-adds are written out: left to contraction, which of these are fused
       // (and with them the last bit of a few bins) changes with unrelated edits of the kernels.
-      // The first pair's p2 (every pair's in one-wavefront segments) rounds its product first.
+      // The first pair's p2 (every pair's in one-wavefront segments) rounds its product first: not
+      // for its accuracy, which either form has, but as it has been, so that the FP32 products give
+      // the bits they gave before they were written out.
       const float p = fmaf(del, W[r].y, sig);  // sig - 2 delta s
       const float p2 = T == 64 || r0 + r == 0 ? minus_product(sig, del, W[r].y)
                                               : fmaf(-del, W[r].y, sig);

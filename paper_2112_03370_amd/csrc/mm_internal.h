@@ -109,7 +109,7 @@ struct Timing {
 };
 
 
-// Per-solve device workspace: time-domain buffers (unfused and direct products), long-segment
+// Per-solve device workspace: time-domain buffers (unfused products only), long-segment
 // tiles, the PCG vectors and scalars.  A plan holds one for the plain calls; a server gives every
 // running request its own, so that solves on one plan can overlap.
 // An instantiated graph of `chunk` PCG iterations, as captured for one solution vector and

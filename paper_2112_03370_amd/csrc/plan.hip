@@ -689,8 +689,8 @@ bool needs_time_buffers(const Plan* P) {
 }
 
 int32_t reduction_blocks(int64_t n_kept) {
-  // a pixel per thread up to 512 workgroups (two per CU; every wavefront sums all partials, so
-  // more would cost more than they hide), then four pixels per thread
+  // a pixel per thread up to 512 workgroups (two per CU; every workgroup of the next kernel sums all
+  // partials, so more would cost more than they hide), then four pixels per thread
   const int64_t one = std::min<int64_t>((n_kept + 255) / 256, 512);
   const int64_t four = std::min<int64_t>((n_kept + 1023) / 1024, 1024);
   return static_cast<int32_t>(std::max<int64_t>({one, four, 1}));

@@ -3,14 +3,13 @@
 //
 // Layout: per-sample arrays are separate coalesced streams (local pixel int32, cos/sin FP32);
 // each thread owns 8 consecutive samples, read with two 16-byte loads per stream (at any 4-byte
-// alignment).  Pixel-domain
-// vectors are FP64 [n_kept][3] and stay cache-resident while the time streams go by; the
-// un-pointing loads the pixels of a thread's first and last samples together and a third pixel
-// only when one occurs (scan runs make that rare), since these kernels are bound by the count
-// and the latency of vector memory instructions rather than by bytes.  P^T accumulates in FP64: samples of one
-// pixel arrive in runs (the scan dwells on a pixel for several samples), so each thread first
-// sums its own run pieces, then a wavefront segmented scan merges runs that continue across
-// lanes, and only the lane that closes a run issues the three FP64 atomic adds.
+// alignment).  Pixel-domain vectors are FP64 [n_kept][3] and stay cache-resident while the time
+// streams go by; the un-pointing loads the pixels of a thread's first and last samples together and
+// a third pixel only when one occurs (scan runs make that rare), since these kernels are bound by the
+// count and the latency of vector memory instructions rather than by bytes.  P^T accumulates in
+// FP64: samples of one pixel arrive in runs (the scan dwells on a pixel for several samples), so each
+// thread first sums its own run pieces, then a wavefront segmented scan merges runs that continue
+// across lanes, and the completed runs are listed and added by one FP64 atomic per lane.
 #include "mm_internal.h"
 #include "segment_io.h"
 #include "wave_runs.h"

@@ -5,9 +5,8 @@
 // for diagonal weights W^-1 and Legendre baselines (Appendix A, Eq. polytemplate): on every
 // baseline interval of L samples the templates are sqrt((2k+1)/L) P_k(x_j), k < n_poly, at the
 // midpoints x_j = (2j+1)/L - 1.  The orthogonalisation kernel T^T W^-1 T is block-diagonal, one
-// n_poly x n_poly block per baseline, built on the device in FP64 at plan time and
-// pseudo-inverted on the host (eigen-directions below 1e-12 of the largest dropped, the paper's
-// SVD threshold).  A baseline lies inside one stationary interval (or outside all of them), so
+// n_poly x n_poly block per baseline, built and pseudo-inverted on the device in FP64 at plan
+// time (eigen-directions below 1e-12 of the largest dropped, the paper's SVD threshold).  A baseline lies inside one stationary interval (or outside all of them), so
 // its weight w is the c_0 of that interval's band; gap samples (flagged or excised) weigh 0.
 //
 // The product runs as one kernel, one workgroup per baseline, every step in FP64:
@@ -25,7 +24,9 @@
 // What bounds it: the chain table entry -> pointing -> pixels -> sums -> coefficients -> pointing
 // sums, whose waits 16 wavefronts per CU have to cover, then the FP64 instructions.  128 detectors
 // x 2^20 samples, baselines of 8,192, 3 templates: 896 us with 4 samples per lane, all of them in
-// registers and the scaled Legendre recurrence twice per sample; 517 us here (3.1 TB/s of pointing).
+// registers and the scaled Legendre recurrence twice per sample; 501 us here (3.2 TB/s of pointing).
+// The registers spilled at 512 threads cost traffic: 5.7 GB per 2^28 samples, 4.9 GB with 4 samples
+// per lane and no spills; eight wavefronts per CU and no spills 4.1 GB, but 1,197 us against 996.
 // Re-reading the pointing in 3 instead of holding it: 762 us (the reads come late, not from HBM).
 // t in registers instead of LDS: 889 us (spills).  One workgroup size for all baselines
 // left the short ones with idle wavefronts: 64 x 2^19 samples, baselines of 500 (3 templates)
@@ -126,9 +127,13 @@ __device__ __forceinline__ void subtract(double (&t)[kLane], double x0, double d
 }
 
 // Wavefronts per SIMD: 512 threads need four for two workgroups per CU and spill some of their
-// registers for it (25 at three templates); smaller workgroups fill a CU with three and no spills,
-// which is faster where four would spill much: 64 x 2^19 samples, 3 templates, baselines of 3,000
-// 180 -> 153 us, but 1 template, baselines of 600 154 -> 173 us.
+// registers for it (25 at three templates, 52 to 65 at four to seven, 115 at eight).  With room for
+// two and no spills, 128 x 2^19 samples and baselines of 8,192 take 316 us instead of 263 (3
+// templates), 337 for 289 (4), 361 for 301 (5), 380 for 335 (6), 405 for 379 (7), 424 for 407 (8; of
+// 16,384 samples 391 for 404), but with one template, where nothing spills, 182 for 203.
+// Smaller workgroups fill a CU with three and no spills, which is faster where four would spill
+// much: 64 x 2^19 samples, 3 templates, baselines of 3,000 180 -> 153 us, but 1 template, baselines
+// of 600 154 -> 173 us.
 template <int NP, int T>
 constexpr int template_waves() {
   return T == 512 || NP < 3 ? 4 : 3;

@@ -248,8 +248,9 @@ __device__ __forceinline__ void drain_lane(const LongArgs& a, const SegmentStrea
         if (o + j >= 0 && o + j < c.out_len) a.u[c.out0 + o + j] = v[j];
     }
   } else {
-    // rows of the window's overhang (half of them at N = 4 lambda): nothing to merge.  (Bridging and
-    // merging them cost the right-hand side of 8 x 2^20 samples, lambda = 2^14, 3 us of 138.)
+    // rows of the window's overhang (half of them at N = 4 lambda): nothing to merge (bridged and
+    // merged all the same, the right-hand side of 8 x 2^20 samples, lambda = 2^15, took 239.2 us
+    // instead of 236.5)
     if (!__any(o > -kLane && o < c.out_len)) return;
     LanePointing<kLane, false> lane;
     lane.load(win, a.lam + o, a.lam, a.lam + c.out_len);
