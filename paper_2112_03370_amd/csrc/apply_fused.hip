@@ -86,6 +86,13 @@ __global__ __launch_bounds__(FftCfg<LOG>::T) void k_apply_fused(
   // lambda = 512, 18 detectors x 2^17 samples, a solve takes 1,236 us against 1,264 with one; all
   // four at once take 208 registers and 1,477 us.
   constexpr int kDeep = LOG <= 13 ? 2 : 1;
+  // Scans aligned to the lanes (one pixel a lane) have one sum per sample instead of two, where the
+  // branch costs no registers that matter: in 1,024-thread workgroups, which are capped at 128 and,
+  // one to a CU, bound by vector instructions.  256 detectors x 2^20 samples on 16-sample runs,
+  // lambda = 8000 2,172 -> 2,078 us, 6000 2,279 -> 2,195 us; smaller workgroups would pass 128
+  // registers and lose a wavefront per SIMD (lambda = 4000 1,746 -> 2,577 us).  In the scatter it
+  // costs none anywhere (lambda = 2000 1,524 -> 1,486 us, 500 1,517 -> 1,475 us).
+  constexpr bool kOnePixel = LOG == 14;
   static_assert(N == 4 * T * SG, "four gather rounds");
   const int rot = ((wg / ncol) & 1) == 0 ? 2 : 0;
   for (int rr = 0; rr < 4; rr += kDeep) {
@@ -102,7 +109,7 @@ __global__ __launch_bounds__(FftCfg<LOG>::T) void k_apply_fused(
 #pragma unroll
     for (int e = 0; e < kDeep; ++e) {
       float v[SG];
-      lane[e].finish(x, px[e], v);
+      lane[e].template finish<kOnePixel>(x, px[e], v);
       // samples n..n+SG-1 are complex points n/2.. (n/2 even: contiguous pairs after padding)
       float2* dst = buf + pad(n[e] >> 1);
 #pragma unroll
@@ -151,7 +158,7 @@ __global__ __launch_bounds__(FftCfg<LOG>::T) void k_apply_fused(
     lane.bridge_flags(u);
     int at = pad(((lam + base + 64 * SS * wave) >> 1) + 1);
     if constexpr (T == 64) at = min(at, kBuf - kListPoints);
-    wave_point_runs<SS, kListed>(lane.kk, lane.qq, lane.uu, u, flush, buf + at);
+    wave_point_runs<SS, kListed, true>(lane.kk, lane.qq, lane.uu, u, flush, buf + at);
   }
 }
 

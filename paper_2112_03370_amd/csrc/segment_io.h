@@ -185,21 +185,29 @@ struct LanePointing {
     }
   }
 
-  template <class T>
+  // kOnePixel: wavefronts whose lanes all see one pixel form one sum per sample instead of two.
+  template <bool kOnePixel = false, class T>
   __device__ __forceinline__ void finish(const double* __restrict__ x, Pixels& f,
                                          T (&v)[S]) const {
     if constexpr (kFromData) {
 #pragma unroll
       for (int j = 0; j < S; ++j) v[j] = kk[j] < 0 ? T(0) : static_cast<T>(qq[j]);
     } else {
+      if (kOnePixel && !__any(f.kb != f.ka)) {
 #pragma unroll
-      for (int j = 0; j < S; ++j) {
-        // both candidate pixels' sums, then one select (cheaper than selecting three FP64
-        // pixel values)
-        const double q = static_cast<double>(qq[j]), u = static_cast<double>(uu[j]);
-        const double ta = f.a[0] + q * f.a[1] + u * f.a[2];
-        const double tb = f.b[0] + q * f.b[1] + u * f.b[2];
-        v[j] = static_cast<T>(kk[j] == f.ka ? ta : tb);
+        for (int j = 0; j < S; ++j)
+          v[j] = static_cast<T>(f.a[0] + static_cast<double>(qq[j]) * f.a[1] +
+                                static_cast<double>(uu[j]) * f.a[2]);
+      } else {
+#pragma unroll
+        for (int j = 0; j < S; ++j) {
+          // both candidate pixels' sums, then one select (cheaper than selecting three FP64
+          // pixel values)
+          const double q = static_cast<double>(qq[j]), u = static_cast<double>(uu[j]);
+          const double ta = f.a[0] + q * f.a[1] + u * f.a[2];
+          const double tb = f.b[0] + q * f.b[1] + u * f.b[2];
+          v[j] = static_cast<T>(kk[j] == f.ka ? ta : tb);
+        }
       }
       if (f.flagged) {
 #pragma unroll

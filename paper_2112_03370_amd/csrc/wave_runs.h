@@ -244,8 +244,9 @@ __device__ __forceinline__ void wave_merge_runs_listed(const int (&key)[SPL],
 // samples), a lane's two sums are formed without branches: each sample counts in one of them and
 // as a zero in the other.  The walk executes both sides of its branch at nearly every sample, since
 // some lane of 64 changes pixel there, with the products formed beforehand: about twice the
-// instructions, in kernels that are bound by the issue of vector instructions.
-template <int SPL, int CAP, class T, class Flush>
+// instructions, in kernels that are bound by the issue of vector instructions.  kOnePixel: one sum
+// per lane where no lane sees a second pixel.
+template <int SPL, int CAP, bool kOnePixel = false, class T, class Flush>
 __device__ __forceinline__ void wave_point_runs(const int (&key)[SPL], const float (&q)[SPL],
                                                 const float (&w)[SPL], const T (&u)[SPL],
                                                 const Flush& flush, void* at) {
@@ -260,7 +261,20 @@ __device__ __forceinline__ void wave_point_runs(const int (&key)[SPL], const flo
   };
   int r_in = 0, in_base = 0;
   LaneRuns<3> r;
-  if (!__any(changes > 1)) {  // wavefront-uniform
+  if (kOnePixel && !__any(changes > 0)) {  // wavefront-uniform
+    r.single = true;
+    r.hk = -1;
+    r.tk = key[0];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) r.head[c] = r.acc[c] = 0.0;
+#pragma unroll
+    for (int j = 0; j < SPL; ++j) {
+      const double t = static_cast<double>(u[j]);
+      r.acc[0] += t;
+      r.acc[1] = fma(static_cast<double>(q[j]), t, r.acc[1]);
+      r.acc[2] = fma(static_cast<double>(w[j]), t, r.acc[2]);
+    }
+  } else if (!__any(changes > 1)) {  // wavefront-uniform
     r.single = changes == 0;
     r.hk = r.single ? -1 : key[0];
     r.tk = key[SPL - 1];
